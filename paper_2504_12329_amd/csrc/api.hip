@@ -120,7 +120,6 @@ enum PrefillMode { kPassDefault, kPassTwoTerm, kPassFast };
 static void set_pass_mode(Model *m, PrefillMode mode) {
     m->long_terms = mode == kPassFast ? 0 : kDefaultLongTerms;
     m->f16_pass = mode == kPassDefault && m->f16_on;
-    m->ring_min_rows = (mode == kPassFast || m->f16_pass) ? kRingMinRowsFast : kRingMinRows;
 }
 static int prefill_impl(Model *m, const int32_t *tokens, int32_t n, bool tokens_dev, const st_trigger_rule *rule,
                         PrefillMode mode = kPassDefault) {
@@ -323,10 +322,11 @@ int st_prefill_plan_check(const st_config *cfg, int32_t rows, int32_t *launches,
     if (rows <= 0 || rows > cfg->max_chunk) return fail(ST_ERANGE, "rows %d outside 1..max_chunk", rows);
     if (launches) *launches = 0;
     if (blocks) *blocks = 0;
-    if (rows < kRingMinRowsFast) return ST_OK;  // shorter chunks take the streaming kernel: one tile list, no leftovers
+    if (rows < kRingMinRows) return ST_OK;  // shorter chunks take the streaming kernel: one tile list, no leftovers
     const int h = cfg->hidden, I = cfg->intermediate, qd = cfg->n_q_heads * cfg->head_dim;
     const int qkv = (cfg->n_q_heads + 2 * cfg->n_kv_heads) * cfg->head_dim;
     const long long cap = (long long)partial_floats(*cfg);
+    constexpr int kPlanCountRows = 193;  // shorter passes are walked, but report no launches
     const struct {
         const char *name;
         int dual, N, K;
@@ -337,15 +337,15 @@ int st_prefill_plan_check(const st_config *cfg, int32_t rows, int32_t *launches,
               {"down", 0, h, I, (kDefaultLongTerms & kTermDown) != 0}};
     for (const auto &e : g) {
         if (e.K % 64 || e.K < 128) continue;  // the general-shape kernel serves such a K
-        // a projection whose input carries two bf16 terms runs the doubled contraction [A | Alo] x [B | B]: the
-        // plans of both forms are walked
+        // a projection whose input carries two bf16 terms runs on tiles of half the rows: the plans of both forms are walked
         for (int terms = 1; terms <= 2; ++terms) {
             int nl = 0, nb = 0, ni = 0;
-            const int rc = ring_plan_check(e.dual, rows, e.N, terms * e.K, cap, 1, &nl, &nb, &ni);
+            const int rc = ring_plan_check(e.dual, terms == 2, rows, e.N, e.K, cap, 1, &nl, &nb, &ni);
             if (rc)
                 return fail(ST_EINVAL, "block plan of the %s projection at %d rows (%d-term input) fails check %d",
                             e.name, rows, terms, rc);
-            if (terms != (e.def_two ? 2 : 1)) continue;  // the counts reported are the default pass's
+            // the counts reported are the default pass's
+            if (terms != (e.def_two ? 2 : 1) || rows < kPlanCountRows) continue;
             if (launches) *launches += nl;
             if (blocks) *blocks += nb;
         }
@@ -394,7 +394,6 @@ static int build_model(const st_config *cfg, const st_weights *w, void *kv, void
     m->graphs_off = getenv("ST_NO_GRAPH") != nullptr;
     m->graph_failed = false;
     m->long_terms = kDefaultLongTerms;
-    m->ring_min_rows = kRingMinRows;
     m->f16_on = m->f16_pass = false;
     static std::once_flag lds_once;
     static hipError_t lds_rc = hipSuccess;

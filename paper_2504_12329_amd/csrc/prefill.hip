@@ -340,24 +340,36 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(const bf16_t *__restric
 }
 
 // ---------------------------------------------------------------------------------------
-// Long chunks: the same contraction with a 256 x 256 block tile, K step 64, on four waves that each own
-// a 128 x 128 tile (256 accumulator registers), built around the three limits measured on this chip:
+// Longer chunks: the same contraction with a block tile of up to 256 LDS rows of activations x 256 weight rows, K step
+// 64, built around the limits measured on this chip:
 //   * tile traffic from L2 moves about 40 % faster in whole 128-byte lines, hence K step 64;
-//   * LDS delivers 128 bytes per clock, so fragments are read once per 128 x 128 wave tile (half the
-//     LDS bytes per MFMA of a 128 x 64 wave tile), from rows whose 16-byte chunks are XOR-swizzled so
-//     that the reads are conflict-free without padding;
+//   * LDS serves a 16-byte read in four clocks if its lanes are spread right (ring_swz), and fragments are read once per
+//     wave tile;
 //   * the vector memory path accepts one 1 KB load per 16 clocks per CU and stalls the issuing wave
 //     beyond that, and with one wave per SIMD a stalled wave is an idle MFMA pipe.  Tiles therefore
-//     go global -> LDS directly (no staging registers), one load instruction per four MFMAs, all
-//     through the K loop.  That needs slots freed early: the ring has five 32 KB slots, one operand of
-//     one K step each (A0 B0 A1 B1 A2 ...), so loads run up to two and a half steps ahead of the math.
-// Per K step of 64: 64 MFMAs, 32 fragment reads (fetched one 16-wide step ahead into a second register
-// set), 16 direct loads and one barrier.  Needs K % 64 == 0 and at least two steps per K slice.
+//     go global -> LDS directly (no staging registers), spread over the K loop, or from waves of their own.  That needs
+//     slots freed early: the ring has five 32 KB slots, one operand of one K step each (B0 A0 B1 A1 B2 ...), so loads run
+//     up to two and a half steps ahead of the math.
+// Two-term activations put the high and the low terms of 128 rows into the 256 LDS rows, and both meet the same weight
+// fragment: per K step of 64 the same 64 MFMAs per wave, and the same bytes, as 256 rows of one term, but half the
+// accumulators (so that four loading waves fit beside the four multiplying ones), row tiles half as high, and the K
+// loop once instead of twice ([A | Alo] x [B | B], as it was).  Row tiles of a launch have equal heights in steps of 32
+// (one term: 64) rows: 386 rows are four tiles of 128 + 96 + 96 + 96, not two of 256.  Before and after, four layers on
+// 512 cached keys, two terms: 7B shape 300 / 386 / 700 rows 2219 / 2256 / 2905 -> 1531 / 1835 / 2571 us, 1.5B shape 256 /
+// 512 rows 843 / 927 -> 562 / 785 us.  A K step of a full tile takes 1.5-1.7 us: MFMA pipes 78 % busy at the 1.7 GHz the
+// chip then runs at (its power limit: neither loads from waves of their own nor half the LDS cycles moved it by more
+// than 1 %).
+// Needs K % 64 == 0 and at least two steps per K slice.
 // ---------------------------------------------------------------------------------------
 constexpr int kRingBK = 64, kRingSlot = 256 * kRingBK * 2, kRingSlots = 5;
 constexpr int kRingLds = kRingSlot * kRingSlots;  // 160 KB: all of a CU's LDS
 
-__device__ __forceinline__ int ring_swz(int row) { return (row + (row >> 3)) & 7; }
+// Position of 16-byte chunk c of LDS row `row` (128-byte rows): c ^ ring_swz(row).  A 16-byte LDS read is served in four
+// cycles of 16 lanes, lanes {0-3, 12-15, 20-27}, {4-11, 16-19, 28-31} and the same of the upper half (found by timing
+// every pair of lanes against each other), over 64 banks of four bytes = two rows: among the eight even (odd) rows of
+// each set row / 2 takes every value mod 8.  The earlier (row + row / 8) & 7, made for sets of consecutive lanes,
+// cost two cycles where one does: 8.0 against 4.5 clocks per read.
+__device__ __forceinline__ int ring_swz(int row) { return (row >> 1) & 7; }
 
 // 64 lanes x 16 bytes from per-lane global addresses to 1 KB of LDS starting at lds_off (wave-uniform)
 __device__ __forceinline__ void load_to_lds16(const void *g, uint32_t lds_off) {
@@ -396,6 +408,7 @@ __device__ __forceinline__ void static_for(F &&f) {  // f(ic<0>{}), ..., f(ic<N-
 // tail_kps columns; a unit is one slice of 32 tiles (column-major) and unit u runs on XCD u % 8.
 struct RingGrid {
     int My, Nx, x0, TY, TX, S, kps, per, blocks;  // x0: column tile of the launch's first column (in its own tiles)
+    int h_base, h_extra;                          // heights of the row tiles (see ring_units)
     int tail_x0, tail_tiles, tail_s, tail_kps;
 };
 // What block `bid` of a launch works on: tile (x, y) in the launch's own tiles (x before adding x0), K range
@@ -442,248 +455,312 @@ __host__ __device__ inline bool ring_block(const RingGrid &gg, int bid, int M, i
     return true;
 }
 
-// HALF (fused SwiGLU form only): the block tile is 256 x (64 gate + 64 up) weight rows -- half the columns, half the
-// MFMAs per fragment of activations -- for the tiles left over after whole rounds of full tiles (one more round of
-// half the length instead of a round that leaves half the chip idle).
-// F16: A and B hold fp16 numbers (single-term activations, the model's fp16 copy of the weights).  out_f16: the
-// fused epilogue writes fp16 (one term) instead of bf16 (+ its low term).
-template <bool DUAL, bool HALF = false, bool F16 = false>
-__global__ __launch_bounds__(256) void k_gemm_ring(const bf16_t *__restrict__ A, const bf16_t *__restrict__ Alo, int lda,
-                                                   const bf16_t *__restrict__ B, int M, int N, int K,
-                                                   float *__restrict__ part, bf16_t *__restrict__ outb,
-                                                   bf16_t *__restrict__ outlo, int ldo, RingGrid gg, int out_f16) {
-    extern __shared__ __align__(16) unsigned char ring[];
-    RingBlock rb;
-    // Two-term activations (Alo != nullptr): the contraction runs over 2K columns, [A | Alo] against [B | B]; K step
-    // ka >= K / 64 takes its activations from Alo and wraps round in the weights.
-    if (!ring_block(gg, blockIdx.x, M, N, Alo ? 2 * K : K, &rb)) return;
-    const int x = rb.x, y = rb.y, kbeg = rb.kbeg, kend = rb.kend, ldp = rb.ldp;
-    float *pz = DUAL ? nullptr : part + rb.part_off;  // where this block's fp32 tile goes (plain form)
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
-    const int l32 = lane & 31, kg = lane >> 5;
-    static_assert(DUAL || !HALF, "the half-width tile exists for the fused form only");
-    constexpr int NB = HALF ? 2 : 4;   // 32-row weight fragments per wave
-    constexpr int NLB = HALF ? 4 : 8;  // direct loads per wave for one weight slot
-    const int m0 = y * 256, n0 = (x + gg.x0) * (HALF ? 64 : DUAL ? 128 : 256);
-    const int nk = (kend - kbeg) / kRingBK;
+// Rows of tile y: the rows of a launch are dealt to the My row tiles in units of kUnit (32 rows with two terms, 64 with
+// one), as evenly as they go: the first h_extra tiles have h_base + 1 units, the others h_base (at most four).
+__host__ __device__ inline int ring_units(const RingGrid &gg, int y) { return gg.h_base + (y < gg.h_extra ? 1 : 0); }
+__host__ __device__ inline int ring_row0(const RingGrid &gg, int y, int unit) {
+    return unit * (y * gg.h_base + (y < gg.h_extra ? y : gg.h_extra));
+}
+
+// The block's tile: NF activation fragments of 32 LDS rows (one term: NF * 32 rows; two terms: NF * 16 rows, the high
+// terms in the first NF / 2 fragments, the low terms in the rest) against 256 weight rows (HALF: 128).  Full height:
+// four multiplying waves as 2 x 2; lower tiles: as 1 x 4, every wave all activation rows against a quarter of the weight
+// rows, so that all of them get shorter with the tile (at full height 2 x 2 reads fewer fragments per MFMA: 3-4 % faster).
+// HALF: half the columns and half the MFMAs per fragment of activations, for launches that full tiles would leave
+// short of blocks, and for the tiles left over after whole rounds of full tiles.
+template <int NF, bool DUAL, bool HALF, int TERMS, bool F16>
+__device__ __forceinline__ void ring_tile(unsigned char *ring, const bf16_t *__restrict__ A, const bf16_t *__restrict__ Alo,
+                                          int lda, const bf16_t *__restrict__ B, int M, int N, int K, float *__restrict__ pz,
+                                          int ldp, bf16_t *__restrict__ outb, bf16_t *__restrict__ outlo, int ldo, int m0,
+                                          int n0, int kbeg, int nk, int out_f16) {
+    static_assert(TERMS == 1 || !F16, "two terms are bf16");
+    constexpr bool SPEC = TERMS == 2;  // waves 4-7 load, waves 0-3 multiply
+    constexpr int WM = NF == 8 ? 2 : 1, WN = 4 / WM, TB = HALF ? 128 : 256;
+    constexpr int NB = TB / WN / 32;   // 32-row weight fragments per wave
+    constexpr int NLA = NF, NLB = HALF ? 4 : 8;  // direct loads per loading wave for one activation / weight slot
+    constexpr int NI = NF / TERMS, NIW = NI / WM;  // 32-row tiles of the block; of a wave
+    constexpr bool GU16 = HALF && DUAL && WM == 1;  // a wave's one weight fragment holds 16 gate and 16 up rows
+    const int tid = threadIdx.x, lane = tid & 63, wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool loader = SPEC && wave8 >= 4;
+    const int wave = wave8 & 3, wm = wave / WN, wn = wave % WN, l32 = lane & 31, kg = lane >> 5;
     const uint32_t ring0 = (uint32_t)(uintptr_t)ring;  // LDS byte offset of the ring (low half of the flat address)
 
-    // direct loads: instruction i of a wave fills LDS rows [(wave*8+i)*8, +8) of a slot, lane -> (row lane/8,
+    // direct loads: instruction i of a wave fills LDS rows [(wave*NL+i)*8, +8) of a slot, lane -> (row lane/8,
     // 16-byte position lane%8, which holds global chunk position ^ swizzle(row)); rows past the edge re-read
     // the last valid row (their results are never stored)
-    uint32_t pa[8], pb[NLB];  // byte offsets from A / B (every operand of the library is far below 4 GB)
+    uint32_t pa[NLA], pb[NLB];  // byte offsets from A / B (every operand of the library is far below 4 GB)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int row = (wave * 8 + i) * 8 + (lane >> 3);
+    for (int i = 0; i < NLA; ++i) {
+        const int row = (wave * NLA + i) * 8 + (lane >> 3);
         const int c = (lane & 7) ^ ring_swz(row);
-        pa[i] = (uint32_t)(((size_t)min(m0 + row, M - 1) * lda + c * 8) * sizeof(bf16_t));
+        pa[i] = (uint32_t)(((size_t)min(m0 + row % (NI * 32), M - 1) * lda + c * 8) * sizeof(bf16_t));
     }
 #pragma unroll
     for (int i = 0; i < NLB; ++i) {
         const int row = (wave * NLB + i) * 8 + (lane >> 3);
         const int c = (lane & 7) ^ ring_swz(row);
         int bn;
-        if (HALF)  // rows 0..63 of the tile are gate rows, 64..127 the matching up rows
-            bn = min(n0 + (row & 63), N - 1) + (row >> 6) * N;
-        else if (DUAL)  // rows 0..127 of the tile are gate rows, 128..255 the matching up rows (N = I)
-            bn = min(n0 + (row & 127), N - 1) + (row >> 7) * N;
+        if (GU16)
+            bn = min(n0 + (row >> 5) * 16 + (row & 15), N - 1) + ((row >> 4) & 1) * N;
+        else if (DUAL)  // the first half of the tile are gate rows, the second the matching up rows (N = I)
+            bn = min(n0 + row % (TB / 2), N - 1) + row / (TB / 2) * N;
         else
             bn = min(n0 + row, N - 1);
         pb[i] = (uint32_t)(((size_t)bn * K + c * 8) * sizeof(bf16_t));
     }
-    // the K position of a step is a wave-uniform base (scalar registers), the lane offsets above never change
-    const int nkw = K / kRingBK, k0 = kbeg / kRingBK;  // K steps of the weights; first step of this block
-    auto baseA = [&](int kt) {
-        const int ka = k0 + kt;
-        return ka < nkw ? A + (size_t)ka * kRingBK : Alo + (size_t)(ka - nkw) * kRingBK;
-    };
-    auto baseB = [&](int kt) {
-        const int ka = k0 + kt;
-        return B + (size_t)(ka < nkw ? ka : ka - nkw) * kRingBK;
-    };
+    // the K position of a step is a wave-uniform base (scalar registers), the lane offsets above never change;
+    // with two terms waves 2 and 3 fill the low half of the activation slot
+    const bf16_t *Aw = (TERMS == 2 && wave >= 2 ? Alo : A) + kbeg, *Bw = B + kbeg;
     auto loadA = [&](auto i_c, int slot, const bf16_t *base) {
         constexpr int i = decltype(i_c)::value;
-        load_to_lds16(base, pa[i], ring0 + slot * kRingSlot + (wave * 8 + i) * 1024);
+        load_to_lds16(base, pa[i], ring0 + slot * kRingSlot + (wave * NLA + i) * 1024);
     };
     auto loadB = [&](auto i_c, int slot, const bf16_t *base) {
         constexpr int i = decltype(i_c)::value;
-        if constexpr (i < NLB) load_to_lds16(base, pb[i], ring0 + slot * kRingSlot + (wave * NLB + i) * 1024);
+        load_to_lds16(base, pb[i], ring0 + slot * kRingSlot + (wave * NLB + i) * 1024);
     };
+    auto next_slot = [](int s, int d) { return s + d >= kRingSlots ? s + d - kRingSlots : s + d; };
 
-    f32x16 acc[4][NB];
+    // Ring order B0 A0 B1 A1 B2 ...: after K step kt the slots of B(kt) and A(kt) take A(kt+2) and B(kt+3) (loading
+    // waves), or A(kt+2) and, under the next step, B(kt+3) (waves that do both).
+    if constexpr (SPEC) {
+        if (loader) {
+            static_for<NLB>([&](auto i_c) { loadB(i_c, 0, Bw); });
+            static_for<NLA>([&](auto i_c) { loadA(i_c, 1, Aw); });
+            static_for<NLB>([&](auto i_c) { loadB(i_c, 2, Bw + kRingBK); });
+            static_for<NLA>([&](auto i_c) { loadA(i_c, 3, Aw + kRingBK); });
+            if (nk > 2) {
+                static_for<NLB>([&](auto i_c) { loadB(i_c, 4, Bw + 2 * kRingBK); });
+                wait_loads<2 * NLB + NLA>();  // B0 and A0 are in
+            } else {
+                wait_loads<NLB + NLA>();
+            }
+            __builtin_amdgcn_s_barrier();
+            const bf16_t *an = Aw + 2 * kRingBK, *bn = Bw + 3 * kRingBK;
+            int slot = 0;
+            for (int kt = 0; kt + 1 < nk; ++kt) {
+                if (kt >= 1) {  // A(kt+1), B(kt+2) into the slots of B(kt-1), A(kt-1)
+                    static_for<NLA>([&](auto i_c) { loadA(i_c, slot, an); });
+                    slot = next_slot(slot, 1);
+                    if (kt + 2 < nk) static_for<NLB>([&](auto i_c) { loadB(i_c, slot, bn); });
+                    slot = next_slot(slot, 1);
+                    an += kRingBK, bn += kRingBK;
+                }
+                if (kt + 2 < nk) wait_loads<NLB>(); else wait_loads<0>();  // A(kt+1) and B(kt+1) are in
+                __builtin_amdgcn_s_barrier();
+            }
+            return;
+        }
+    }
+
+    f32x16 acc[NIW][NB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NIW; ++i)
 #pragma unroll
         for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    // fragment reads: lane (row l32, K half kg) of 32-row block t reads chunk (2*ks + kg) ^ swizzle; the
-    // swizzle of row 32*t + l32 is swizzle(l32) ^ 4*(t & 1)
-    const int a_off = (wm * 128 + l32) * 128;
+    // fragment reads: lane (row l32, K half kg) of 32-row block t reads chunk (2*ks + kg) ^ swizzle(l32)
+    constexpr int NBH = NB > 1 ? NB / 2 : 1;  // fused form: weight fragments j and j + NBH are gate and matching up rows
     int b_off[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j)
-        b_off[j] = (HALF   ? (j * 64 + wn * 32 + l32)
-                    : DUAL ? ((j >> 1) * 128 + wn * 64 + (j & 1) * 32 + l32)
-                           : (wn * 128 + j * 32 + l32)) * 128;
-    const int ch_even = (kg ^ ring_swz(l32)) * 16, ch_odd = ch_even ^ 64;
-    const int ch_half = wn ? ch_odd : ch_even;  // HALF: both weight fragments of a wave sit in 32-row block wn or 2 + wn
+        b_off[j] = (DUAL && !GU16 ? j / NBH * (TB / 2) + (wn * NBH + j % NBH) * 32 + l32 : (wn * NB + j) * 32 + l32) * 128;
+    const int a_off = (wm * NIW * 32 + l32) * 128, ch0 = (kg ^ ring_swz(l32)) * 16;
 
-    u32x4 fa[2][4], fb[2][NB];
-    // fragment q of a 16-wide step: q = 0..3 weight fragments (0..1 with HALF), 4..7 activation fragments
+    constexpr int NFW = NF / WM, NM = NFW * NB, NR = NFW + NB;  // fragments of activations, MFMAs and reads of a 16-wide step
+    u32x4 fa[2][NFW], fb[2][NB];
+    // read q of a 16-wide step: the weight fragments, then the activation fragments
     auto fetch = [&](auto buf_c, auto q_c, int slotA, int slotB, int ks) {
         constexpr int buf = decltype(buf_c)::value, q = decltype(q_c)::value;
-        if constexpr (q < 4) {
-            if constexpr (q < NB) {
-                const int ch = (HALF ? ch_half : (q & 1) ? ch_odd : ch_even) ^ (ks * 32);
-                fb[buf][q] = *reinterpret_cast<const u32x4 *>(ring + slotB * kRingSlot + b_off[q] + ch);
-            }
-        } else {
-            const int ch = ((q & 1) ? ch_odd : ch_even) ^ (ks * 32);
-            fa[buf][q & 3] = *reinterpret_cast<const u32x4 *>(ring + slotA * kRingSlot + a_off + (q & 3) * 4096 + ch);
-        }
+        const int ch = ch0 ^ (ks * 32);
+        if constexpr (q < NB)
+            fb[buf][q] = *reinterpret_cast<const u32x4 *>(ring + slotB * kRingSlot + b_off[q] + ch);
+        else if constexpr (q < NR)
+            fa[buf][q - NB] = *reinterpret_cast<const u32x4 *>(
+                ring + slotA * kRingSlot + a_off + ((q - NB) / NIW * NI + (q - NB) % NIW) * 4096 + ch);
     };
-    auto mma_one = [&](auto buf_c, auto i_c, auto j_c) {
-        constexpr int buf = decltype(buf_c)::value, i = decltype(i_c)::value, j = decltype(j_c)::value;
-        if constexpr (j < NB) {
-            if constexpr (F16)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(fa[buf][i]), as_f16x8(fb[buf][j]),
-                                                                   acc[i][j], 0, 0, 0);
-            else
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fa[buf][i]), as_bf16x8(fb[buf][j]),
-                                                                    acc[i][j], 0, 0, 0);
-        }
+    auto mma = [&](auto buf_c, auto m_c) {
+        constexpr int buf = decltype(buf_c)::value, q = decltype(m_c)::value / NB, j = decltype(m_c)::value % NB, i = q % NIW;
+        if constexpr (F16)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(fa[buf][q]), as_f16x8(fb[buf][j]), acc[i][j], 0, 0, 0);
+        else
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fa[buf][q]), as_bf16x8(fb[buf][j]), acc[i][j], 0, 0, 0);
     };
-    // One 16-wide step: four groups of { one direct load (KIND 1: weight instruction D0+g, 2: activation
-    // instruction D0+g, 0: none), two fragment reads for the following step, four MFMAs }; the scheduling
-    // fences keep that interleave.
-    auto step = [&](auto cur_c, auto fetch_c, int slotA, int slotB, int ks_next, auto kind_c, auto d0_c, int dslot,
+    // One 16-wide step: its MFMAs, behind each of the first ones a fragment read of the following step, and NL direct
+    // loads spread over it (KIND 1: activation instruction D0 + g, 2: weight instruction D0 + g); the scheduling
+    // fences keep that interleave, so that each is issued while an MFMA runs.
+    auto step = [&](auto cur_c, auto fetch_c, int slotA, int slotB, int ks_next, auto kind_c, auto d0_c, auto nl_c, int dslot,
                     const bf16_t *dbase) {
         constexpr int cur = decltype(cur_c)::value, kind = decltype(kind_c)::value, d0 = decltype(d0_c)::value;
+        constexpr int nl = kind ? decltype(nl_c)::value : 0;
         constexpr bool FETCH = decltype(fetch_c)::value != 0;
-        // the two reads and the load sit between the group's MFMAs, each issued while the MFMA before it runs
-#define ST_GEMM_GROUP(g)                                                      \
-    mma_one(ic<cur>{}, ic<g>{}, ic<0>{});                                     \
-    __builtin_amdgcn_sched_barrier(0);                                        \
-    if (FETCH) fetch(ic<cur ^ 1>{}, ic<2 * g>{}, slotA, slotB, ks_next);      \
-    __builtin_amdgcn_sched_barrier(0);                                        \
-    mma_one(ic<cur>{}, ic<g>{}, ic<1>{});                                     \
-    __builtin_amdgcn_sched_barrier(0);                                        \
-    if (FETCH) fetch(ic<cur ^ 1>{}, ic<2 * g + 1>{}, slotA, slotB, ks_next);  \
-    __builtin_amdgcn_sched_barrier(0);                                        \
-    mma_one(ic<cur>{}, ic<g>{}, ic<2>{});                                     \
-    __builtin_amdgcn_sched_barrier(0);                                        \
-    if (kind == 1) loadB(ic<d0 + g>{}, dslot, dbase);                         \
-    if (kind == 2) loadA(ic<d0 + g>{}, dslot, dbase);                         \
-    __builtin_amdgcn_sched_barrier(0);                                        \
-    mma_one(ic<cur>{}, ic<g>{}, ic<3>{});                                     \
-    __builtin_amdgcn_sched_barrier(0);
-        ST_GEMM_GROUP(0) ST_GEMM_GROUP(1) ST_GEMM_GROUP(2) ST_GEMM_GROUP(3)
-#undef ST_GEMM_GROUP
+        static_for<NM>([&](auto m_c) {
+            constexpr int m = decltype(m_c)::value;
+            mma(ic<cur>{}, m_c);
+            __builtin_amdgcn_sched_barrier(0);
+            // reads go in pairs, spread over the step
+            if constexpr (FETCH)
+                static_for<NR>([&](auto q_c) {
+                    constexpr int q = decltype(q_c)::value;
+                    if constexpr (m == (q >> 1) * (2 * NM / NR) + (q & 1)) {
+                        fetch(ic<cur ^ 1>{}, q_c, slotA, slotB, ks_next);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                });
+            // load g follows the MFMA at 3/4 of its share of the step
+            static_for<nl>([&](auto g_c) {
+                constexpr int g = decltype(g_c)::value;
+                if constexpr (m == (4 * g + 3) * NM / (4 * nl) - ((4 * g + 3) * NM / (4 * nl) > 0 ? 1 : 0)) {
+                    if constexpr (kind == 1) loadA(ic<d0 + g>{}, dslot, dbase);
+                    if constexpr (kind == 2) loadB(ic<d0 + g>{}, dslot, dbase);
+                }
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
     };
+    constexpr int HA = NLA / 2, HB = NLB / 2;
 
-    // prologue: A0 B0 A1 whole and the first half of B1 (nk >= 2)
-    {
-        const bf16_t *a0 = baseA(0), *b0 = baseB(0), *a1 = baseA(1), *b1 = baseB(1);
-        loadA(ic<0>{}, 0, a0), loadA(ic<1>{}, 0, a0), loadA(ic<2>{}, 0, a0), loadA(ic<3>{}, 0, a0);
-        loadA(ic<4>{}, 0, a0), loadA(ic<5>{}, 0, a0), loadA(ic<6>{}, 0, a0), loadA(ic<7>{}, 0, a0);
-        loadB(ic<0>{}, 1, b0), loadB(ic<1>{}, 1, b0), loadB(ic<2>{}, 1, b0), loadB(ic<3>{}, 1, b0);
-        loadB(ic<4>{}, 1, b0), loadB(ic<5>{}, 1, b0), loadB(ic<6>{}, 1, b0), loadB(ic<7>{}, 1, b0);
-        loadA(ic<0>{}, 2, a1), loadA(ic<1>{}, 2, a1), loadA(ic<2>{}, 2, a1), loadA(ic<3>{}, 2, a1);
-        loadA(ic<4>{}, 2, a1), loadA(ic<5>{}, 2, a1), loadA(ic<6>{}, 2, a1), loadA(ic<7>{}, 2, a1);
-        loadB(ic<0>{}, 3, b1), loadB(ic<1>{}, 3, b1), loadB(ic<2>{}, 3, b1), loadB(ic<3>{}, 3, b1);
+    // prologue (waves that do both): B0 A0 B1 whole and the first half of A1 (nk >= 2)
+    if constexpr (!SPEC) {
+        static_for<NLB>([&](auto i_c) { loadB(i_c, 0, Bw); });
+        static_for<NLA>([&](auto i_c) { loadA(i_c, 1, Aw); });
+        static_for<NLB>([&](auto i_c) { loadB(i_c, 2, Bw + kRingBK); });
+        static_for<HA>([&](auto i_c) { loadA(i_c, 3, Aw + kRingBK); });
+        wait_loads<NLB + HA>();  // B0 and A0 are in
     }
-    wait_loads<12>();  // A0 and B0 are in
     __builtin_amdgcn_s_barrier();
-    fetch(ic<0>{}, ic<0>{}, 0, 1, 0), fetch(ic<0>{}, ic<1>{}, 0, 1, 0), fetch(ic<0>{}, ic<2>{}, 0, 1, 0);
-    fetch(ic<0>{}, ic<3>{}, 0, 1, 0), fetch(ic<0>{}, ic<4>{}, 0, 1, 0), fetch(ic<0>{}, ic<5>{}, 0, 1, 0);
-    fetch(ic<0>{}, ic<6>{}, 0, 1, 0), fetch(ic<0>{}, ic<7>{}, 0, 1, 0);
+    static_for<NR>([&](auto q_c) { fetch(ic<0>{}, q_c, 1, 0, 0); });
     __builtin_amdgcn_sched_barrier(0);
 
-    const bf16_t *bn1 = baseB(1), *an2 = baseA(2), *bn2 = baseB(2);  // bases of B(kt+1), A(kt+2), B(kt+2)
-    int wrap_in = nkw - (k0 + 2);  // K steps until A(kt+2) crosses into the low term (<= 0: never in this block)
-    int sA = 0;  // ring slot of this K step's activations; its weights sit in the next slot, and so on round
-    auto fwd = [](int s, int d) { return s + d >= kRingSlots ? s + d - kRingSlots : s + d; };
+    const bf16_t *an1 = Aw + kRingBK, *an2 = Aw + 2 * kRingBK, *bn2 = Bw + 2 * kRingBK;  // bases of A(kt+1), A(kt+2), B(kt+2)
+    int sB = 0;  // ring slot of this K step's weights; its activations sit in the next slot, and so on round
     // AHEAD: 2 = K steps kt+1 and kt+2 exist, 1 = only kt+1, 0 = this is the last
-    auto kstep = [&](int, auto ahead_c) {
+    auto kstep = [&](auto ahead_c) {
         constexpr int AHEAD = decltype(ahead_c)::value;
-        const int sB = fwd(sA, 1), sA1 = fwd(sA, 2), sB1 = fwd(sA, 3), sA2 = fwd(sA, 4);
-        step(ic<0>{}, ic<1>{}, sA, sB, 1, ic<(AHEAD >= 1 ? 1 : 0)>{}, ic<4>{}, sB1, bn1);  // rest of B(kt+1)
-        step(ic<1>{}, ic<1>{}, sA, sB, 2, ic<(AHEAD >= 2 ? 2 : 0)>{}, ic<0>{}, sA2, an2);  // A(kt+2), first half
-        step(ic<0>{}, ic<1>{}, sA, sB, 3, ic<(AHEAD >= 2 ? 2 : 0)>{}, ic<4>{}, sA2, an2);  // A(kt+2), second half
-        if (AHEAD >= 1) {
-            // all fragments of this K step are in registers and K step kt+1 has landed (only A(kt+2) may
+        const int sA = next_slot(sB, 1), sB1 = next_slot(sB, 2), sA1 = next_slot(sB, 3), sB2 = next_slot(sB, 4);
+        step(ic<0>{}, ic<1>{}, sA, sB, 1, ic<(!SPEC && AHEAD >= 1 ? 1 : 0)>{}, ic<HA>{}, ic<NLA - HA>{}, sA1, an1);  // rest of A(kt+1)
+        step(ic<1>{}, ic<1>{}, sA, sB, 2, ic<(!SPEC && AHEAD >= 2 ? 2 : 0)>{}, ic<0>{}, ic<HB>{}, sB2, bn2);   // B(kt+2)
+        step(ic<0>{}, ic<1>{}, sA, sB, 3, ic<(!SPEC && AHEAD >= 2 ? 2 : 0)>{}, ic<HB>{}, ic<HB>{}, sB2, bn2);  // B(kt+2)
+        if constexpr (AHEAD >= 1) {
+            // all fragments of this K step are in registers and K step kt+1 has landed (only B(kt+2) may
             // still be in flight); after the barrier that holds for every wave, so both slots are free
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            if (AHEAD >= 2) wait_loads<8>(); else wait_loads<0>();
+            if constexpr (!SPEC) {
+                if constexpr (AHEAD >= 2) wait_loads<NLB>(); else wait_loads<0>();
+            }
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
-            step(ic<1>{}, ic<1>{}, sA1, sB1, 0, ic<(AHEAD >= 2 ? 1 : 0)>{}, ic<0>{}, sA, bn2);  // B(kt+2), first half
+            step(ic<1>{}, ic<1>{}, sA1, sB1, 0, ic<(!SPEC && AHEAD >= 2 ? 1 : 0)>{}, ic<0>{}, ic<HA>{}, sB, an2);  // A(kt+2)
         } else {
-            step(ic<1>{}, ic<0>{}, sA1, sB1, 0, ic<0>{}, ic<0>{}, sA, bn2);
+            step(ic<1>{}, ic<0>{}, sA1, sB1, 0, ic<0>{}, ic<0>{}, ic<0>{}, sB, an2);
         }
-        sA = sA1;
-        // bases of the next step's loads: B(kt+2) becomes B(kt+1), the other two move on by one K step and cross
-        // from the high to the low term (and back to the weights' first column) at most once in a block's range
-        bn1 = bn2, an2 += kRingBK, bn2 += kRingBK;
-        if (--wrap_in == 0) an2 = Alo, bn2 = B;
+        sB = sB1;
+        an1 = an2, an2 += kRingBK, bn2 += kRingBK;  // A(kt+2) becomes A(kt+1)
     };
     int kt = 0;
-    for (; kt + 2 < nk; ++kt) kstep(kt, ic<2>{});
-    kstep(kt++, ic<1>{});
-    kstep(kt++, ic<0>{});
+    for (; kt + 2 < nk; ++kt) kstep(ic<2>{});
+    kstep(ic<1>{});
+    kstep(ic<0>{});
 
     // epilogue: register r of a 32x32 tile is row 8*(r/4) + 4*(lane/32) + r%4, column lane%32
-    if constexpr (DUAL) {
+    auto silu_mul = [](float gt, float up) {  // hardware exp2 and reciprocal (1 ulp each, far below bf16)
+        return gt * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gt)) * up;
+    };
+    // stores columns col, col + 1 of one row (col even) as 16-bit numbers, with the second bf16 term where it is wanted
+    auto put2 = [&](int row, int col, float x0, float x1) {
+        const uint32_t pk = out_f16 ? pack_f16x2(x0, x1) : pack_bf16x2(x0, x1);
+        if (row < M && col + 1 < N)
+            *reinterpret_cast<uint32_t *>(outb + (size_t)row * ldo + col) = pk;
+        else if (row < M && col < N)  // an odd width: the last column alone
+            outb[(size_t)row * ldo + col] = (bf16_t)(pk & 0xffffu);
+        if (!out_f16 && outlo) {  // second bf16 term of the activation (feeds a two-term down projection)
+            const uint32_t lo = pack_bf16x2(x0 - bf16_lo(pk), x1 - bf16_hi(pk));
+            if (row < M && col + 1 < N)
+                *reinterpret_cast<uint32_t *>(outlo + (size_t)row * ldo + col) = lo;
+            else if (row < M && col < N)
+                outlo[(size_t)row * ldo + col] = (bf16_t)(lo & 0xffffu);
+        }
+    };
+    const bool odd = l32 & 1;
+    const int mw = m0 + wm * NIW * 32;
+    if constexpr (GU16) {
+        // lanes l32 < 16 hold gate columns, l32 + 16 the matching up columns: after the exchange lane row bit 4 = b
+        // finishes rows r + b and r + 2 + b of a group of four; neighbouring lanes then swap one value each, so that
+        // each stores two columns of one row
+        const bool up_half = l32 & 16;
+#pragma unroll
+        for (int i = 0; i < NIW; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; r += 4) {
+                float g[4], u[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) with_xor16(acc[i][0][r + e], g[e], u[e]);
+                const float v0 = silu_mul(up_half ? g[1] : g[0], up_half ? u[1] : u[0]);
+                const float v1 = silu_mul(up_half ? g[3] : g[2], up_half ? u[3] : u[2]);
+                const float other = dpp_move<0xB1, 0xf>(0.f, odd ? v0 : v1);  // quad_perm [1,0,3,2]
+                const int row = mw + i * 32 + 8 * (r >> 2) + 4 * kg + (up_half ? 1 : 0) + (odd ? 2 : 0);
+                put2(row, n0 + wn * 16 + (l32 & 14), odd ? other : v0, odd ? v1 : other);
+            }
+    } else if constexpr (DUAL) {
         // Two rows at a time: neighbouring lanes (columns c, c + 1) swap one value each, so that the even lane holds
         // both columns of the first row and the odd lane both of the second -- one 4-byte store per lane instead of
-        // two 2-byte ones.  silu goes through the hardware exp2 and reciprocal (1 ulp each, far below bf16).
-        const bool odd = l32 & 1;
+        // two 2-byte ones.
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < NIW; ++i)
 #pragma unroll
-            for (int j = 0; j < NB / 2; ++j)
+            for (int j = 0; j < NBH; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; r += 2) {
-                    float a[2];
-#pragma unroll
-                    for (int e = 0; e < 2; ++e) {
-                        const float gt = acc[i][j][r + e], up = acc[i][j + NB / 2][r + e];
-                        a[e] = gt * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gt)) * up;
-                    }
-                    const float other = dpp_move<0xB1, 0xf>(0.f, odd ? a[0] : a[1]);  // quad_perm [1,0,3,2]
-                    const float x0 = odd ? other : a[0], x1 = odd ? a[1] : other;
-                    const uint32_t pk = out_f16 ? pack_f16x2(x0, x1) : pack_bf16x2(x0, x1);
-                    const int row = m0 + wm * 128 + i * 32 + 8 * (r >> 2) + 4 * kg + (r & 3) + (odd ? 1 : 0);
-                    const int col = n0 + wn * (NB * 16) + j * 32 + (l32 & ~1);
-                    if (row < M && col + 1 < N)
-                        *reinterpret_cast<uint32_t *>(outb + (size_t)row * ldo + col) = pk;
-                    else if (row < M && col < N)  // an odd width: the last column alone
-                        outb[(size_t)row * ldo + col] = (bf16_t)(pk & 0xffffu);
-                    if (!out_f16 && outlo) {  // second bf16 term of the activation (feeds a two-term down projection)
-                        const uint32_t lo = pack_bf16x2(x0 - bf16_lo(pk), x1 - bf16_hi(pk));
-                        if (row < M && col + 1 < N)
-                            *reinterpret_cast<uint32_t *>(outlo + (size_t)row * ldo + col) = lo;
-                        else if (row < M && col < N)
-                            outlo[(size_t)row * ldo + col] = (bf16_t)(lo & 0xffffu);
-                    }
+                    const float a0 = silu_mul(acc[i][j][r], acc[i][j + NB - NBH][r]);
+                    const float a1 = silu_mul(acc[i][j][r + 1], acc[i][j + NB - NBH][r + 1]);
+                    const float other = dpp_move<0xB1, 0xf>(0.f, odd ? a0 : a1);  // quad_perm [1,0,3,2]
+                    const int row = mw + i * 32 + 8 * (r >> 2) + 4 * kg + (r & 3) + (odd ? 1 : 0);
+                    put2(row, n0 + (wn * NBH + j) * 32 + (l32 & ~1), odd ? other : a0, odd ? a1 : other);
                 }
     } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < NIW; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int row = m0 + wm * 128 + i * 32 + 8 * (r >> 2) + 4 * kg + (r & 3);
+                const int row = mw + i * 32 + 8 * (r >> 2) + 4 * kg + (r & 3);
                 if (row >= M) continue;
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
-                    const int col = n0 + wn * 128 + j * 32 + l32;
+                    const int col = n0 + (wn * NB + j) * 32 + l32;
                     if (col < N) pz[(size_t)row * ldp + col] = acc[i][j][r];
                 }
             }
     }
+}
+
+// F16: A and B hold fp16 numbers (single-term activations, the model's fp16 copy of the weights).  out_f16: the
+// fused epilogue writes fp16 (one term) instead of bf16 (+ its low term).
+template <bool DUAL, bool HALF, int TERMS, bool F16>
+__global__ __launch_bounds__(TERMS == 2 ? 512 : 256) void k_gemm_ring(const bf16_t *__restrict__ A,
+                                                                      const bf16_t *__restrict__ Alo, int lda,
+                                                                      const bf16_t *__restrict__ B, int M, int N, int K,
+                                                                      float *__restrict__ part, bf16_t *__restrict__ outb,
+                                                                      bf16_t *__restrict__ outlo, int ldo, RingGrid gg,
+                                                                      int out_f16) {
+    extern __shared__ __align__(16) unsigned char ring[];
+    RingBlock rb;
+    if (!ring_block(gg, blockIdx.x, M, N, K, &rb)) return;
+    float *pz = DUAL ? nullptr : part + rb.part_off;  // where this block's fp32 tile goes (plain form)
+    const int m0 = ring_row0(gg, rb.y, 64 / TERMS), n0 = (rb.x + gg.x0) * ((HALF ? 128 : 256) / (DUAL ? 2 : 1));
+    const int kbeg = __builtin_amdgcn_readfirstlane(rb.kbeg);  // wave-uniform: the load bases live in scalar registers
+    const int nk = __builtin_amdgcn_readfirstlane((rb.kend - rb.kbeg) / kRingBK);
+#define ST_RING_TILE(NFV)                                                                                                  \
+    ring_tile<NFV, DUAL, HALF, TERMS, F16>(ring, A, Alo, lda, B, M, N, K, pz, rb.ldp, outb, outlo, ldo, m0, n0, kbeg, nk, \
+                                           out_f16)
+    switch (__builtin_amdgcn_readfirstlane(ring_units(gg, rb.y))) {
+        case 1: ST_RING_TILE(2); break;
+        case 2: ST_RING_TILE(4); break;
+        case 3: ST_RING_TILE(6); break;
+        default: ST_RING_TILE(8); break;
+    }
+#undef ST_RING_TILE
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1593,15 +1670,16 @@ static void gemm_launch(const Model &m, dim3 grid, const bf16_t *A, const bf16_t
                        outlo, ldo, gg);
 }
 
-template <bool DUAL, bool HALF = false>
+template <bool DUAL, bool HALF>
 static void ring_launch(const Model &m, bool f16, bool out_f16, dim3 grid, const bf16_t *A, const bf16_t *Alo, int lda,
                         const bf16_t *B, int M, int N, int K, bf16_t *outb, bf16_t *outlo, int ldo, const RingGrid &gg) {
-    if (f16)
-        hipLaunchKernelGGL((k_gemm_ring<DUAL, HALF, true>), grid, dim3(256), kRingLds, m.stream, A, Alo, lda, B, M, N, K,
-                           m.ws.qkv, outb, outlo, ldo, gg, (int)out_f16);
-    else
-        hipLaunchKernelGGL((k_gemm_ring<DUAL, HALF, false>), grid, dim3(256), kRingLds, m.stream, A, Alo, lda, B, M, N, K,
-                           m.ws.qkv, outb, outlo, ldo, gg, (int)out_f16);
+#define ST_RING_GO(TERMSV, F16V)                                                                                            \
+    hipLaunchKernelGGL((k_gemm_ring<DUAL, HALF, TERMSV, F16V>), grid, dim3(TERMSV == 2 ? 512 : 256), kRingLds, m.stream, A, \
+                       Alo, lda, B, M, N, K, m.ws.qkv, outb, outlo, ldo, gg, (int)out_f16)
+    if (Alo) ST_RING_GO(2, false);
+    else if (f16) ST_RING_GO(1, true);
+    else ST_RING_GO(1, false);
+#undef ST_RING_GO
 }
 
 // The ring and streaming kernels use more dynamic LDS than a kernel gets by default; the limit is raised once per
@@ -1617,10 +1695,11 @@ hipError_t raise_lds_limits() {
     auto take = [&](hipError_t r) {
         if (e == hipSuccess) e = r;
     };
-    take(raise_one(k_gemm_ring<false, false, false>)), take(raise_one(k_gemm_ring<true, false, false>));
-    take(raise_one(k_gemm_ring<true, true, false>));
-    take(raise_one(k_gemm_ring<false, false, true>)), take(raise_one(k_gemm_ring<true, false, true>));
-    take(raise_one(k_gemm_ring<true, true, true>));
+#define ST_RING_LIMIT(D, H)                                                                                 \
+    take(raise_one(k_gemm_ring<D, H, 1, false>)), take(raise_one(k_gemm_ring<D, H, 1, true>)), \
+        take(raise_one(k_gemm_ring<D, H, 2, false>));
+    ST_RING_LIMIT(false, false) ST_RING_LIMIT(false, true) ST_RING_LIMIT(true, false) ST_RING_LIMIT(true, true)
+#undef ST_RING_LIMIT
     take(raise_one(k_gemm_stream<1, 64, true, 1, true>)), take(raise_one(k_gemm_stream<2, 64, true, 1, true>));
     take(raise_one(k_gemm_stream<3, 64, true, 1, true>)), take(raise_one(k_gemm_stream<4, 64, false, 1, true>));
     take(raise_one(k_gemm_stream<5, 64, false, 1, true>)), take(raise_one(k_gemm_stream<6, 64, false, 1, true>));
@@ -1703,8 +1782,8 @@ static StreamShape stream_shape(const Model &m, int M, int N, int K, int terms =
     return best;
 }
 
-// Launches of the 256 x 256 ring kernel for one GEMM of a chunk of more than kSplitRows rows: K slices, leftover
-// tiles and block numbering.  Pure host arithmetic (ring_plan_check walks it without a GPU).
+// Launches of the ring kernel for one GEMM of a long chunk: tile width, K slices, leftover tiles and block numbering.
+// Pure host arithmetic (ring_plan_check walks it without a GPU).
 struct RingPlan {
     int n;             // launches: 1, or 2 for the fused form with half-width leftover tiles
     RingGrid g[2];
@@ -1714,66 +1793,95 @@ struct RingPlan {
     PartTail tail;     // extra slices of the tail columns
 };
 
-static RingPlan ring_plan(bool dual, int M, int N, int K, size_t cap, bool allow_tail) {
+// One block per CU at a time, so a launch takes (rounds of 256 blocks) x (K steps per block x the time of a step + what
+// a block spends filling its ring and storing its tile); the fp32 slices of the plain form are written once and read
+// again by the consumer.  Microseconds; a step of a full tile measured 1.7, of a half-width one 0.97-1.1.
+struct RingCost {
+    static constexpr double kFill = 2.5, kLaunch = 2.5;
+    // rows: mean height of the row tiles, out of the bm of a full one
+    static double block(bool half, bool dual, int bm, double rows, int steps) {
+        const double tile_bytes = rows * (half ? 128 : 256) * (dual ? 1 : 4);
+        return steps * (half ? 0.35 + 0.70 * rows / bm : 0.50 + 1.20 * rows / bm) + kFill + tile_bytes / 58e3;
+    }
+    static double rounds(long blocks) { return (double)((blocks + 255) / 256); }
+    static double slices(int s, int M, int N) { return (double)s * M * N * 8 / 4e6; }
+};
+
+// two_term: A arrives as two bf16 terms; a block then takes up to 128 rows instead of 256 (see k_gemm_ring).
+static int ring_unit(bool two_term) { return two_term ? 32 : 64; }
+static RingPlan ring_plan(bool dual, bool two_term, int M, int N, int K, size_t cap, bool allow_tail) {
     RingPlan p{};
     RingGrid gg;
-    gg.My = (M + 255) / 256;
-    gg.Nx = (N + (dual ? 128 : 256) - 1) / (dual ? 128 : 256);
+    const int unit = ring_unit(two_term), bm = 4 * unit, nk = K / kRingBK, units = (M + unit - 1) / unit;
+    gg.My = (units + 3) / 4;
+    gg.h_base = units / gg.My, gg.h_extra = units % gg.My;
+    const double rows = (double)units * unit / gg.My;
     gg.TY = 1;
     while (gg.TY * 2 <= gg.My && gg.TY < 8) gg.TY *= 2;
     gg.TX = 32 / gg.TY;
     gg.S = 1, gg.kps = K, gg.x0 = 0;
     gg.tail_x0 = gg.tail_tiles = 0, gg.tail_s = 1, gg.tail_kps = K;
-    const int tiles = gg.My * gg.Nx, nk = K / kRingBK;
+    const int width = dual ? 128 : 256;                          // output columns of a full tile
+    const int nx = (N + width - 1) / width, nxh = (N + width / 2 - 1) / (width / 2);
+    const long tiles = (long)gg.My * nx, tiles_h = (long)gg.My * nxh;
+    bool half = false;
     p.n = 1;
     if (dual) {
-        // Whole rounds of 256 full tiles, then the column tiles left over as half-width tiles in a launch of their
-        // own: twice the blocks at half the length each, so the last round keeps every CU busy for half a round
-        // instead of half the CUs for a whole one.
-        if (tiles > 256 && tiles % 256 && 256 % gg.My == 0) {
-            const int nx_main = tiles / 256 * 256 / gg.My;
-            RingGrid th = gg;
-            th.Nx = 2 * (gg.Nx - nx_main), th.x0 = 2 * nx_main;
-            if (th.x0 * 64 + th.Nx * 64 > N + 63) th.Nx = (N - th.x0 * 64 + 63) / 64;  // a ragged last column tile
-            th.per = (th.My * th.Nx + 7) / 8, th.blocks = 8 * th.per;
-            gg.Nx = nx_main;
-            p.n = 2, p.g[1] = th, p.half[1] = true, p.grid_x[1] = th.blocks;
+        // Full tiles only, half-width tiles only, or whole rounds of 256 full tiles and the column tiles left over as
+        // half-width tiles in a launch of their own: twice the blocks at half the length each, so the last round
+        // keeps every CU busy for half a round instead of half the CUs for a whole one.
+        double best = RingCost::rounds(tiles) * RingCost::block(false, true, bm, rows, nk);
+        const double all_half = RingCost::rounds(tiles_h) * RingCost::block(true, true, bm, rows, nk);
+        gg.Nx = nx;
+        if (all_half < best) best = all_half, half = true, gg.Nx = nxh;
+        const int nx_main = (int)(tiles / 256 * 256 / gg.My);
+        if (tiles > 256 && nx_main < nx) {
+            const int left_h = nxh - 2 * nx_main;  // half-width columns (a ragged last one included)
+            const double split = RingCost::rounds((long)nx_main * gg.My) * RingCost::block(false, true, bm, rows, nk) +
+                                 RingCost::rounds((long)left_h * gg.My) * RingCost::block(true, true, bm, rows, nk) + RingCost::kLaunch;
+            if (split < best) {
+                RingGrid th = gg;
+                th.Nx = left_h, th.x0 = 2 * nx_main;
+                th.per = (th.My * th.Nx + 7) / 8, th.blocks = 8 * th.per;
+                gg.Nx = nx_main, half = false;
+                p.n = 2, p.g[1] = th, p.half[1] = true, p.grid_x[1] = th.blocks;
+            }
         }
     } else {
-        // One block per CU at a time: pick the K slices that minimise (rounds of 256 blocks) x (K steps per
-        // slice + a fixed cost for filling the ring and writing the tile)
-        // Short passes (one or two row tiles) have few tiles, so they may take up to 16 slices; there the partial
-        // sums every slice writes and the consumer reads again (8 bytes per element at ~4 TB/s, in units of a
-        // 1.4 us K step) are part of the price.
-        long best = -1;
+        double best = -1;
         const int max_s = M <= 512 ? 16 : 8;
-        const double slice_steps = M <= 512 ? (double)M * N * 8 / 4e12 / 1.4e-6 : 0.0;
-        for (int s = 1; s <= max_s; ++s) {
-            const int steps = (nk + s - 1) / s;
-            if (steps < 4 && s > 1) break;
-            if (s > 1 && (size_t)s * M * N > cap) break;
-            const long cost = (long)((tiles * s + 255) / 256) * (steps + 6) + (long)(s * slice_steps);
-            if (best < 0 || cost < best) best = cost, gg.S = s;
-        }
+        for (int h = 0; h < 2; ++h)
+            for (int s = 1; s <= max_s; ++s) {
+                const int steps = (nk + s - 1) / s;
+                if (s > 1 && (steps < 3 || (size_t)s * M * N > cap)) break;
+                const int used = (nk + steps - 1) / steps;
+                if (used != s || nk - (s - 1) * steps < 2) continue;  // the last slice needs two steps
+                const double cost = RingCost::rounds((h ? tiles_h : tiles) * s) * RingCost::block(h, false, bm, rows, steps) +
+                                    RingCost::slices(s, M, N);
+                if (best < 0 || cost < best) best = cost, gg.S = s, half = h;
+            }
+        gg.Nx = half ? nxh : nx;
         gg.kps = (nk + gg.S - 1) / gg.S * kRingBK;
-        gg.S = (K + gg.kps - 1) / gg.kps;
-        if (K - (gg.S - 1) * gg.kps < 2 * kRingBK) gg.S = 1, gg.kps = K;  // a last slice of one step: do not split
-        // Or: whole rounds of 256 tiles at full K, and only the column tiles left over cut into K slices (a
+        // Or: whole rounds of 256 full tiles at full K, and only the column tiles left over cut into K slices (a
         // consumer that takes a PartTail adds their extra slices).  320 tiles with K = 432 steps: three rounds of
         // half the K range each become one round at full K plus one round of quarter slices.
-        if (allow_tail && tiles > 256 && tiles % 256 && 256 % gg.My == 0) {
-            const int nx_main = tiles / 256 * 256 / gg.My, tail_tiles = (gg.Nx - nx_main) * gg.My;
-            const int ld = N - nx_main * 256;
-            long tbest = -1;
+        const int nx_main = (int)(tiles / 256 * 256 / gg.My);
+        if (allow_tail && tiles > 256 && nx_main < nx) {
+            const int tail_tiles = (nx - nx_main) * gg.My, ld = N - nx_main * 256;
+            double tbest = -1;
             int ts = 1;
             for (int s = 1; s <= 8; ++s) {
                 const int steps = (nk + s - 1) / s;
                 if (s > 1 && (steps < 4 || nk - (s - 1) * steps < 2)) break;
                 if ((size_t)M * N + (size_t)(s - 1) * M * ld > cap) break;
-                const long cost = (long)((tail_tiles * s + 255) / 256) * (steps + 6);
+                const double cost = RingCost::rounds((long)tail_tiles * s) * RingCost::block(false, false, bm, rows, steps) +
+                                    RingCost::slices(s - 1, M, ld);
                 if (tbest < 0 || cost < tbest) tbest = cost, ts = s;
             }
-            if ((long)(tiles / 256) * (nk + 6) + tbest < best) {
+            const double cost = RingCost::rounds((long)nx_main * gg.My) * RingCost::block(false, false, bm, rows, nk) + tbest +
+                                RingCost::slices(1, M, N);
+            if (cost < best) {
+                half = false;
                 gg.tail_x0 = nx_main, gg.tail_tiles = tail_tiles, gg.tail_s = ts;
                 gg.tail_kps = (nk + ts - 1) / ts * kRingBK;
                 gg.Nx = nx_main, gg.S = 1, gg.kps = K;  // the main part: the first nx_main column tiles at full K
@@ -1785,20 +1893,22 @@ static RingPlan ring_plan(bool dual, int M, int N, int K, size_t cap, bool allow
     gg.per = (gg.S * gg.My * gg.Nx + 7) / 8;
     gg.blocks = 8 * gg.per;
     const int tail_units = (gg.tail_tiles + 31) / 32 * gg.tail_s;
-    p.g[0] = gg, p.half[0] = false, p.grid_x[0] = gg.blocks + (tail_units + 7) / 8 * 256;
+    p.g[0] = gg, p.half[0] = half, p.grid_x[0] = gg.blocks + (tail_units + 7) / 8 * 256;
     return p;
 }
 
-// Alo != nullptr: two-term activations, the plan covers the doubled contraction [A | Alo] x [B | B].
+// Alo != nullptr: two-term activations.
 template <bool DUAL>
 static int ring_gemm(const Model &m, bool f16, bool out_f16, const bf16_t *A, const bf16_t *Alo, int lda, const bf16_t *B,
                      int M, int N, int K, bf16_t *outb, bf16_t *outlo, int ldo, PartTail *tail) {
-    const RingPlan p = ring_plan(DUAL, M, N, Alo ? 2 * K : K, partial_floats(m.c), tail != nullptr);
-    ring_launch<DUAL, false>(m, f16, out_f16, dim3(p.grid_x[0]), A, Alo, lda, B, M, N, K, outb, outlo, ldo, p.g[0]);
-    if constexpr (DUAL)
-        if (p.n == 2)
-            ring_launch<true, true>(m, f16, out_f16, dim3(p.grid_x[1]), A, Alo, lda, B, M, N, K, outb, outlo, ldo,
-                                    p.g[1]);
+    const RingPlan p = ring_plan(DUAL, Alo != nullptr, M, N, K, partial_floats(m.c), tail != nullptr);
+    for (int l = 0; l < p.n; ++l) {
+        const dim3 grid(p.grid_x[l]);
+        if (p.half[l])
+            ring_launch<DUAL, true>(m, f16, out_f16, grid, A, Alo, lda, B, M, N, K, outb, outlo, ldo, p.g[l]);
+        else
+            ring_launch<DUAL, false>(m, f16, out_f16, grid, A, Alo, lda, B, M, N, K, outb, outlo, ldo, p.g[l]);
+    }
     if (tail) *tail = p.tail;
     return p.slices;
 }
@@ -1806,24 +1916,26 @@ static int ring_gemm(const Model &m, bool f16, bool out_f16, const bf16_t *A, co
 // Walks every block id of the plan on the host: 0 if each (output tile, 64-column K step) of the GEMM is covered by
 // exactly one block, every block has at least two K steps, and (plain form) every partial-sum tile lies inside
 // cap_floats; a negative code names the first failure.  blocks_out: working blocks, ids_out: ids launched.
-int ring_plan_check(int dual, int M, int N, int K, long long cap_floats, int allow_tail, int *launches_out,
+int ring_plan_check(int dual, int two_term, int M, int N, int K, long long cap_floats, int allow_tail, int *launches_out,
                     int *blocks_out, int *ids_out) {
     if (M <= 0 || N <= 0 || K < 2 * kRingBK || K % kRingBK) return -1;
-    const RingPlan p = ring_plan(dual != 0, M, N, K, (size_t)cap_floats, allow_tail != 0);
-    const int nk = K / kRingBK, my = (M + 255) / 256;
-    const int out_cols = dual ? 64 : 256;  // count output columns in units every tile width is a multiple of
+    const RingPlan p = ring_plan(dual != 0, two_term != 0, M, N, K, (size_t)cap_floats, allow_tail != 0);
+    const int unit = ring_unit(two_term != 0), nk = K / kRingBK, my = p.g[0].My;
+    const int out_cols = dual ? 64 : 128;  // count output columns in units every tile width is a multiple of
     const int ncu = (N + out_cols - 1) / out_cols;
     std::vector<unsigned char> seen((size_t)my * ncu * nk, 0);
     int working = 0, ids = 0;
     for (int l = 0; l < p.n; ++l) {
-        const int width = p.half[l] ? 64 : dual ? 128 : 256, per_tile = width / out_cols;
+        const int width = (p.half[l] ? 128 : 256) / (dual ? 2 : 1), per_tile = width / out_cols;
         ids += p.grid_x[l];
         for (int bid = 0; bid < p.grid_x[l]; ++bid) {
             RingBlock rb;
             if (!ring_block(p.g[l], bid, M, N, K, &rb)) continue;
             ++working;
             const int n0 = (rb.x + p.g[l].x0) * width;
-            if (rb.y < 0 || rb.y >= my || n0 < 0 || n0 >= N) return -2;
+            const int units = ring_units(p.g[l], rb.y), r0 = ring_row0(p.g[l], rb.y, unit);
+            if (rb.y < 0 || rb.y >= my || n0 < 0 || n0 >= N || units < 1 || units > 4 || r0 >= M) return -2;
+            if (rb.y == my - 1 && r0 + units * unit < M) return -2;  // the last row tile ends at or past the last row
             if (rb.kbeg < 0 || rb.kend > K || (rb.kend - rb.kbeg) % kRingBK || rb.kend - rb.kbeg < 2 * kRingBK) return -3;
             for (int c = 0; c < per_tile; ++c) {
                 const int cu = n0 / out_cols + c;
@@ -1835,8 +1947,8 @@ int ring_plan_check(int dual, int M, int N, int K, long long cap_floats, int all
                 }
             }
             if (!dual) {
-                const int rows = (rb.y * 256 + 256 < M ? rb.y * 256 + 256 : M), cols = (n0 + 256 < N ? n0 + 256 : N);
-                const long long lo = rb.part_off + (long long)rb.y * 256 * rb.ldp + n0;
+                const int rows = (r0 + units * unit < M ? r0 + units * unit : M), cols = (n0 + width < N ? n0 + width : N);
+                const long long lo = rb.part_off + (long long)r0 * rb.ldp + n0;
                 const long long hi = rb.part_off + (long long)(rows - 1) * rb.ldp + cols - 1;
                 if (lo < 0 || hi >= cap_floats) return -5;
                 if (rb.part_off > 0 && p.tail.n > 0 && rb.ldp != N &&
@@ -1866,7 +1978,7 @@ static int gemm(const Model &m, const bf16_t *A, const bf16_t *Alo, int lda, con
     // (the ring kernel addresses its operands with 32-bit byte offsets)
     const bool fits32 = (size_t)M * lda * sizeof(bf16_t) < ((size_t)1 << 32) &&
                         (size_t)(DUAL ? 2 : 1) * N * K * sizeof(bf16_t) < ((size_t)1 << 32);
-    const bool big = M >= m.ring_min_rows && K % kRingBK == 0 && K >= 2 * kRingBK && fits32;
+    const bool big = M >= ring_min_rows(Alo != nullptr) && K % kRingBK == 0 && K >= 2 * kRingBK && fits32;
     if (!big && !DUAL && !Alo && M <= kSplitRows && K % kRingBK == 0) {
         // one activation term below the ring threshold: fp16 operands, or single bf16 (ST_PREFILL_FAST)
         const StreamShape sh = stream_shape(m, M, N, K, 1);
@@ -2107,7 +2219,7 @@ void launch_prefill_layers(const Model &m, int32_t pos0, int32_t n) {
                              t.f16_attn);
         hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n), dim3(norm_threads(n)), 0, m.stream, w.x, w.qkv, so, (size_t)n * h,
                            m.norm_mlp[l], w.xn, t.f16_xg ? nullptr : xn_lo, h, c.rms_eps, to, (int)t.f16_xg);
-        if (n < (h % kRingBK == 0 ? m.ring_min_rows : kSmallRows + 1)) {  // small chunk: gate/up as a plain split-K
+        if (n < (h % kRingBK == 0 ? ring_min_rows(t.gu_two) : kSmallRows + 1)) {  // small chunk: gate/up as a plain split-K
                                                                            // GEMM over all 2I rows, SwiGLU in the consumer
             int sg = gemm<false>(m, w.xn, t.f16_xg ? nullptr : xn_lo, h, t.f16_xg ? m.wgu16[l] : m.wgu[l], n, 2 * I, h,
                                  nullptr, nullptr, 0, nullptr, t.f16_xg);
@@ -2327,7 +2439,7 @@ void launch_prefill_varlen(const Model &m, const BatchRows &b, const FlashSeg *s
                                    nullptr, t.f16_attn);
         hipLaunchKernelGGL(k_rmsnorm_rows, dim3(R), dim3(norm_threads(R)), 0, m.stream, w.x, w.qkv, so, (size_t)R * h,
                            m.norm_mlp[l], w.xn, t.f16_xg ? nullptr : xn_lo, h, c.rms_eps, PartTail{}, (int)t.f16_xg);
-        if (R < (h % kRingBK == 0 ? m.ring_min_rows : kSmallRows + 1)) {
+        if (R < (h % kRingBK == 0 ? ring_min_rows(t.gu_two) : kSmallRows + 1)) {
             const int sg = gemm<false>(m, w.xn, t.f16_xg ? nullptr : xn_lo, h, t.f16_xg ? m.wgu16[l] : m.wgu[l], R, 2 * I, h,
                                        nullptr, nullptr, 0, nullptr, t.f16_xg);
             hipLaunchKernelGGL(k_swiglu_rows, dim3((I / 4 + 255) / 256, R), dim3(256), 0, m.stream, w.qkv, sg,

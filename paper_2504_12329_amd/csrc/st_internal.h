@@ -97,12 +97,14 @@ struct AttnRows {
 // the four projections and the rotated queries of the attention
 enum LongTerms { kTermQKV = 1, kTermO = 2, kTermGateUp = 4, kTermDown = 8, kTermQuery = 16, kTermAll = 31 };
 constexpr int kDefaultLongTerms = kTermAll;
-// Passes of at least this many rows take the 256 x 256 ring GEMMs, shorter ones the weight-streaming kernel.  Measured
-// per layer of the 32B shape on 4096 cached keys, streaming against ring kernel -- two bf16 terms: 129 rows 0.50 / 0.60,
-// 224 rows 0.63 / 0.64, 256 rows 0.69 / 0.64 ms; one term (fp16 operands): 129 rows 0.36 / 0.40, 160 rows 0.38 / 0.41,
-// 192 rows 0.41 / 0.42, 224 rows 0.47 / 0.43, 256 rows 0.50 / 0.44 ms (single bf16: 0.02-0.03 ms less on both sides).
-constexpr int kRingMinRows = 241;      // two bf16 terms
-constexpr int kRingMinRowsFast = 193;  // one term: ST_PREFILL_FAST, or the fp16 operand mode
+// Passes of at least this many rows take the ring GEMMs, shorter ones the weight-streaming kernel.  Time of a pass of
+// four layers on 512 cached keys, streaming against ring kernel, at the 1.5B / 7B / 32B shapes -- two bf16 terms: 88 rows
+// 465 : 455, 955 : 951, 1446 : 1449 us; 100 rows 515 : 467, 1068 : 927, 1650 : 1442 us; 144 rows 612 : 478, 1265 : 1087,
+// 1968 : 1937 us (up to 96 rows, three activation tiles, the streaming kernel keeps loading and multiplying waves apart).
+// One term (fp16 operands): 160 rows 540 : 511, 1054 : 1048, 1571 : 1590 us; 176 rows 564 : 490, 1121 : 978, 1676 : 1530 us.
+constexpr int kRingMinRows = 97;       // two bf16 terms
+constexpr int kRingMinRowsFast = 161;  // one term: ST_PREFILL_FAST, or the fp16 operand mode
+inline int ring_min_rows(bool two_term) { return two_term ? kRingMinRows : kRingMinRowsFast; }
 
 constexpr int kLmBlocks = 1024;   // blocks (and arg-max partials) of the LM-head kernel
 constexpr int kAttnSplits = 128;  // most key ranges one kv head is split into at decode
@@ -135,7 +137,6 @@ struct Model {
     bool graphs_off;                 // capture failed or was disabled: steps are launched kernel by kernel
     bool graph_failed;               // graphs_off because a capture or instantiation failed (reported, not silent)
     int long_terms;                  // LongTerms mask of the pass being enqueued (see pass_terms in prefill.hip)
-    int ring_min_rows;               // passes of at least this many rows take the 256 x 256 ring GEMMs
     // fp16 copies of the O, gate/up and down projection matrices of every layer (st_model_attach_f16), empty until
     // attached
     std::vector<const bf16_t *> wo16, wgu16, wdown16;
@@ -195,7 +196,7 @@ void launch_decode_persist(const Model &m, const st_trigger_rule *rule, int32_t 
 // Feeds ws.tokens[0,n) at positions [pos0, pos0+n) through all layers; leaves the residual rows in ws.x.
 // Host walk over the block numbering of the long-chunk GEMM (0 = every tile and K step covered exactly once and
 // every partial-sum tile inside cap_floats; negative = which check failed).
-int ring_plan_check(int dual, int M, int N, int K, long long cap_floats, int allow_tail, int *launches_out,
+int ring_plan_check(int dual, int two_term, int M, int N, int K, long long cap_floats, int allow_tail, int *launches_out,
                     int *blocks_out, int *ids_out);
 size_t partial_floats(const st_config &c);  // floats of Workspace::qkv (the split-K / split-key partial results)
 hipError_t raise_lds_limits();              // once per process, before the first ring / streaming GEMM launch
