@@ -1083,13 +1083,14 @@ __global__ __launch_bounds__(256) void k_swiglu_rows(const float *__restrict__ p
 // ---------------------------------------------------------------------------------------
 constexpr int kFlashKeys = 64;
 
-// Resolves blockIdx.x to (segment, row block inside it); all values are wave-uniform.
+// Resolves row block bx of nbx to (segment, row block inside it); all values are wave-uniform.
 struct FlashWhere {
     int m, kv0, row_base, bx, nbx;
     size_t cache;
 };
-__device__ __forceinline__ FlashWhere flash_where(const FlashSeg *segs, int n_seg, size_t seq_stride, int m, int kv0) {
-    FlashWhere w = {m, kv0, 0, (int)blockIdx.x, (int)gridDim.x, 0};
+__device__ __forceinline__ FlashWhere flash_where(const FlashSeg *segs, int n_seg, size_t seq_stride, int m, int kv0, int bx,
+                                                  int nbx) {
+    FlashWhere w = {m, kv0, 0, bx, nbx, 0};
     if (segs) {
         int j = 0;
         while (j + 1 < n_seg && w.bx >= segs[j + 1].blk0) ++j;
@@ -1117,7 +1118,7 @@ __global__ __launch_bounds__(256) void k_flash_prefill(const bf16_t *__restrict_
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, kg = lane >> 5;
     const int g = blockIdx.y, n_split = gridDim.z, z = blockIdx.z;
-    const FlashWhere fw = flash_where(segs, n_seg, seq_stride, m, kv0);
+    const FlashWhere fw = flash_where(segs, n_seg, seq_stride, m, kv0, blockIdx.x, gridDim.x);
     m = fw.m, kv0 = fw.kv0;
     kc += fw.cache, vc += fw.cache;
     const int rows = m * G;
@@ -1317,40 +1318,51 @@ __global__ __launch_bounds__(256) void k_flash_prefill(const bf16_t *__restrict_
     }
 }
 
-// head_dim 128 (every chunk length): the same attention with at most 256 registers per lane, so that two waves
-// share a SIMD and one wave's softmax runs under another's MFMAs, and one barrier per 64-key tile:
-//   * K tiles go global -> LDS directly into two 16 KB slots whose 16-byte chunks are XOR-swizzled by the key
-//     row, so the S^T fragment reads need neither staging registers nor padding;
+// head_dim 128 (every chunk length): eight waves, two per SIMD, that take turns: while waves 0-3 run the MFMAs of one
+// key tile (S^T of the next tile and V^T P^T of this one), waves 4-7 run the softmax of theirs, and the other way round
+// in the next slot; a barrier ends each slot.  Left to themselves the two waves of a SIMD fall into step -- both in
+// their MFMAs, then both in their softmax -- and the matrix pipe idles during the latter (52 % busy, vector pipe 43 %,
+// the two adding up to the whole time).
+//   * K and V tiles of 64 keys go global -> LDS directly, 16-byte chunks swizzled by the key row; the next tiles are
+//     requested one iteration (two slots) ahead;
 //   * the S^T fragment of lane i reads key row swap(i) (bits 2 and 3 of i exchanged): the 32x32 MFMA output
 //     then leaves every lane with eight *consecutive* keys per 16-key step, so P^T feeds the second MFMA
-//     straight from registers and each V^T fragment is one 16-byte read;
+//     straight from registers; the V^T fragments are transposing LDS reads (ds_read_b64_tr_b16: in a group of 16 lanes
+//     lane 4r + q delivers four columns of row r, lane i receives column i of the four rows);
 //   * the running maximum is raised only when it would grow by more than 2^8 (softmax is shift-invariant and
 //     the final division by the row sum absorbs the reference), which makes the rescale of the 64 output
 //     registers rare; tiles wholly below the diagonal skip the causal compare.
+// KSPLIT = false: a block is 256 folded rows, both halves read the same tiles.  KSPLIT = true (short chunks): 128 rows,
+// waves 0-3 take the even and waves 4-7 the odd key tiles, and the two halves are merged through LDS at the end.
+// Block ids: kv head fastest, so that with 8 kv heads an XCD (id mod 8) keeps to one head's keys.
 // Interface and key-split partial results are those of k_flash_prefill.
 // ---------------------------------------------------------------------------------------
-template <int NW, bool TWO>  // NW waves per block, 32 folded rows each; TWO: queries arrive as two bf16 terms
-__global__ __launch_bounds__(64 * NW, 2) void k_flash_long(const bf16_t *__restrict__ qb,
-                                                    const bf16_t *__restrict__ qb_lo, const bf16_t *__restrict__ kc,
-                                                    const bf16_t *__restrict__ vc, bf16_t *__restrict__ out,
-                                                    bf16_t *__restrict__ outlo, float *__restrict__ part_o,
-                                                    float *__restrict__ part_ml, int m, int kv0, int nq, int G,
-                                                    int max_seq, const FlashSeg *__restrict__ segs, int n_seg,
-                                                    size_t seq_stride, int m_total, int f16) {
-    constexpr int D = 128, VS = kFlashKeys + 8;  // V^T rows of 144 bytes: 16-byte reads conflict-free
-    __shared__ __align__(16) unsigned char Ks[2][kFlashKeys * D * 2];
-    __shared__ __align__(16) bf16_t Vt[2][D * VS];
+constexpr int kFlashTile = kFlashKeys * 128 * 2;  // bytes of one K or V tile
+constexpr int kFlashLds = 8 * kFlashTile;
+typedef short s16x4 __attribute__((ext_vector_type(4)));
 
+enum FlashForm { kFlashSingle, kFlashSplit, kFlashShared };
+template <bool TWO, int FORM>  // TWO: queries arrive as two bf16 terms
+__global__ __launch_bounds__(FORM == kFlashSingle ? 256 : 512, 2) void k_flash_long(const bf16_t *__restrict__ qb, const bf16_t *__restrict__ qb_lo,
+                                                       const bf16_t *__restrict__ kc, const bf16_t *__restrict__ vc,
+                                                       bf16_t *__restrict__ out, bf16_t *__restrict__ outlo,
+                                                       float *__restrict__ part_o, float *__restrict__ part_ml, int m,
+                                                       int kv0, int nq, int nkv, int max_seq,
+                                                       const FlashSeg *__restrict__ segs, int n_seg, size_t seq_stride,
+                                                       int m_total, int f16, int nbx, int n_split) {
+    constexpr int D = 128;
+    constexpr bool KSPLIT = FORM == kFlashSplit, PAIR = FORM != kFlashSingle;
+    extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l32 = lane & 31, kg = lane >> 5;
-    const int g = blockIdx.y, n_split = gridDim.z, z = blockIdx.z;
-    const FlashWhere fw = flash_where(segs, n_seg, seq_stride, m, kv0);
+    const int half = PAIR ? wave >> 2 : 0, w4 = wave & 3, l32 = lane & 31, kg = lane >> 5;
+    const int g = blockIdx.x % nkv, z = blockIdx.x / (nkv * nbx), G = nq / nkv;
+    const FlashWhere fw = flash_where(segs, n_seg, seq_stride, m, kv0, blockIdx.x / nkv % nbx, nbx);
     m = fw.m, kv0 = fw.kv0;
     kc += fw.cache, vc += fw.cache;
     const int rows = m * G;
-    constexpr int kLongRows = 32 * NW, NT = 64 * NW;
+    constexpr int kRows = FORM == kFlashShared ? 256 : 128;
     // blocks with the most keys (the last rows) are dispatched first, so the causal tail is made of short blocks
-    const int r0 = (fw.nbx - 1 - fw.bx) * kLongRows, rw0 = r0 + wave * 32;
+    const int r0 = (fw.nbx - 1 - fw.bx) * kRows, rw0 = r0 + wave % (kRows / 32) * 32;
     const int ldq = nq * D;
     const bool wave_active = rw0 < rows;
     const int row = min(rw0 + l32, rows - 1);
@@ -1358,18 +1370,54 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_long(const bf16_t *__restr
     const int q_abs = kv0 + qtok;
     const int wave_first_q = kv0 + min(rw0, rows - 1) / G;          // smallest position among the wave's rows
     const int wave_last_key = kv0 + min(rw0 + 31, rows - 1) / G;
-    const int n_keys = kv0 + min(r0 + kLongRows - 1, rows - 1) / G + 1;
+    const int n_keys = kv0 + min(r0 + kRows - 1, rows - 1) / G + 1;
     const int n_tiles = (n_keys + kFlashKeys - 1) / kFlashKeys;
     const int tps = (n_tiles + n_split - 1) / n_split;
     const int t_begin = z * tps, t_end = min(n_tiles, t_begin + tps);
+    // iteration i of a wave is tile t_begin + i, or t_begin + 2 i + half
+    const int n_it = __builtin_amdgcn_readfirstlane(max(0, KSPLIT ? (t_end - t_begin + 1) / 2 : t_end - t_begin));
+    auto tile_of = [&](int i) { return KSPLIT ? t_begin + 2 * i + half : t_begin + i; };
     const float scale = 1.4426950408889634f / sqrtf((float)D);
 
-    bf16x8 qf[D / 16], ql[TWO ? D / 16 : 1];
+    // tiles: a 1 KB load instruction fills four key rows of 256 bytes; lane -> (row lane/16, 16-byte position lane%16
+    // holding chunk position ^ swz(row)).  The swizzle spreads both kinds of reads over all banks: the 16 rows of an S^T
+    // read take 16 different positions, and so do the (row, chunk) pairs of a transposing V read.
+    auto swz = [](int r) { return ((r & 3) << 2) | ((r >> 2) & 3); };
+    constexpr int kLoads = FORM == kFlashShared ? 2 : 4;  // instructions per wave for one tile
+    const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+    const bf16_t *kbase = kc + (size_t)g * max_seq * D, *vbase = vc + (size_t)g * max_seq * D;
+    auto slot_k = [&](int i) { return FORM == kFlashShared ? (i & 3) * kFlashTile : (half * 4 + (i & 1)) * kFlashTile; };
+    auto slot_v = [&](int i) { return FORM == kFlashShared ? (4 + (i & 3)) * kFlashTile : (half * 4 + 2 + (i & 1)) * kFlashTile; };
+    auto load_tile = [&](const bf16_t *base, int i, int slot) {
+        const int key0 = tile_of(i) * kFlashKeys;
 #pragma unroll
-    for (int s = 0; s < D / 16; ++s) {
-        qf[s] = as_bf16x8(*reinterpret_cast<const u32x4 *>(qb + (size_t)(fw.row_base + qtok) * ldq + head * D + 16 * s + 8 * kg));
-        if constexpr (TWO)
-            ql[s] = as_bf16x8(*reinterpret_cast<const u32x4 *>(qb_lo + (size_t)(fw.row_base + qtok) * ldq + head * D + 16 * s + 8 * kg));
+        for (int e = 0; e < kLoads; ++e) {
+            const int r4 = (wave % (16 / kLoads) * kLoads + e) * 4, r = r4 + (lane >> 4);
+            const int c = (lane & 15) ^ swz(r);
+            const int kabs = min(key0 + r, n_keys - 1);  // clamped rows lie above the diagonal: masked
+            load_to_lds16(base, (uint32_t)kabs * (D * 2) + c * 16, lds0 + slot + r4 * 256);
+        }
+    };
+    // K runs kLead + 1 and V kLead iterations ahead.  With shared tiles (two leads) each half loads a part of them, and
+    // waves 0-3 read theirs a slot before waves 4-7 could have waited for parts requested in the iteration before.
+    constexpr int kLead = FORM == kFlashShared ? 2 : 1;
+    if (!PAIR && n_it > 0) {
+        load_tile(kbase, 0, slot_k(0));
+        load_tile(vbase, 0, slot_v(0));
+    }
+    if (PAIR && n_it > 0) {  // (tiles past the last one: rows of the last key, never used)
+        for (int i = 0; i <= kLead; ++i) load_tile(kbase, i, slot_k(i));
+        for (int i = 0; i < kLead; ++i) load_tile(vbase, i, slot_v(i));
+    }
+
+    bf16x8 qf[D / 16], ql[TWO ? D / 16 : 1];
+    {
+        const size_t q0 = (size_t)(fw.row_base + qtok) * ldq + head * D + 8 * kg;
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s) {
+            qf[s] = as_bf16x8(*reinterpret_cast<const u32x4 *>(qb + q0 + 16 * s));
+            if constexpr (TWO) ql[s] = as_bf16x8(*reinterpret_cast<const u32x4 *>(qb_lo + q0 + 16 * s));
+        }
     }
 
     f32x16 o[D / 32];
@@ -1379,91 +1427,72 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_long(const bf16_t *__restr
         for (int r = 0; r < 16; ++r) o[t][r] = 0.f;
     float m_i = -INFINITY, l_i = 0.f;
 
-    const bf16_t *kbase = kc + (size_t)g * max_seq * D;
-    const bf16_t *vbase = vc + (size_t)g * max_seq * D;
-    const uint32_t ks0 = (uint32_t)(uintptr_t)&Ks[0][0];
-    // K: a wave loads 64/NW key rows of the tile with 1 KB instructions of four 256-byte rows each;
-    // lane -> (row lane/16, 16-byte position lane%16 holding chunk position ^ (row & 15))
-    constexpr int KI = 16 / NW;  // K instructions per wave per tile
-    auto load_k = [&](int t) {
-        const int key0 = t * kFlashKeys;
-#pragma unroll
-        for (int i = 0; i < KI; ++i) {
-            const int r4 = (wave * KI + i) * 4, r = r4 + (lane >> 4);
-            const int c = (lane & 15) ^ (r & 15);
-            const int kabs = min(key0 + r, n_keys - 1);  // clamped rows lie above the diagonal: masked
-            load_to_lds16(kbase + (size_t)kabs * D + c * 8, ks0 + (t & 1) * (kFlashKeys * D * 2) + r4 * 256);
-        }
-    };
-    // V: thread -> keys 2*(tid%32), +1 of 8-column groups tid/32 + (NT/32)*q; written transposed, two keys per word
-    constexpr int VQ = 16 / (NT / 32);
-    u32x4 vr[VQ][2];
-    auto load_v = [&](int t) {
-        const int key0 = t * kFlashKeys;
-#pragma unroll
-        for (int q = 0; q < VQ; ++q)
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const int kabs = min(key0 + 2 * (tid & 31) + p, n_keys - 1);
-                vr[q][p] = *reinterpret_cast<const u32x4 *>(vbase + (size_t)kabs * D + ((tid >> 5) + (NT / 32) * q) * 8);
-            }
-    };
-    auto stash_v = [&](int t) {
-        bf16_t *vt = &Vt[t & 1][0];
-        const int kp = tid & 31;
-#pragma unroll
-        for (int q = 0; q < VQ; ++q) {
-            const int col = (tid >> 5) + (NT / 32) * q;
-            const uint32_t a[4] = {vr[q][0].x, vr[q][0].y, vr[q][0].z, vr[q][0].w};
-            const uint32_t b[4] = {vr[q][1].x, vr[q][1].y, vr[q][1].z, vr[q][1].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                *reinterpret_cast<uint32_t *>(&vt[(8 * col + 2 * e) * VS + 2 * kp]) = (a[e] & 0xffffu) | (b[e] << 16);
-                *reinterpret_cast<uint32_t *>(&vt[(8 * col + 2 * e + 1) * VS + 2 * kp]) =
-                    (a[e] >> 16) | (b[e] & 0xffff0000u);
-            }
-        }
-    };
-
     // S^T fragment rows: lane i of a 32-key sub-tile reads key swap(i)
     const int krow = (l32 & 19) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
-    const int k_swz = krow & 15;
+    const uint32_t k_lane = lds0 + krow * 256 + ((kg ^ swz(krow)) << 4);  // chunk 2 st + kg is at k_lane ^ (st << 5)
+    // V^T: lane 4r + q of a 16-lane group gb reads columns 4q .. 4q + 3 of key row r; its chunk is 4 tt + 2 gb + q / 2
+    const int vr = (lane & 15) >> 2, vq = lane & 3, vgb = (lane >> 4) & 1;
+    const uint32_t v_lane = lds0 + (8 * kg + vr) * 256 + (((vr << 2) | (((vgb << 1) | (vq >> 1)) ^ (kg << 1))) << 4) + (vq & 1) * 8;
 
     f32x16 sacc[2];
     bf16x8 pf[4];
-    auto tile_active = [&](int t) { return wave_active && t * kFlashKeys <= wave_last_key; };
-    // S^T of tile t: two 32-key sub-tiles x 32 rows
-    // (fragment reads run kAhead MFMAs ahead of their use, one read pinned behind each MFMA: an LDS read takes
-    // longer than the one or two MFMAs the compiler's own schedule leaves between a read and its use)
-    constexpr int kAhead = 4;
-    auto scores = [&](int t) {
-        if (!tile_active(t)) return;
-        const unsigned char *kt = &Ks[t & 1][0];
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) sacc[u][r] = 0.f;
-        constexpr int NS = D / 16;  // 16-wide steps of a sub-tile; fragment i is sub-tile i / NS, step i % NS
-        bf16x8 kf[kAhead];
-        auto kread = [&](auto i_c) {
-            constexpr int i = decltype(i_c)::value, u = i / NS, s = i % NS;
-            kf[i % kAhead] = as_bf16x8(
-                *reinterpret_cast<const u32x4 *>(kt + (u * 32 + krow) * 256 + (((2 * s + kg) ^ k_swz) * 16)));
-        };
-        static_for<kAhead>([&](auto i_c) { kread(i_c); });
+    auto active = [&](int i) { return wave_active && tile_of(i) < t_end && tile_of(i) * kFlashKeys <= wave_last_key; };
+    constexpr int kAhead = 4, NS = 2 * D / 16, NV = (D / 32) * 4;
+    // MFMAs of one slot: S^T of iteration i + 1 (two 32-key sub-tiles x 32 rows) and O^T += V^T P^T of iteration i, one
+    // fragment of each in turn (a dependent pair of S^T MFMAs keeps one of the others between it), fragment reads kAhead
+    // ahead of their use; the first ones are issued by open_reads, before the barrier in front of the slot.
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+    bf16x8 kf[kAhead], vf[kAhead];
+    uint32_t kt, vt;  // (tiles are 256-byte aligned: xor stays inside)
+    auto kread = [&](auto n_c) {  // S fragment n: sub-tile n % 2, 16-wide step n / 2
+        constexpr int n = decltype(n_c)::value, u = n % 2, st = n / 2;
+        kf[n % kAhead] = as_bf16x8(*((const lds_u32x4 *)(uintptr_t)((kt ^ (st << 5)) + u * 32 * 256)));
+    };
+    auto vread = [&](auto n_c) {  // V fragment n: output tile n % 4, 16-key step n / 4; two reads of four keys
+        constexpr int n = decltype(n_c)::value, tt = n % 4, s2 = n / 4;
+        const uint32_t a0 = (vt ^ (tt << 6)) + s2 * 4096, a1 = (vt ^ (tt << 6) ^ 16) + s2 * 4096 + 1024;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(uintptr_t)a0);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(uintptr_t)a1);
+        const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+        vf[n % kAhead] = as_bf16x8(u32x4{l2.x, l2.y, h2.x, h2.y});
+    };
+    auto open_reads = [&](auto do_s_c, auto do_pv_c, int i) {
+        kt = k_lane + slot_k(i + 1), vt = v_lane + slot_v(i);
+        if constexpr (decltype(do_s_c)::value != 0) static_for<kAhead>([&](auto n_c) { kread(n_c); });
+        if constexpr (decltype(do_pv_c)::value != 0) static_for<kAhead>([&](auto n_c) { vread(n_c); });
         __builtin_amdgcn_sched_barrier(0);
-        static_for<2 * NS>([&](auto i_c) {
-            constexpr int i = decltype(i_c)::value, u = i / NS, s = i % NS;
-            sacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i % kAhead], qf[s], sacc[u], 0, 0, 0);
-            if constexpr (TWO) sacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i % kAhead], ql[s], sacc[u], 0, 0, 0);
-            if constexpr (i + kAhead < 2 * NS) kread(ic<i + kAhead>{});
-            __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](auto do_s_c, auto do_pv_c) {
+        constexpr bool do_s = decltype(do_s_c)::value != 0, do_pv = decltype(do_pv_c)::value != 0;
+        if constexpr (do_s) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sacc[u][r] = 0.f;
+        }
+        static_assert(NS == NV, "one fragment of each in turn");
+        static_for<NS>([&](auto n_c) {
+            constexpr int n = decltype(n_c)::value, u = n % 2, st = n / 2, tt = n % 4, s2 = n / 4;
+            if constexpr (do_s) {
+                sacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[n % kAhead], qf[st], sacc[u], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (do_pv) {
+                o[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[n % kAhead], pf[s2], o[tt], 0, 0, 0);
+                if constexpr (n + kAhead < NV) vread(ic<n + kAhead>{});
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (do_s) {
+                if constexpr (TWO) sacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[n % kAhead], ql[st], sacc[u], 0, 0, 0);
+                if constexpr (n + kAhead < NS) kread(ic<n + kAhead>{});
+                __builtin_amdgcn_sched_barrier(0);
+            }
         });
     };
-    // online softmax of tile t: lane = query row; register r of sub-tile u is key 32u + 16*(r/8) + 8*kg + r%8
-    auto softmax = [&](int t) {
-        if (!tile_active(t)) return;
-        const int key0 = t * kFlashKeys;
+    // online softmax of iteration i: lane = query row; register r of sub-tile u is key 32u + 16*(r/8) + 8*kg + r%8
+    auto softmax = [&](int i) {
+        const int key0 = tile_of(i) * kFlashKeys;
         if (key0 + kFlashKeys - 1 > wave_first_q) {  // the tile touches the diagonal for some row of this wave
 #pragma unroll
             for (int u = 0; u < 2; ++u)
@@ -1512,43 +1541,88 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_long(const bf16_t *__restr
             pf[s2] = as_bf16x8(pk);
         }
     };
-    // O^T += V^T P^T for tile t
-    auto weighted_values = [&](int t) {
-        if (!tile_active(t)) return;
-        const bf16_t *vt = &Vt[t & 1][0];
-        constexpr int NV = (D / 32) * 4;  // fragment i: output tile i / 4, 16-key step i % 4
-        bf16x8 vf[kAhead];
-        auto vread = [&](auto i_c) {
-            constexpr int i = decltype(i_c)::value, tt = i / 4, s2 = i % 4;
-            vf[i % kAhead] = as_bf16x8(*reinterpret_cast<const u32x4 *>(&vt[(tt * 32 + l32) * VS + 16 * s2 + 8 * kg]));
-        };
-        static_for<kAhead>([&](auto i_c) { vread(i_c); });
-        __builtin_amdgcn_sched_barrier(0);
-        static_for<NV>([&](auto i_c) {
-            constexpr int i = decltype(i_c)::value, tt = i / 4, s2 = i % 4;
-            o[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i % kAhead], pf[s2], o[tt], 0, 0, 0);
-            if constexpr (i + kAhead < NV) vread(ic<i + kAhead>{});
-            __builtin_amdgcn_sched_barrier(0);
-        });
-    };
 
-    // One barrier per tile: before it a wave writes its part of V^T(t) and waits for its part of K(t); after it
-    // the loads of tile t+1 start into the other slots, which every wave finished reading before the barrier.
-    if (t_begin < t_end) {
-        load_k(t_begin);
-        load_v(t_begin);
-    }
-    for (int t = t_begin; t < t_end; ++t) {
-        stash_v(t);
+    // Slots: waves 0-3 run S(0) in slot 0, softmax(i) in slot 2i + 1, the MFMAs of iteration i in slot 2i + 2; waves 4-7
+    // one slot later.  A wave requests its part of K(i + 1 + kLead) and V(i + kLead) at the start of its softmax(i) and
+    // waits for it at the end of its next slot; the barrier that ends that slot lies before the first read of these
+    // tiles.  The tiles overwritten, K(i - 1) and V(i - 2) (KSPLIT: K(i) and V(i - 1)), were last read in a slot that has
+    // ended for both halves (KSPLIT: for this one).
+    if (!PAIR && n_it > 0) {
         wait_loads<0>();
         __builtin_amdgcn_s_barrier();
-        if (t + 1 < t_end) {
-            load_k(t + 1);
-            load_v(t + 1);
+        for (int i = 0; i < n_it; ++i) {
+            if (i + 1 < n_it) {
+                load_tile(kbase, i + 1, slot_k(i + 1));
+                load_tile(vbase, i + 1, slot_v(i + 1));
+            }
+            if (active(i)) {
+                open_reads(ic<1>{}, ic<0>{}, i - 1);
+                multiply(ic<1>{}, ic<0>{});
+                softmax(i);
+                open_reads(ic<0>{}, ic<1>{}, i);
+                multiply(ic<0>{}, ic<1>{});
+            }
+            if (i + 1 < n_it) {
+                wait_loads<0>();
+                __builtin_amdgcn_s_barrier();  // tile i + 1 is whole, and tile i has been read by every wave
+            }
         }
-        scores(t);
-        softmax(t);
-        weighted_values(t);
+    }
+    if (PAIR && n_it > 0) {
+        wait_loads<0>();
+        __builtin_amdgcn_s_barrier();
+        if (half) __builtin_amdgcn_s_barrier();
+        open_reads(ic<1>{}, ic<0>{}, -1);
+        multiply(ic<1>{}, ic<0>{});
+        __builtin_amdgcn_s_barrier();
+        // (a tile beyond the wave's last key has zero weights; its scores are computed and not used)
+        auto weights = [&](int i) {
+            if (active(i)) {
+                softmax(i);
+            } else {
+#pragma unroll
+                for (int s2 = 0; s2 < 4; ++s2) pf[s2] = as_bf16x8(u32x4{0, 0, 0, 0});
+            }
+        };
+        for (int i = 0; i + 1 < n_it; ++i) {
+            if (i + 1 + kLead < n_it) load_tile(kbase, i + 1 + kLead, slot_k(i + 1 + kLead));
+            if (i + kLead < n_it) load_tile(vbase, i + kLead, slot_v(i + kLead));
+            weights(i);
+            open_reads(ic<1>{}, ic<1>{}, i);
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_s_setprio(1);
+            multiply(ic<1>{}, ic<1>{});
+            __builtin_amdgcn_s_setprio(0);
+            wait_loads<0>();
+            __builtin_amdgcn_s_barrier();
+        }
+        weights(n_it - 1);
+        open_reads(ic<0>{}, ic<1>{}, n_it - 1);
+        __builtin_amdgcn_s_barrier();
+        multiply(ic<0>{}, ic<1>{});
+        __builtin_amdgcn_s_barrier();
+        if (!half) __builtin_amdgcn_s_barrier();
+    }
+    if constexpr (KSPLIT) {  // the odd tiles' half hands its (max, sum, output) over through LDS
+        float *xo = reinterpret_cast<float *>(smem) + w4 * 64 * 64 + lane;
+        float *xm = reinterpret_cast<float *>(smem) + 4 * 64 * 64 + w4 * 128 + lane;
+        if (half) {
+#pragma unroll
+            for (int tt = 0; tt < D / 32; ++tt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) xo[(tt * 16 + r) * 64] = o[tt][r];
+            xm[0] = m_i, xm[64] = l_i;
+        }
+        __syncthreads();
+        if (half) return;
+        const float m2 = xm[0], l2 = xm[64], mm = fmaxf(m_i, m2);
+        const float e1 = m_i == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_i - mm);
+        const float e2 = m2 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m2 - mm);
+        m_i = mm, l_i = l_i * e1 + l2 * e2;
+#pragma unroll
+        for (int tt = 0; tt < D / 32; ++tt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[tt][r] = o[tt][r] * e1 + xo[(tt * 16 + r) * 64] * e2;
     }
     if (!wave_active || rw0 + l32 >= rows) return;
     if (n_split == 1) {
@@ -1587,61 +1661,73 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_long(const bf16_t *__restr
     }
 }
 
-// Merges the key splits of one (token, head): block = 256 threads = 256/D rows x D elements.  The (max, sum) pairs
-// of all splits (at most 32) are fetched by the first threads of each row in one go and turned into weights in
-// LDS; the partial outputs are then loaded eight splits at a time, so nothing waits on a chain of dependent loads.
-// Splits are added in ascending order.
-template <int D>
+// Merges the key splits of one (token, head): a thread owns four consecutive elements of a row, D/4 threads a row, and
+// SG such groups share a row's splits (group j takes splits j, j + SG, ...; the groups are added in order).  The (max,
+// sum) pairs of all splits (at most 32) are fetched in one go into LDS; the partial outputs are loaded several splits at
+// a time, so nothing waits on a chain of dependent loads.  (With one element per thread 28000 rows of two splits took
+// 18.6 us, now 9; few rows of many splits want the groups: 252 rows of 21 splits 7.1 us with one group, 4.6 with four.)
+template <int D, int SG>
 __global__ __launch_bounds__(256) void k_flash_combine(const float *__restrict__ part_o,
                                                        const float *__restrict__ part_ml, int n_split, int n_rows,
                                                        bf16_t *__restrict__ out, bf16_t *__restrict__ outlo, int f16) {
-    constexpr int RPB = 256 / D, kMaxSplits = 32;
-    __shared__ float m_s[RPB][kMaxSplits], w_s[RPB][kMaxSplits], l_s[RPB];
-    const int g = threadIdx.x / D, e = threadIdx.x % D;
+    constexpr int TPR = D / 4, RPB = 256 / TPR / SG, kMaxSplits = 32, kBatch = SG == 1 ? 8 : 4;
+    __shared__ float m_s[RPB][kMaxSplits], l_s[RPB][kMaxSplits];
+    __shared__ float4 red[SG > 1 ? SG - 1 : 1][RPB][TPR];
+    const int e = threadIdx.x % TPR, j = threadIdx.x / TPR % SG, g = threadIdx.x / (TPR * SG);
     const int r = blockIdx.x * RPB + g;
     const bool live = r < n_rows;
-    float2 ml = make_float2(-INFINITY, 0.f);
-    if (live && e < n_split) ml = reinterpret_cast<const float2 *>(part_ml)[(size_t)e * n_rows + r];
-    if (e < kMaxSplits) m_s[g][e] = ml.x;
+    for (int z = e + TPR * j; z < n_split; z += TPR * SG) {
+        const float2 ml = live ? reinterpret_cast<const float2 *>(part_ml)[(size_t)z * n_rows + r] : make_float2(-INFINITY, 0.f);
+        m_s[g][z] = ml.x, l_s[g][z] = ml.y;
+    }
+    const float4 *po = reinterpret_cast<const float4 *>(part_o) + (size_t)(live ? r : 0) * TPR + e;
+    const size_t stride = (size_t)n_rows * TPR;
+    float4 v[kBatch];
+    auto load = [&](int z0) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            v[u] = z0 + u * SG < n_split ? po[(size_t)(z0 + u * SG) * stride] : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    load(j);
     __syncthreads();
     float M = -INFINITY;
     for (int z = 0; z < n_split; ++z) M = fmaxf(M, m_s[g][z]);
-    if (e < kMaxSplits) {
-        const float w = ml.x == -INFINITY ? 0.f : exp2f(ml.x - M);
-        w_s[g][e] = w;
-        m_s[g][e] = w * ml.y;   // reused: weighted row sums
-    }
-    __syncthreads();
-    if (e == 0) {
-        float L = 0.f;
-        for (int z = 0; z < n_split; ++z) L += m_s[g][z];
-        l_s[g] = L;
-    }
-    float A = 0.f;
-    if (live) {
-        for (int z0 = 0; z0 < n_split; z0 += 8) {
-            float v[8];
+    auto weight = [&](int z) { return m_s[g][z] == -INFINITY ? 0.f : exp2f(m_s[g][z] - M); };
+    float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int z0 = j; z0 < n_split; z0 += kBatch * SG) {
+        if (z0 != j) load(z0);
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                v[u] = z0 + u < n_split ? part_o[((size_t)(z0 + u) * n_rows + r) * D + e] : 0.f;
+        for (int u = 0; u < kBatch; ++u)
+            if (z0 + u * SG < n_split) {
+                const float w = weight(z0 + u * SG);
+                A.x += v[u].x * w, A.y += v[u].y * w, A.z += v[u].z * w, A.w += v[u].w * w;
+            }
+    }
+    if constexpr (SG > 1) {
+        if (j) red[j - 1][g][e] = A;
+        __syncthreads();
+        if (j) return;
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (z0 + u < n_split) A += v[u] * w_s[g][z0 + u];
+        for (int i = 0; i < SG - 1; ++i) {
+            const float4 q = red[i][g][e];
+            A.x += q.x, A.y += q.y, A.z += q.z, A.w += q.w;
         }
     }
-    __syncthreads();
     if (!live) return;
-    const float v = A / l_s[g];
-    const bf16_t hi = to_16(f16, v);
-    out[(size_t)r * D + e] = hi;
-    if (outlo) outlo[(size_t)r * D + e] = f32_to_bf16(v - bf16_to_f32(hi));
+    float L = 0.f;
+    for (int z = 0; z < n_split; ++z) L += weight(z) * l_s[g][z];
+    const float v0 = A.x / L, v1 = A.y / L, v2 = A.z / L, v3 = A.w / L;
+    const u32x2 pk = {pack_16x2(f16, v0, v1), pack_16x2(f16, v2, v3)};
+    reinterpret_cast<u32x2 *>(out)[(size_t)r * TPR + e] = pk;
+    if (outlo) {
+        const u32x2 lo = {pack_bf16x2(v0 - bf16_lo(pk.x), v1 - bf16_hi(pk.x)), pack_bf16x2(v2 - bf16_lo(pk.y), v3 - bf16_hi(pk.y))};
+        reinterpret_cast<u32x2 *>(outlo)[(size_t)r * TPR + e] = lo;
+    }
 }
 
 // ---------------------------------------------------------------------------------------
 // launcher
 // ---------------------------------------------------------------------------------------
-constexpr int kLongWaves = 4;  // waves per block of k_flash_long
-
 constexpr int kInvariantRows = 64;  // most rows of a batched decode step (see stream_shape)
 
 // Floats the split-K partial buffer (ws.qkv) holds (the workspace is carved with the same figure).
@@ -1698,6 +1784,9 @@ hipError_t raise_lds_limits() {
 #define ST_RING_LIMIT(D, H)                                                                                 \
     take(raise_one(k_gemm_ring<D, H, 1, false>)), take(raise_one(k_gemm_ring<D, H, 1, true>)), \
         take(raise_one(k_gemm_ring<D, H, 2, false>));
+    take(raise_one(k_flash_long<false, kFlashSingle>)), take(raise_one(k_flash_long<true, kFlashSingle>));
+    take(raise_one(k_flash_long<false, kFlashSplit>)), take(raise_one(k_flash_long<true, kFlashSplit>));
+    take(raise_one(k_flash_long<false, kFlashShared>));
     ST_RING_LIMIT(false, false) ST_RING_LIMIT(false, true) ST_RING_LIMIT(true, false) ST_RING_LIMIT(true, true)
 #undef ST_RING_LIMIT
     take(raise_one(k_gemm_stream<1, 64, true, 1, true>)), take(raise_one(k_gemm_stream<2, 64, true, 1, true>));
@@ -2146,51 +2235,62 @@ static void launch_flash(const Model &m, const bf16_t *qb, const bf16_t *qb_lo, 
     if (splits > n_tiles) splits = n_tiles;
     if (splits > 32) splits = 32;
     const size_t cap = partial_floats(c);
-    if (long_chunk && !ragged) {
-        // k_flash_long: the count that minimises (rounds of resident blocks) x (tiles per block + 2 for the set-up
-        // and the store) x the time of a tile step, plus the merge pass over the partial results (its bytes at
-        // 4 TB/s + a launch).  640 blocks of 42 tiles on 512 slots are two rounds; 960 blocks of 27 are two shorter ones.
-        const int slots = 512;                      // two blocks per CU
-        const double step_us = qb_lo ? 2.2 : 1.7;   // a tile step with / without the second term of the queries
+    int form = kFlashSingle, nbx = rblocks;
+    if (long_chunk) {
+        // k_flash_long: of the block forms and the split counts, the one that minimises (rounds of resident blocks) x
+        // (iterations per block x the time of one + what a block spends before and after them) + the partial results
+        // written, and the merge pass that reads them.  From four rounds on the unequal (causal) blocks balance out,
+        // longest first.  Microseconds, fitted to rocprofv3 times at 2 to 4096 rows of the three model shapes.
+        const double two = qb_lo ? 1.0 : 0.8;
         double best = -1;
-        // (from two rounds of blocks on, the causal spread of their lengths, longest first, balances the CUs
-        // better than splitting does, and the merge pass would cost more than it saves: measured at 4096 rows)
-        const int sp_max = rblocks * nkv >= 2 * slots ? 1 : (n_tiles < 32 ? n_tiles : 32);
-        for (int sp = 1; sp <= sp_max; ++sp) {
-            if (sp > 1 && (size_t)sp * n * nq * (d + 2) > cap) break;
-            const int tps = (n_tiles + sp - 1) / sp, used = (n_tiles + tps - 1) / tps;
-            if (used != sp) continue;  // the same blocks as a smaller count
-            const int rounds = (rblocks * nkv * sp + slots - 1) / slots;
-            const double merge = sp > 1 ? 3.0 + (double)n * nq * d * 4 * (sp + 1) / 4e6 : 0.0;
-            const double cost = rounds * (tps + 2) * step_us + merge;
-            if (best < 0 || cost < best) best = cost, splits = sp;
+        for (int f = kFlashSingle; f <= kFlashShared; ++f) {
+            if (f == kFlashShared && (ragged || qb_lo)) continue;  // (two-term queries leave it no registers)
+            const int nb = f == kFlashShared ? (rblocks + 1) / 2 : rblocks;
+            const int sp_max = nb * nkv >= 1024 ? 1 : (n_tiles < 32 ? n_tiles : 32);
+            for (int sp = 1; sp <= sp_max; ++sp) {
+                if (sp > 1 && (size_t)sp * n_rows_all * nq * (d + 2) > cap) break;
+                const int tps = (n_tiles + sp - 1) / sp, used = (n_tiles + tps - 1) / tps;
+                if (used != sp) continue;  // the same blocks as a smaller count
+                const int blocks = nb * nkv * sp, slots = f == kFlashSingle ? 512 : 256;
+                const int its = f == kFlashSplit ? (tps + 1) / 2 : tps;
+                const double rounds = blocks <= 4 * slots ? (double)((blocks + slots - 1) / slots) : (double)blocks / slots;
+                const double rows_bytes = (double)n_rows_all * nq * d * 4;
+                const double merge = sp > 1 ? sp * rows_bytes / 4e6 + 3.0 + (sp + 1) * rows_bytes / 4e6 : 0.0;
+                const double cost = rounds * (its * 2.6 * two + (f == kFlashSingle ? 6.5 : 10.0)) + merge;
+                if (best < 0 || cost < best) best = cost, splits = sp, form = f, nbx = nb;
+            }
         }
     }
     while (splits > 1 && (size_t)splits * n_rows_all * nq * (d + 2) > cap) --splits;
     float *part_o = w.qkv, *part_ml = w.qkv + (size_t)splits * n_rows_all * nq * d;
-    dim3 fgrid(rblocks, nkv, splits);
     const FlashSeg *segs = ragged ? ragged->segs_dev : nullptr;
     const int n_seg = ragged ? ragged->n_seg : 0;
     const size_t seq_stride = ragged ? ragged->seq_stride : 0;
-    if (long_chunk && qb_lo)
-        hipLaunchKernelGGL((k_flash_long<kLongWaves, true>), fgrid, dim3(64 * kLongWaves), 0, m.stream, qb, qb_lo, kc, vc,
-                           attn, attn_lo, part_o, part_ml, n, pos0, nq, G, c.max_seq, segs, n_seg, seq_stride, n_rows_all,
-                           (int)f16_out);
-    else if (long_chunk)
-        hipLaunchKernelGGL((k_flash_long<kLongWaves, false>), fgrid, dim3(64 * kLongWaves), 0, m.stream, qb, qb_lo, kc, vc,
-                           attn, attn_lo, part_o, part_ml, n, pos0, nq, G, c.max_seq, segs, n_seg, seq_stride, n_rows_all,
-                           (int)f16_out);
-    else
-        hipLaunchKernelGGL(k_flash_prefill<64>, fgrid, dim3(256), 0, m.stream, qb, kc, vc, attn, attn_lo, part_o,
-                           part_ml, n, pos0, nq, G, c.max_seq, segs, n_seg, seq_stride, n_rows_all, (int)f16_out);
+#define ST_FLASH(TWOV, FORMV)                                                                                              \
+    hipLaunchKernelGGL((k_flash_long<TWOV, FORMV>), dim3(nbx * nkv * splits), dim3(FORMV == kFlashSingle ? 256 : 512),     \
+                       FORMV == kFlashSingle ? kFlashLds / 2 : kFlashLds, m.stream, qb, qb_lo, kc, vc, attn, attn_lo,      \
+                       part_o, part_ml, n, pos0, nq, nkv, c.max_seq, segs, n_seg, seq_stride, n_rows_all, (int)f16_out, nbx, \
+                       splits)
+    if (!long_chunk)
+        hipLaunchKernelGGL(k_flash_prefill<64>, dim3(rblocks, nkv, splits), dim3(256), 0, m.stream, qb, kc, vc, attn, attn_lo,
+                           part_o, part_ml, n, pos0, nq, G, c.max_seq, segs, n_seg, seq_stride, n_rows_all, (int)f16_out);
+    else if (qb_lo && form == kFlashSingle) ST_FLASH(true, kFlashSingle);
+    else if (qb_lo) ST_FLASH(true, kFlashSplit);
+    else if (form == kFlashSingle) ST_FLASH(false, kFlashSingle);
+    else if (form == kFlashSplit) ST_FLASH(false, kFlashSplit);
+    else ST_FLASH(false, kFlashShared);
+#undef ST_FLASH
     if (splits > 1) {
         const int n_rows = n_rows_all * nq;
-        if (d == 128)
-            hipLaunchKernelGGL(k_flash_combine<128>, dim3((n_rows + 1) / 2), dim3(256), 0, m.stream, part_o, part_ml,
-                               splits, n_rows, attn, attn_lo, (int)f16_out);
-        else
-            hipLaunchKernelGGL(k_flash_combine<64>, dim3((n_rows + 3) / 4), dim3(256), 0, m.stream, part_o, part_ml,
-                               splits, n_rows, attn, attn_lo, (int)f16_out);
+#define ST_COMBINE(DV, SGV)                                                                                            \
+    hipLaunchKernelGGL((k_flash_combine<DV, SGV>), dim3((n_rows * (DV / 4) * SGV + 255) / 256), dim3(256), 0, m.stream, \
+                       part_o, part_ml, splits, n_rows, attn, attn_lo, (int)f16_out)
+        const bool groups = n_rows <= 1024 && splits >= 4;
+        if (d == 128 && groups) ST_COMBINE(128, 4);
+        else if (d == 128) ST_COMBINE(128, 1);
+        else if (groups) ST_COMBINE(64, 4);
+        else ST_COMBINE(64, 1);
+#undef ST_COMBINE
     }
 }
 
