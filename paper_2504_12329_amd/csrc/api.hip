@@ -670,14 +670,7 @@ int st_trigger_scan(const st_trigger_rule *rule, const int32_t *tokens, int32_t 
     if (!scratch) return fail(ST_EINVAL, "host outputs need a device scratch of cap+1 int32");
     launch_trigger_scan(*rule, tokens, lo, hi, scratch + 1, cap, scratch, s);
     if (int rc = check_launch("trigger scan")) return rc;
-    ST_HIP(hipMemcpyAsync(n_found, scratch, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    ST_HIP(hipStreamSynchronize(s));
-    int32_t k = *n_found < cap ? *n_found : cap;
-    if (k > 0) {
-        ST_HIP(hipMemcpyAsync(positions, scratch + 1, sizeof(int32_t) * k, hipMemcpyDeviceToHost, s));
-        ST_HIP(hipStreamSynchronize(s));
-    }
-    return ST_OK;
+    return deliver_scan(scratch, hi - lo, positions, cap, n_found, s);
 }
 
 int st_handoff(st_model *small, st_model *large, int32_t *seq, int32_t *T, int32_t n_large, int32_t budget,
@@ -943,6 +936,20 @@ struct Batch {
 };
 constexpr int kMaxBatch = 64;
 
+// Host buffers that an enqueued copy reads live as long as this: every way out of the scope waits for the stream, once.
+struct WaitForStream {
+    hipStream_t s;
+    bool done = false;
+    explicit WaitForStream(hipStream_t stream) : s(stream) {}
+    hipError_t now() {
+        done = true;
+        return hipStreamSynchronize(s);
+    }
+    ~WaitForStream() {
+        if (!done) (void)hipStreamSynchronize(s);
+    }
+};
+
 size_t batch_extra(const st_config &c, int32_t n, char *base, Batch *b) {
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -1070,8 +1077,8 @@ int st_batch_decode_step(st_batch *h, int32_t n_rows, const int32_t *seqs, const
         if (b->kv_len[s] > max_pos) max_pos = b->kv_len[s];
     }
     int32_t *dev = b->row_ints;
+    WaitForStream wait{b->base.stream};  // `host` is read by the copy
     ST_HIP(hipMemcpyAsync(dev, host.data(), sizeof(int32_t) * host.size(), hipMemcpyHostToDevice, b->base.stream));
-    ST_HIP(hipStreamSynchronize(b->base.stream));  // `host` leaves scope before the copy would otherwise be read
     BatchRows rows = {dev, dev + n_rows, dev + 2 * (size_t)n_rows, dev + 3 * b->row_cap, b->seq_stride,
                       b->q_rows, b->o_rows, b->part_ml, b->part_acc, logits ? b->logits : nullptr, nullptr};
     launch_batch_step(b->base, rows, n_rows, attn_bucket(max_pos + 1));
@@ -1082,7 +1089,7 @@ int st_batch_decode_step(st_batch *h, int32_t n_rows, const int32_t *seqs, const
     if (next_tokens)
         ST_HIP(hipMemcpyAsync(next_tokens, rows.row_next, sizeof(int32_t) * n_rows, hipMemcpyDeviceToHost,
                               b->base.stream));
-    ST_HIP(hipStreamSynchronize(b->base.stream));
+    ST_HIP(wait.now());
     for (int32_t r = 0; r < n_rows; ++r) b->kv_len[seqs[r]] += 1;
     return ST_OK;
 }
@@ -1124,10 +1131,10 @@ int st_batch_prefill_many(st_batch *h, int32_t n, const int32_t *seqs, const int
     }
     int32_t *dev = b->row_ints, *next = dev + 3 * b->row_cap;
     hipStream_t st = b->base.stream;
+    WaitForStream wait{st};  // `host` and `segs` are read by the copies
     ST_HIP(hipMemcpyAsync(dev, host.data(), sizeof(int32_t) * 3 * (size_t)R, hipMemcpyHostToDevice, st));
     ST_HIP(hipMemcpyAsync(next, host.data() + 3 * (size_t)R, sizeof(int32_t) * n, hipMemcpyHostToDevice, st));
     ST_HIP(hipMemcpyAsync(b->seg_tab, segs.data(), sizeof(FlashSeg) * n, hipMemcpyHostToDevice, st));
-    ST_HIP(hipStreamSynchronize(st));
     BatchRows rows = {dev, dev + R, dev + 2 * (size_t)R, next, b->seq_stride, b->q_rows, b->o_rows, b->part_ml,
                       b->part_acc, logits ? b->logits : nullptr, b->seg_tab};
     set_pass_mode(&b->base, kPassDefault);
@@ -1135,7 +1142,7 @@ int st_batch_prefill_many(st_batch *h, int32_t n, const int32_t *seqs, const int
     if (int rc = check_launch("ragged catch-up pass")) return rc;
     if (logits) ST_HIP(hipMemcpyAsync(logits, b->logits, sizeof(float) * (size_t)n * c.vocab, hipMemcpyDeviceToHost, st));
     if (next_tokens) ST_HIP(hipMemcpyAsync(next_tokens, next, sizeof(int32_t) * n, hipMemcpyDeviceToHost, st));
-    ST_HIP(hipStreamSynchronize(st));
+    ST_HIP(wait.now());
     for (int32_t j = 0; j < n; ++j) b->kv_len[seqs[j]] += lens[j];
     return ST_OK;
 }

@@ -233,5 +233,7 @@ void launch_prefill_varlen(const Model &m, const BatchRows &b, const FlashSeg *s
 // ---- launchers (trigger.hip) ----
 void launch_trigger_scan(const st_trigger_rule &rule, const int32_t *tokens, int32_t lo, int32_t hi,
                          int32_t *positions, int32_t cap, int32_t *n_found, hipStream_t stream);
+// Reads a scan's result back (dev[0] the count, then the positions); waits for the stream.
+int deliver_scan(const int32_t *dev, int32_t range, int32_t *positions, int32_t cap, int32_t *n_found, hipStream_t s);
 
 }  // namespace st

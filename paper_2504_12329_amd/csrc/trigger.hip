@@ -9,6 +9,7 @@
 // a position costs O(1) whatever the window; the scan starts w tokens before `lo`, which is as far back as any
 // position of the range looks.  One 1024-thread block walks the tokens in tiles, carries the two maxima from tile
 // to tile and compacts the firing positions in ascending order with wave ballots.
+#include <cstring>
 #include <mutex>
 
 #include "st_device.h"
@@ -30,46 +31,106 @@ __device__ __forceinline__ int wave_running_max(int v, int lane) {
     return v;
 }
 
+// A thread owns four consecutive positions of a 4096-token tile: one block's chain of tiles is bound by the latency of a
+// tile (token load, two dependent bitmap loads, three barriers), not by its work.  4608 / 18000 tokens, kernel alone:
+// 14.4 / 47.2 us with one position per thread, 10.4 / 24.8 us with four.
+constexpr int kScanPer = 4, kScanTile = 1024 * kScanPer;
+
 __global__ __launch_bounds__(1024) void k_trigger_scan(const int32_t *__restrict__ tokens, int lo, int hi,
                                                        const uint32_t *__restrict__ kw,
                                                        const uint32_t *__restrict__ delim, int window, int vocab,
                                                        int32_t *__restrict__ positions, int cap,
                                                        int32_t *__restrict__ n_found) {
     __shared__ int wave_d[16], wave_k[16], wave_n[16];
-    __shared__ int carry_d, carry_k, base;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int w = window - 1;
     const int scan_from = w == 0 ? lo : max(0, lo - w);
-    if (threadIdx.x == 0) carry_d = carry_k = -1, base = 0;
-    __syncthreads();
-    for (int start = scan_from; start < hi; start += 1024) {
-        const int p = start + (int)threadIdx.x;
-        const int id = p < hi ? tokens[p] : -1;  // -1 belongs to no set
-        const bool is_k = in_set(kw, id, vocab), is_d = w > 0 && in_set(delim, id, vocab);
-        const int run_d = wave_running_max(is_d ? p : -1, lane), run_k = wave_running_max(is_k ? p : -1, lane);
-        int before_d = __shfl_up(run_d, 1, kWave);  // lastD(p - 1) within this wave
-        if (lane == 0) before_d = -1;
+    int carry_d = -1, carry_k = -1, base = 0;  // the same in every thread
+    auto fetch = [&](int start, int (&id)[kScanPer]) {
+#pragma unroll
+        for (int e = 0; e < kScanPer; ++e) {
+            const int p = start + (int)threadIdx.x * kScanPer + e;
+            id[e] = p < hi ? tokens[p] : -1;  // -1 belongs to no set
+        }
+    };
+    int id[kScanPer];
+    if (scan_from < hi) fetch(scan_from, id);
+    for (long start = scan_from; start < hi; start += kScanTile) {
+        const int p0 = (int)start + (int)threadIdx.x * kScanPer;
+        bool is_k[kScanPer], is_d[kScanPer];
+        int own_d = -1, own_k = -1;
+#pragma unroll
+        for (int e = 0; e < kScanPer; ++e) {
+            is_k[e] = in_set(kw, id[e], vocab), is_d[e] = w > 0 && in_set(delim, id[e], vocab);
+            if (is_d[e]) own_d = p0 + e;
+            if (is_k[e]) own_k = p0 + e;
+        }
+        if (start + kScanTile < hi) fetch((int)start + kScanTile, id);  // under this tile's reductions
+        const int run_d = wave_running_max(own_d, lane), run_k = wave_running_max(own_k, lane);
+        int last_d = __shfl_up(run_d, 1, kWave), last_k = __shfl_up(run_k, 1, kWave);  // of the lanes before this one
+        if (lane == 0) last_d = last_k = -1;
         if (lane == kWave - 1) wave_d[wave] = run_d, wave_k[wave] = run_k;
         __syncthreads();
-        int pre_d = carry_d, pre_k = carry_k;  // maxima over everything before this wave
-        for (int v = 0; v < wave; ++v) pre_d = max(pre_d, wave_d[v]), pre_k = max(pre_k, wave_k[v]);
-        const int last_d = max(pre_d, before_d), last_k = max(pre_k, run_k);
-        const bool fire = p >= lo && p < hi && (w == 0 ? is_k : (p - w >= 0 && last_d == p - w && last_k > p - w));
-        const unsigned long long mask = __ballot(fire);
-        if (lane == 0) wave_n[wave] = __popcll(mask);
-        __syncthreads();
-        int off = base + __popcll(mask & ((1ull << lane) - 1ull));
-        for (int v = 0; v < wave; ++v) off += wave_n[v];
-        if (fire && off < cap) positions[off] = p;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int tot = 0, md = carry_d, mk = carry_k;
-            for (int v = 0; v < 16; ++v) tot += wave_n[v], md = max(md, wave_d[v]), mk = max(mk, wave_k[v]);
-            base += tot, carry_d = md, carry_k = mk;
+        int all_d = carry_d, all_k = carry_k;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            if (v == wave) last_d = max(last_d, all_d), last_k = max(last_k, all_k);  // everything before this wave
+            all_d = max(all_d, wave_d[v]), all_k = max(all_k, wave_k[v]);
         }
+        carry_d = all_d, carry_k = all_k;
+        unsigned fire = 0;
+#pragma unroll
+        for (int e = 0; e < kScanPer; ++e) {
+            const int p = p0 + e;
+            if (is_k[e]) last_k = p;
+            // here last_d is the last delimiter before p, last_k the last keyword up to p
+            const bool f = p >= lo && p < hi && (w == 0 ? is_k[e] : (p - w >= 0 && last_d == p - w && last_k > p - w));
+            fire |= (unsigned)f << e;
+            if (is_d[e]) last_d = p;
+        }
+        const int cnt = __popc(fire);  // 0 .. 4: its three bits are summed over the lower lanes by ballots
+        const unsigned long long b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2), b2 = __ballot(cnt & 4);
+        if (lane == 0) wave_n[wave] = __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
         __syncthreads();
+        const unsigned long long below = (1ull << lane) - 1ull;
+        int off = __popcll(b0 & below) + 2 * __popcll(b1 & below) + 4 * __popcll(b2 & below), all_n = base;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            if (v == wave) off += all_n;
+            all_n += wave_n[v];
+        }
+        base = all_n;
+#pragma unroll
+        for (int e = 0; e < kScanPer; ++e)
+            if (fire >> e & 1u) {
+                if (off < cap) positions[off] = p0 + e;
+                ++off;
+            }
+        // (wave_d and wave_k were read before the second barrier, and wave_n is next written behind the next tile's first)
     }
     if (threadIdx.x == 0) *n_found = base;
+}
+
+// Copies the result (count and positions, contiguous on the device: count first) to the host: one copy and one wait for
+// up to kScanFirst positions, the rest in a second one.  (Count and positions in turn cost a second round trip: 57 against
+// 34 us for a scan of 4608 tokens with its call.)
+constexpr int kScanFirst = 1024;
+int deliver_scan(const int32_t *dev, int32_t range, int32_t *positions, int32_t cap, int32_t *n_found, hipStream_t s) {
+    int32_t host[1 + kScanFirst];
+    int32_t most = cap < range ? cap : range;
+    const int32_t first = most < kScanFirst ? most : kScanFirst;
+    hipError_t e = hipMemcpyAsync(host, dev, sizeof(int32_t) * (1 + (size_t)first), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return fail(ST_EHIP, "reading the scan's result back: %s", hipGetErrorString(e));
+    *n_found = host[0];
+    const int32_t k = host[0] < cap ? host[0] : cap, now = k < first ? k : first;
+    if (now > 0) memcpy(positions, host + 1, sizeof(int32_t) * (size_t)now);
+    if (k > now) {
+        e = hipMemcpyAsync(positions + now, dev + 1 + now, sizeof(int32_t) * (size_t)(k - now), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return fail(ST_EHIP, "reading the positions back: %s", hipGetErrorString(e));
+    }
+    return ST_OK;
 }
 
 void launch_trigger_scan(const st_trigger_rule &rule, const int32_t *tokens, int32_t lo, int32_t hi,
@@ -129,14 +190,5 @@ extern "C" int st_trigger_scan_static(const st_trigger_rule *rule, const int32_t
     launch_trigger_scan(*rule, tokens, lo, hi, stage + 1, cap, stage, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ST_EHIP, "trigger scan: %s", hipGetErrorString(e));
-    e = hipMemcpyAsync(n_found, stage, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return fail(ST_EHIP, "reading the count back: %s", hipGetErrorString(e));
-    const int32_t k = *n_found < cap ? *n_found : cap;
-    if (k > 0) {
-        e = hipMemcpyAsync(positions, stage + 1, sizeof(int32_t) * k, hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return fail(ST_EHIP, "reading the positions back: %s", hipGetErrorString(e));
-    }
-    return ST_OK;
+    return deliver_scan(stage, hi - lo, positions, cap, n_found, s);
 }

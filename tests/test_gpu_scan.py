@@ -1,0 +1,44 @@
+"""The trigger scan at the edges of its tiles (4096 positions, four per thread), with results above and below what one
+copy brings back (1024 positions), against the rule written out."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2504_12329_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _rule_written_out(toks, kw, dl, lo, hi, window):
+    w = window - 1
+    fire = []
+    for p in range(lo, hi):
+        if w == 0:
+            ok = toks[p] in kw
+        else:
+            ok = p >= w and toks[p - w] in dl and not any(t in dl for t in toks[p - w + 1:p]) and \
+                any(t in kw for t in toks[p - w + 1:p + 1])
+        if ok:
+            fire.append(p)
+    return fire
+
+
+@pytest.mark.parametrize("window", [1, 2, 6, 257])
+@pytest.mark.parametrize("lo,hi", [(0, 0), (0, 1), (3, 6), (0, 4095), (1, 4097), (0, 4097), (4095, 4098), (7, 9001)])
+def test_scan_tile_edges(window, lo, hi):
+    print(f"scan [{lo}, {hi}) window {window}", flush=True)
+    vocab = 64
+    rng = np.random.Generator(np.random.PCG64(hi * 1000 + window))
+    toks = rng.integers(-2, vocab + 2, size=9001, dtype=np.int32)
+    if window > 6:                              # long sentences: few delimiters
+        toks[(toks == 3) | (toks == 5)] = 7
+        toks[::400] = 3
+    kw, dl = set(range(8, 40)), {3, 5}
+    rule = B.TriggerRule(vocab, B.host_bitmap(vocab, kw), B.host_bitmap(vocab, dl) if window > 1 else None, window)
+    dev = torch.from_numpy(toks).cuda()
+    want = _rule_written_out(toks.tolist(), kw, dl, lo, hi, window)
+    for cap in (0, 5, 1024, 1025, 4096):
+        n, pos = B.st_trigger_scan_static(rule, dev, lo, hi, cap)
+        assert n == len(want) and pos.tolist() == want[:cap]
+    n, pos = B.st_trigger_scan(rule, dev, lo, hi, 9001)
+    assert n == len(want) and pos.tolist() == want
