@@ -836,7 +836,9 @@ __global__ __launch_bounds__(SPEC ? 512 : 256) void k_gemm_stream(const bf16_t *
     const int wstage = nt * G::kWTile, a_ring = na * kAStage;
     // SPEC: eight waves, 0-3 multiply and 4-7 load (a wave is held ~70 clocks at every direct load it issues, time
     // the multiplying waves then do not lose); otherwise four waves do both.
-    const bool computes = !SPEC || wave < 4, loads = !SPEC || wave >= 4;
+    // (SPEC: nt may be below four, the multiplying waves past the last weight tile then idle; otherwise nt >= 4, because
+    // a wave that does both issues its loads between its MFMAs)
+    const bool computes = !SPEC || wave < min(4, nt), loads = !SPEC || wave >= 4;
     const int lw = SPEC ? (wave - 4) & 3 : wave;  // loader index: 0, 1 weights; 2, 3 activations
 
     // direct loads: a 1 KB instruction fills kRpi LDS rows; lane -> (row lane/kLpr, 16-byte position lane%kLpr
@@ -1815,15 +1817,17 @@ hipError_t raise_lds_limits() {
     return e;
 }
 
-// Shape of a streaming GEMM launch: K columns per stage, weight tiles per block (4..8), K slices, ring depths.
+// Shape of a streaming GEMM launch: K columns per stage, weight tiles per block (2..8), K slices, ring depths.
 struct StreamShape {
     int bk, nt, splits, kps, nw, na;
 };
 
+constexpr int kSpecTiles = 3;  // most activation tiles of the streaming kernel's form with loading waves of their own
+
 template <int MT, int BK, int TERMS = 2, bool F16 = false>
 static void stream_launch(const Model &m, const StreamShape &sh, const bf16_t *A, const bf16_t *Alo, int lda,
                           const bf16_t *B, int M, int N, int K) {
-    constexpr bool SPEC = MT <= 3;  // eight waves fit the register file up to three activation tiles (measured: a
+    constexpr bool SPEC = MT <= kSpecTiles;  // eight waves fit the register file up to three activation tiles (measured: a
                                     // few percent faster there, slower with four)
     auto kern = k_gemm_stream<MT, BK, SPEC, TERMS, F16>;
     using G = StreamGeom<BK>;
@@ -1835,11 +1839,15 @@ static void stream_launch(const Model &m, const StreamShape &sh, const bf16_t *A
 
 // One block per CU at a time, so the time is (rounds of 256 blocks) x (bytes a block loads, weights and activations
 // alike, + a fixed cost per block); the partial sums written and read again are charged per CU as well.
+// Up to three activation tiles (loading waves of their own): down to two weight tiles per block and two stages per slice,
+// because the small projections of the 1.5B shape are latency, not bytes (with at least four tiles and four stages its batched step of 3 / 16 / 40 rows took 339 / 393 / 452 us for four
+// layers, now 320 / 377 / 435; a pass of 21 rows 1957 -> 1921 us; the 7B and 32B shapes the same within 0.6 %).
 // Up to kInvariantRows rows (the most a batched decode step holds) the K slices are those of a 16-row launch whatever
 // M is, and only the tile count per block follows M: a row's sums are then formed in the same order in every batch,
 // so its logits do not depend on which or how many other rows share the step.
 static StreamShape stream_shape(const Model &m, int M, int N, int K, int terms = 2) {
     const int MT = (M + 31) / 32;
+    const bool spec = MT <= kSpecTiles;
     const int bk = MT * terms <= 8 ? 64 : 32, seg = bk * 2, nk = K / bk;  // 128-byte row segments while the tiles fit
     const int fixed = 640 / seg;  // stages' worth of time a block spends filling its ring and storing its tile
     const size_t cap = partial_floats(m.c);
@@ -1848,11 +1856,11 @@ static StreamShape stream_shape(const Model &m, int M, int N, int K, int terms =
     auto search = [&](int cost_rows, int mt, int cap_rows, int only_steps) {
         StreamShape best = {bk, 8, 1, K, 2, 2};
         double best_cost = -1;
-        for (int nt = 8; nt >= 4; --nt) {
+        for (int nt = 8; nt >= (spec ? 2 : 4); --nt) {
             const int tiles = (N + 32 * nt - 1) / (32 * nt);
             for (int s = 1; s <= 32; ++s) {
                 const int steps = (nk + s - 1) / s;
-                if (s > 1 && (steps * bk < 256 || (size_t)s * cap_rows * N > cap)) break;
+                if (s > 1 && (steps * bk < (spec ? 128 : 256) || (size_t)s * cap_rows * N > cap)) break;
                 if (only_steps > 0 && steps != only_steps) continue;
                 const int used = (nk + steps - 1) / steps;  // slices that are not empty
                 const int rounds = (tiles * used + 255) / 256;
