@@ -1847,7 +1847,7 @@ static void stream_launch(const Model &m, const StreamShape &sh, const bf16_t *A
 // so its logits do not depend on which or how many other rows share the step.
 static StreamShape stream_shape(const Model &m, int M, int N, int K, int terms = 2) {
     const int MT = (M + 31) / 32;
-    const bool spec = MT <= kSpecTiles;
+    const bool spec = MT <= kSpecTiles && terms == 2;  // (with one term the smaller blocks measured 1-2 % slower)
     const int bk = MT * terms <= 8 ? 64 : 32, seg = bk * 2, nk = K / bk;  // 128-byte row segments while the tiles fit
     const int fixed = 640 / seg;  // stages' worth of time a block spends filling its ring and storing its tile
     const size_t cap = partial_floats(m.c);
