@@ -55,7 +55,7 @@ enum {
     ST_PREFILL_FAST = 16u    /* st_prefill: in passes of more than 128 rows round every GEMM and attention input to
                               one bf16.  By default every pass carries those inputs as two bf16 terms (16 mantissa
                               bits), which leaves the bf16 K/V cache as its only rounding: its logits are then as
-                              close to an fp32 evaluation as the decode step's.  Up to about 240 rows the second
+                              close to an fp32 evaluation as the decode step's.  Up to about 100 rows the second
                               term costs no time (the weight stream sets it); longer passes are bound by the MFMA
                               rate and pay twice the MFMA work.  With this flag passes of 129 rows and more take
                               single bf16 inputs: 1.3x (129 rows) to 1.8x (1024 rows and more) faster, at about
@@ -120,7 +120,7 @@ void st_model_destroy(st_model *m);
  * every layer as fp16 into `buf` (device memory owned by the caller, 256-byte aligned, st_query_f16_bytes bytes -- as
  * many as those bf16 matrices take -- borrowed until st_model_destroy or a detaching call); weights smaller than 2^-16
  * round to a multiple of 2^-24.  From then on default-precision passes of every length run those three GEMMs per
- * layer on the fp16 MFMA, with single fp16 activations instead of two bf16 terms (from 193 rows on in the MFMA-bound
+ * layer on the fp16 MFMA, with single fp16 activations instead of two bf16 terms (from 161 rows on in the MFMA-bound
  * kernels): the same MFMA rate as one bf16 term, 11 mantissa bits instead of 8.  The QKV projection keeps its input
  * in two bf16 terms and the attention its queries: what reaches the attention logits is the one place where 11 bits
  * showed (through all 64 layers of the 32B shape).  Measured against the CPU oracle, and against the decode step
