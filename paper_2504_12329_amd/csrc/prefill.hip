@@ -1588,19 +1588,19 @@ __global__ __launch_bounds__(FORM == kFlashSingle ? 256 : 512, 2) void k_flash_l
         open_reads(ic<1>{}, ic<0>{}, -1);
         multiply(ic<1>{}, ic<0>{});
         __builtin_amdgcn_s_barrier();
-        // (a tile beyond the wave's last key has zero weights; its scores are computed and not used)
-        auto weights = [&](int i) {
-            if (active(i)) {
-                softmax(i);
-            } else {
-#pragma unroll
-                for (int s2 = 0; s2 < 4; ++s2) pf[s2] = as_bf16x8(u32x4{0, 0, 0, 0});
-            }
-        };
-        for (int i = 0; i + 1 < n_it; ++i) {
+        // A wave multiplies its own n_act tiles (the scores of one more are computed and not used) and from then on only
+        // loads its part of the others': a tile multiplied with zero weights would spread an Inf or NaN in V to rows that
+        // do not see it.
+        const int t_last = wave_active ? min(t_end - 1, wave_last_key / kFlashKeys) : -1;
+        const int n_act = __builtin_amdgcn_readfirstlane(max(0, KSPLIT ? ((t_last - t_begin - half) >> 1) + 1 : t_last - t_begin + 1));
+        auto request = [&](int i) {
             if (i + 1 + kLead < n_it) load_tile(kbase, i + 1 + kLead, slot_k(i + 1 + kLead));
             if (i + kLead < n_it) load_tile(vbase, i + kLead, slot_v(i + kLead));
-            weights(i);
+        };
+        int i = 0;
+        for (; i < min(n_act, n_it - 1); ++i) {
+            request(i);
+            softmax(i);
             open_reads(ic<1>{}, ic<1>{}, i);
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_s_setprio(1);
@@ -1609,10 +1609,18 @@ __global__ __launch_bounds__(FORM == kFlashSingle ? 256 : 512, 2) void k_flash_l
             wait_loads<0>();
             __builtin_amdgcn_s_barrier();
         }
-        weights(n_it - 1);
-        open_reads(ic<0>{}, ic<1>{}, n_it - 1);
+        for (; i < n_it - 1; ++i) {
+            request(i);
+            __builtin_amdgcn_s_barrier();
+            wait_loads<0>();
+            __builtin_amdgcn_s_barrier();
+        }
+        if (n_act == n_it) {
+            softmax(n_it - 1);
+            open_reads(ic<0>{}, ic<1>{}, n_it - 1);
+        }
         __builtin_amdgcn_s_barrier();
-        multiply(ic<0>{}, ic<1>{});
+        if (n_act == n_it) multiply(ic<0>{}, ic<1>{});
         __builtin_amdgcn_s_barrier();
         if (!half) __builtin_amdgcn_s_barrier();
     }
@@ -1638,9 +1646,14 @@ __global__ __launch_bounds__(FORM == kFlashSingle ? 256 : 512, 2) void k_flash_l
             for (int r = 0; r < 16; ++r) o[tt][r] = o[tt][r] * e1 + xo[(tt * 16 + r) * 64] * e2;
     }
     if (!wave_active || rw0 + l32 >= rows) return;
+    // the row's token and head once more, from a value the compiler cannot see through: kept from the top of the kernel
+    // they and the addresses made of them are four registers too many for the two-term loop
+    int row_out = rw0 + l32;
+    asm volatile("" : "+v"(row_out));
+    const int tok_out = row_out / G, head_out = g * G + row_out % G;
     if (n_split == 1) {
         const float inv = 1.0f / l_i;
-        bf16_t *orow = out + (size_t)(fw.row_base + qtok) * ldq + head * D;
+        bf16_t *orow = out + (size_t)(fw.row_base + tok_out) * ldq + head_out * D;
 #pragma unroll
         for (int tt = 0; tt < D / 32; ++tt)
 #pragma unroll
@@ -1653,11 +1666,11 @@ __global__ __launch_bounds__(FORM == kFlashSingle ? 256 : 512, 2) void k_flash_l
                 if (outlo) {  // second bf16 term of the activation (short chunks)
                     u32x2 lo = {pack_bf16x2(v0 - bf16_lo(pk.x), v1 - bf16_hi(pk.x)),
                                 pack_bf16x2(v2 - bf16_lo(pk.y), v3 - bf16_hi(pk.y))};
-                    *reinterpret_cast<u32x2 *>(outlo + (size_t)(fw.row_base + qtok) * ldq + head * D + dcol) = lo;
+                    *reinterpret_cast<u32x2 *>(outlo + (size_t)(fw.row_base + tok_out) * ldq + head_out * D + dcol) = lo;
                 }
             }
     } else {
-        const size_t pr = (size_t)z * m_total * nq + (size_t)(fw.row_base + qtok) * nq + head;
+        const size_t pr = (size_t)z * m_total * nq + (size_t)(fw.row_base + tok_out) * nq + head_out;
         float *po = part_o + pr * D;
 #pragma unroll
         for (int tt = 0; tt < D / 32; ++tt)

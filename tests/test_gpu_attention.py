@@ -43,3 +43,40 @@ def test_attention_of_every_row(G, nkv, kv0, m, mode):
     print_case("worst row", worst)
     assert worst <= TOL[mode]
     g.close()
+
+
+@pytest.mark.parametrize("G,nkv,kv0,m,bad,mode", [
+    (6, 2, 30, 512, 448, "default"), (6, 2, 30, 512, 448, "fast"), (7, 4, 2050, 126, 2112, "default"),
+    (5, 8, 100, 300, 192, "default"), (4, 1, 40, 40, 64, "default")])
+def test_a_non_finite_value_stays_out_of_earlier_key_tiles(G, nkv, kv0, m, bad, mode):
+    """The token at position `bad`, the first of a key tile, has a NaN embedding, so its K and V rows are NaN.  Rows whose
+    32-row wave ends before that tile begins skip it, also where other waves of their block do not, and must be what they
+    are without it, bit for bit."""
+    seq = kv0 + m
+    print_case(f"2 layers, {G} x {nkv} heads: pass of {m} rows on {kv0} keys ({mode}), NaN at {bad}")
+    cfg = synth.model_config("tiny_small", max_seq=seq, max_chunk=seq, n_layers=2)
+    cfg.update(hidden=256, n_q_heads=G * nkv, n_kv_heads=nkv, head_dim=128, intermediate=128, vocab=512)
+    w = synth.make_weights(cfg, 31, device="cuda")
+    w["embed"][511] = float("nan")
+    g = B.Model(cfg, w)
+    toks = synth.make_prompt(seq, 511, 32)
+    kv = g.kv.view(torch.bfloat16).view(2, 2, nkv, seq, 128)
+    rows = []
+    for poison in (False, True):
+        t = toks.copy()
+        if poison:
+            t[bad] = 511
+        g.truncate(0)
+        if kv0:
+            g.prefill(t[:kv0], want_logits=False)
+        g.prefill(t[kv0:], want_logits=False, fast=mode == "fast")
+        rows.append(kv[:, 1].float().clone())
+    # folded row r of the pass is token r / G; the last wave with a row of token q ends with row r | 31
+    last_token = lambda q: min(((q * G + G - 1) | 31) // G, m - 1)  # noqa: E731
+    clear = [q for q in range(m) if kv0 + last_token(q) < bad // 64 * 64]
+    print_case("rows clear of the tile", len(clear), "of", m)
+    assert bool(torch.isnan(rows[1][:, :, bad:]).all())
+    if clear:
+        at = [kv0 + q for q in clear]
+        assert torch.equal(rows[0][:, :, at], rows[1][:, :, at])
+    g.close()
