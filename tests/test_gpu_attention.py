@@ -80,3 +80,37 @@ def test_a_non_finite_value_stays_out_of_earlier_key_tiles(G, nkv, kv0, m, bad, 
         at = [kv0 + q for q in clear]
         assert torch.equal(rows[0][:, :, at], rows[1][:, :, at])
     g.close()
+
+
+@pytest.mark.parametrize("G,nkv,kv0,m", [(6, 2, 0, 480), (7, 4, 0, 480), (5, 8, 0, 1000), (7, 4, 1900, 126), (6, 2, 1300, 21)])
+def test_attention_weights_are_rounded_below_their_maximum(G, nkv, kv0, m):
+    """The bf16 rounding of the attention weights is a pass's largest error.  Weights rounded at any scale are off by 2^-8 / sqrt 3
+    over their mantissa, 1.66e-3 on average, and so is their sum with V.  Taken relative to the running maximum the largest
+    weights lie just below 1, where the mantissa is largest, and the maximum itself is exact: with scores spread by 2.5 the
+    error is 0.5e-3 to 0.75e-3 however the tiles are dealt out (evaluated in 64 bits); relative to a maximum that
+    is raised late it is 1.2e-3 to 1.5e-3.  One layer, so that the last row's logits show it, against the decode step,
+    whose weights stay in fp32, over sixteen sequences; the rest of the two paths differs by 16-bit inputs (1e-5)."""
+    print_case(f"1 layer, {G} x {nkv} heads: last row of a pass of {m} on {kv0} keys against the decode step")
+    seq = kv0 + m
+    cfg = synth.model_config("tiny_small", max_seq=seq, max_chunk=seq, n_layers=1)
+    cfg.update(hidden=256, n_q_heads=G * nkv, n_kv_heads=nkv, head_dim=128, intermediate=128, vocab=2048)
+    w = synth.make_weights(cfg, 33, device="cuda")
+    lw = w["layers"][0]
+    lw["wqkv"][:(G * nkv + nkv) * 128] *= 5   # q and k of deviation 1.6: scores of deviation 2.5
+    lw["wo"] *= 8                             # attention, not the embedding, makes the row
+    lw["w_down"].zero_()
+    g = B.Model(cfg, w)
+    err = 0.0
+    for s in range(16):
+        toks = synth.make_prompt(seq, cfg["vocab"], 100 + s)
+        g.truncate(0)
+        if kv0:
+            g.prefill(toks[:kv0], want_logits=False)
+        a = torch.from_numpy(g.prefill(toks[kv0:])[0]).double()
+        g.truncate(seq - 1)
+        b = torch.from_numpy(g.decode_step(int(toks[-1]))[0]).double()
+        err += float((a - b).norm() / b.norm()) ** 2 / 16
+    err **= 0.5
+    print_case("worst of the weights: rms error", err)
+    assert err <= 1e-3
+    g.close()
