@@ -103,7 +103,7 @@ int st_query_sizes(const st_config *cfg, size_t *kv_bytes, size_t *workspace_byt
  * -- K slices, leftover column tiles, half-width tiles -- and verifies that every output tile and K step is
  * computed by exactly one block and that every partial-sum tile lies inside the workspace st_query_sizes reports.
  * Touches no device.  launches / blocks (may be NULL) receive the GEMM launches and working blocks of one layer
- * (reported as 0 for rows <= 192).  ST_EINVAL with the failing projection in
+ * (0 for rows <= 96, which take the streaming kernel).  ST_EINVAL with the failing projection in
  * st_last_error() if the plan is inconsistent, ST_ERANGE if rows is outside 1..cfg->max_chunk. */
 int st_prefill_plan_check(const st_config *cfg, int32_t rows, int32_t *launches, int32_t *blocks);
 

@@ -326,7 +326,6 @@ int st_prefill_plan_check(const st_config *cfg, int32_t rows, int32_t *launches,
     const int h = cfg->hidden, I = cfg->intermediate, qd = cfg->n_q_heads * cfg->head_dim;
     const int qkv = (cfg->n_q_heads + 2 * cfg->n_kv_heads) * cfg->head_dim;
     const long long cap = (long long)partial_floats(*cfg);
-    constexpr int kPlanCountRows = 193;  // shorter passes are walked, but report no launches
     const struct {
         const char *name;
         int dual, N, K;
@@ -338,17 +337,19 @@ int st_prefill_plan_check(const st_config *cfg, int32_t rows, int32_t *launches,
     for (const auto &e : g) {
         if (e.K % 64 || e.K < 128) continue;  // the general-shape kernel serves such a K
         // a projection whose input carries two bf16 terms runs on tiles of half the rows: the plans of both forms are walked
-        for (int terms = 1; terms <= 2; ++terms) {
-            int nl = 0, nb = 0, ni = 0;
-            const int rc = ring_plan_check(e.dual, terms == 2, rows, e.N, e.K, cap, 1, &nl, &nb, &ni);
-            if (rc)
-                return fail(ST_EINVAL, "block plan of the %s projection at %d rows (%d-term input) fails check %d",
-                            e.name, rows, terms, rc);
-            // the counts reported are the default pass's
-            if (terms != (e.def_two ? 2 : 1) || rows < kPlanCountRows) continue;
-            if (launches) *launches += nl;
-            if (blocks) *blocks += nb;
-        }
+        // (one-term passes below kRingMinRowsFast rows take the streaming kernel; their plans hold all the same), and
+        // with and without a sliced tail, which the ragged passes do not take.  The counts are the default pass's.
+        for (int terms = 1; terms <= 2; ++terms)
+            for (int tail = 0; tail <= !e.dual; ++tail) {
+                int nl = 0, nb = 0, ni = 0;
+                const int rc = ring_plan_check(e.dual, terms == 2, rows, e.N, e.K, cap, tail, &nl, &nb, &ni);
+                if (rc)
+                    return fail(ST_EINVAL, "block plan of the %s projection at %d rows (%d-term input, tail %d) fails check %d",
+                                e.name, rows, terms, tail, rc);
+                if (terms != (e.def_two ? 2 : 1) || tail != !e.dual) continue;
+                if (launches) *launches += nl;
+                if (blocks) *blocks += nb;
+            }
     }
     return ST_OK;
 }
