@@ -107,6 +107,13 @@ int st_query_sizes(const st_config *cfg, size_t *kv_bytes, size_t *workspace_byt
  * st_last_error() if the plan is inconsistent, ST_ERANGE if rows is outside 1..cfg->max_chunk. */
 int st_prefill_plan_check(const st_config *cfg, int32_t rows, int32_t *launches, int32_t *blocks);
 
+/* Host-only: which kernel forms a pass of `rows` rows at position `pos0` takes, so that a test can name the form it runs.
+ * two_term: inputs in two bf16 terms (the default pass) or in one (ST_PREFILL_FAST).  forms[0..3], the QKV, O, gate/up and
+ * down projection: 0 for the streaming or general kernel, otherwise 1 (full-width tiles) | 2 (half-width tiles) | 4 (left-over
+ * columns in K slices of their own) | K slices << 8.  forms[4], the attention at head_dim 128: 1 = four waves,
+ * 2 = eight waves in two halves.  forms[5]: its key ranges. */
+int st_prefill_plan_forms(const st_config *cfg, int32_t rows, int32_t pos0, int32_t two_term, int32_t *forms);
+
 /* Creates a model over caller-owned device buffers (both 256-byte aligned).  Initialises the
  * workspace (RoPE table, counters) on `stream`; the KV length starts at 0.  The weights,
  * `kv` and `workspace` are borrowed until st_model_destroy.  Two models must not share a

@@ -16,7 +16,7 @@ LIB_PATH = os.path.join(HERE, "libst.so")
 ST_OK, ST_EINVAL, ST_ENOMEM, ST_ERANGE, ST_EHIP = 0, -1, -2, -3, -4
 ST_TOKENS_DEVICE, ST_OUT_DEVICE, ST_TOKEN_CHAINED, ST_PREFILL_TWO_TERM, ST_PREFILL_FAST = 1, 2, 4, 8, 16
 
-EXPORTS = ("st_query_sizes", "st_prefill_plan_check", "st_model_create", "st_model_destroy", "st_kv_len", "st_kv_truncate", "st_prefill",
+EXPORTS = ("st_query_sizes", "st_prefill_plan_check", "st_prefill_plan_forms", "st_model_create", "st_model_destroy", "st_kv_len", "st_kv_truncate", "st_prefill",
            "st_query_f16_bytes", "st_model_attach_f16", "st_batch_attach_f16", "st_decode_step", "st_decode_graph_state", "st_decode_step_kind", "st_decode_persist_plan", "st_decode_step_timed", "st_decode_greedy", "st_trigger_scan", "st_trigger_scan_static", "st_handoff", "st_generate",
            "st_generate_policy", "st_batch_query_sizes", "st_batch_create", "st_batch_destroy", "st_batch_kv_len",
            "st_batch_truncate", "st_batch_prefill", "st_batch_prefill_many", "st_batch_decode_step", "st_generate_batch",
@@ -75,6 +75,7 @@ def lib():
         L.st_last_error.restype = C.c_char_p
         L.st_query_sizes.argtypes = [C.POINTER(st_config), C.POINTER(C.c_size_t), C.POINTER(C.c_size_t)]
         L.st_prefill_plan_check.argtypes = [C.POINTER(st_config), C.c_int32, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
+        L.st_prefill_plan_forms.argtypes = [C.POINTER(st_config), C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
         L.st_model_create.argtypes = [C.POINTER(st_config), C.POINTER(st_weights), C.c_void_p, C.c_size_t,
                                       C.c_void_p, C.c_size_t, C.c_void_p, C.POINTER(C.c_void_p)]
         L.st_model_destroy.argtypes = [C.c_void_p]
@@ -142,6 +143,15 @@ def st_prefill_plan_check(cfg, rows):
     nl, nb = C.c_int32(), C.c_int32()
     _check(lib().st_prefill_plan_check(C.byref(make_config(cfg)), int(rows), C.byref(nl), C.byref(nb)))
     return nl.value, nb.value
+
+
+def st_prefill_plan_forms(cfg, rows, pos0, two_term=True):
+    """Kernel forms of a pass of `rows` rows at position `pos0`: for QKV, O, gate/up and down (full, half, tail, K slices), or
+    None (streaming or general kernel); then the attention's waves per block (None at head_dim 64) and key ranges."""
+    f = (C.c_int32 * 6)()
+    _check(lib().st_prefill_plan_forms(C.byref(make_config(cfg)), int(rows), int(pos0), int(two_term), f))
+    gemms = [(bool(v & 1), bool(v & 2), bool(v & 4), v >> 8) if v else None for v in f[:4]]
+    return gemms, {0: None, 1: 4, 2: 8}[f[4]], f[5]
 
 
 def st_decode_persist_plan(cfg, n_cu):

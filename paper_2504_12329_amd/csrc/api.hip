@@ -354,6 +354,15 @@ int st_prefill_plan_check(const st_config *cfg, int32_t rows, int32_t *launches,
     return ST_OK;
 }
 
+int st_prefill_plan_forms(const st_config *cfg, int32_t rows, int32_t pos0, int32_t two_term, int32_t *forms) {
+    if (int rc = validate_config(cfg)) return rc;
+    if (!forms) return fail(ST_EINVAL, "forms is NULL");
+    if (rows <= 0 || rows > cfg->max_chunk) return fail(ST_ERANGE, "rows %d outside 1..max_chunk", rows);
+    if (pos0 < 0 || pos0 > cfg->max_seq - rows) return fail(ST_ERANGE, "position %d does not leave %d rows", pos0, rows);
+    prefill_plan_forms(*cfg, rows, pos0, two_term != 0, forms);
+    return ST_OK;
+}
+
 // Checks the weights and fills a model record over the given cache and workspace (sizes checked by the caller).
 static int build_model(const st_config *cfg, const st_weights *w, void *kv, void *workspace, void *stream, Model *m) {
     if (!w) return fail(ST_EINVAL, "weights is NULL");

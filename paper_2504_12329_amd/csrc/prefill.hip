@@ -1347,8 +1347,9 @@ __global__ __launch_bounds__(256) void k_flash_prefill(const bf16_t *__restrict_
 //     rescale of the 64 output registers in most tiles (0.0-0.7 % of a pass) and cost up to 1.8 times the error of the
 //     whole pass (catch-up of 250 rows at 32B 3.6e-3 against 2.0e-3), the more the fewer key ranges were taken apart;
 //   * tiles wholly below the diagonal skip the causal compare.
-// KSPLIT = false: a block is 256 folded rows, both halves read the same tiles.  KSPLIT = true (short chunks): 128 rows,
-// waves 0-3 take the even and waves 4-7 the odd key tiles, and the two halves are merged through LDS at the end.
+// A block is 128 folded rows; waves 0-3 take the even and waves 4-7 the odd key tiles of its range, and the two halves are
+// merged through LDS at the end.  PAIR = false, for ranges of one or two tiles: four waves and half the LDS, so that two
+// blocks share a CU, each wave doing scores, softmax and output of a tile in turn.
 // Block ids: kv head fastest, so that with 8 kv heads an XCD (id mod 8) keeps to one head's keys.
 // Interface and key-split partial results are those of k_flash_prefill.
 // ---------------------------------------------------------------------------------------
@@ -1356,9 +1357,8 @@ constexpr int kFlashTile = kFlashKeys * 128 * 2;  // bytes of one K or V tile
 constexpr int kFlashLds = 8 * kFlashTile;
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-enum FlashForm { kFlashSingle, kFlashSplit, kFlashShared };
-template <bool TWO, int FORM>  // TWO: queries arrive as two bf16 terms
-__global__ __launch_bounds__(FORM == kFlashSingle ? 256 : 512, 2) void k_flash_long(const bf16_t *__restrict__ qb, const bf16_t *__restrict__ qb_lo,
+template <bool TWO, bool PAIR>  // TWO: queries arrive as two bf16 terms
+__global__ __launch_bounds__(PAIR ? 512 : 256, 2) void k_flash_long(const bf16_t *__restrict__ qb, const bf16_t *__restrict__ qb_lo,
                                                        const bf16_t *__restrict__ kc, const bf16_t *__restrict__ vc,
                                                        bf16_t *__restrict__ out, bf16_t *__restrict__ outlo,
                                                        float *__restrict__ part_o, float *__restrict__ part_ml, int m,
@@ -1366,7 +1366,6 @@ __global__ __launch_bounds__(FORM == kFlashSingle ? 256 : 512, 2) void k_flash_l
                                                        const FlashSeg *__restrict__ segs, int n_seg, size_t seq_stride,
                                                        int m_total, int f16, int nbx, int n_split) {
     constexpr int D = 128;
-    constexpr bool KSPLIT = FORM == kFlashSplit, PAIR = FORM != kFlashSingle;
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = PAIR ? wave >> 2 : 0, w4 = wave & 3, l32 = lane & 31, kg = lane >> 5;
@@ -1375,9 +1374,9 @@ __global__ __launch_bounds__(FORM == kFlashSingle ? 256 : 512, 2) void k_flash_l
     m = fw.m, kv0 = fw.kv0;
     kc += fw.cache, vc += fw.cache;
     const int rows = m * G;
-    constexpr int kRows = FORM == kFlashShared ? 256 : 128;
+    constexpr int kRows = 128;
     // blocks with the most keys (the last rows) are dispatched first, so the causal tail is made of short blocks
-    const int r0 = (fw.nbx - 1 - fw.bx) * kRows, rw0 = r0 + wave % (kRows / 32) * 32;
+    const int r0 = (fw.nbx - 1 - fw.bx) * kRows, rw0 = r0 + w4 * 32;
     const int ldq = nq * D;
     const bool wave_active = rw0 < rows;
     const int row = min(rw0 + l32, rows - 1);
@@ -1390,39 +1389,34 @@ __global__ __launch_bounds__(FORM == kFlashSingle ? 256 : 512, 2) void k_flash_l
     const int tps = (n_tiles + n_split - 1) / n_split;
     const int t_begin = z * tps, t_end = min(n_tiles, t_begin + tps);
     // iteration i of a wave is tile t_begin + i, or t_begin + 2 i + half
-    const int n_it = __builtin_amdgcn_readfirstlane(max(0, KSPLIT ? (t_end - t_begin + 1) / 2 : t_end - t_begin));
-    auto tile_of = [&](int i) { return KSPLIT ? t_begin + 2 * i + half : t_begin + i; };
+    const int n_it = __builtin_amdgcn_readfirstlane(max(0, PAIR ? (t_end - t_begin + 1) / 2 : t_end - t_begin));
+    auto tile_of = [&](int i) { return PAIR ? t_begin + 2 * i + half : t_begin + i; };
     const float scale = 1.4426950408889634f / sqrtf((float)D);
 
     // tiles: a 1 KB load instruction fills four key rows of 256 bytes; lane -> (row lane/16, 16-byte position lane%16
     // holding chunk position ^ swz(row)).  The swizzle spreads both kinds of reads over all banks: the 16 rows of an S^T
     // read take 16 different positions, and so do the (row, chunk) pairs of a transposing V read.
     auto swz = [](int r) { return ((r & 3) << 2) | ((r >> 2) & 3); };
-    constexpr int kLoads = FORM == kFlashShared ? 2 : 4;  // instructions per wave for one tile
+    constexpr int kLoads = 4;  // instructions per wave for one tile
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
     const bf16_t *kbase = kc + (size_t)g * max_seq * D, *vbase = vc + (size_t)g * max_seq * D;
-    auto slot_k = [&](int i) { return FORM == kFlashShared ? (i & 3) * kFlashTile : (half * 4 + (i & 1)) * kFlashTile; };
-    auto slot_v = [&](int i) { return FORM == kFlashShared ? (4 + (i & 3)) * kFlashTile : (half * 4 + 2 + (i & 1)) * kFlashTile; };
+    auto slot_k = [&](int i) { return (half * 4 + (i & 1)) * kFlashTile; };
+    auto slot_v = [&](int i) { return (half * 4 + 2 + (i & 1)) * kFlashTile; };
     auto load_tile = [&](const bf16_t *base, int i, int slot) {
         const int key0 = tile_of(i) * kFlashKeys;
 #pragma unroll
         for (int e = 0; e < kLoads; ++e) {
-            const int r4 = (wave % (16 / kLoads) * kLoads + e) * 4, r = r4 + (lane >> 4);
+            const int r4 = (w4 * kLoads + e) * 4, r = r4 + (lane >> 4);
             const int c = (lane & 15) ^ swz(r);
             const int kabs = min(key0 + r, n_keys - 1);  // clamped rows lie above the diagonal: masked
             load_to_lds16(base, (uint32_t)kabs * (D * 2) + c * 16, lds0 + slot + r4 * 256);
         }
     };
-    // K runs kLead + 1 and V kLead iterations ahead.  With shared tiles (two leads) each half loads a part of them, and
-    // waves 0-3 read theirs a slot before waves 4-7 could have waited for parts requested in the iteration before.
-    constexpr int kLead = FORM == kFlashShared ? 2 : 1;
-    if (!PAIR && n_it > 0) {
+    // PAIR: K runs two iterations ahead and V one (tiles past the last one: rows of the last key, never used)
+    if (n_it > 0) {
         load_tile(kbase, 0, slot_k(0));
+        if (PAIR) load_tile(kbase, 1, slot_k(1));
         load_tile(vbase, 0, slot_v(0));
-    }
-    if (PAIR && n_it > 0) {  // (tiles past the last one: rows of the last key, never used)
-        for (int i = 0; i <= kLead; ++i) load_tile(kbase, i, slot_k(i));
-        for (int i = 0; i < kLead; ++i) load_tile(vbase, i, slot_v(i));
     }
 
     bf16x8 qf[D / 16], ql[TWO ? D / 16 : 1];
@@ -1558,10 +1552,9 @@ __global__ __launch_bounds__(FORM == kFlashSingle ? 256 : 512, 2) void k_flash_l
     };
 
     // Slots: waves 0-3 run S(0) in slot 0, softmax(i) in slot 2i + 1, the MFMAs of iteration i in slot 2i + 2; waves 4-7
-    // one slot later.  A wave requests its part of K(i + 1 + kLead) and V(i + kLead) at the start of its softmax(i) and
-    // waits for it at the end of its next slot; the barrier that ends that slot lies before the first read of these
-    // tiles.  The tiles overwritten, K(i - 1) and V(i - 2) (KSPLIT: K(i) and V(i - 1)), were last read in a slot that has
-    // ended for both halves (KSPLIT: for this one).
+    // one slot later.  A wave requests its part of K(i + 2) and V(i + 1) at the start of its softmax(i) and waits for it at
+    // the end of its next slot; the barrier that ends that slot lies before the first read of these tiles.  The tiles
+    // overwritten, K(i) and V(i - 1), were last read in a slot that has ended for this half.
     if (!PAIR && n_it > 0) {
         wait_loads<0>();
         __builtin_amdgcn_s_barrier();
@@ -1594,10 +1587,10 @@ __global__ __launch_bounds__(FORM == kFlashSingle ? 256 : 512, 2) void k_flash_l
         // loads its part of the others': a tile multiplied with zero weights would spread an Inf or NaN in V to rows that
         // do not see it.
         const int t_last = wave_active ? min(t_end - 1, wave_last_key / kFlashKeys) : -1;
-        const int n_act = __builtin_amdgcn_readfirstlane(max(0, KSPLIT ? ((t_last - t_begin - half) >> 1) + 1 : t_last - t_begin + 1));
+        const int n_act = __builtin_amdgcn_readfirstlane(max(0, ((t_last - t_begin - half) >> 1) + 1));
         auto request = [&](int i) {
-            if (i + 1 + kLead < n_it) load_tile(kbase, i + 1 + kLead, slot_k(i + 1 + kLead));
-            if (i + kLead < n_it) load_tile(vbase, i + kLead, slot_v(i + kLead));
+            if (i + 2 < n_it) load_tile(kbase, i + 2, slot_k(i + 2));
+            if (i + 1 < n_it) load_tile(vbase, i + 1, slot_v(i + 1));
         };
         int i = 0;
         for (; i < min(n_act, n_it - 1); ++i) {
@@ -1626,7 +1619,7 @@ __global__ __launch_bounds__(FORM == kFlashSingle ? 256 : 512, 2) void k_flash_l
         __builtin_amdgcn_s_barrier();
         if (!half) __builtin_amdgcn_s_barrier();
     }
-    if constexpr (KSPLIT) {  // the odd tiles' half hands its (max, sum, output) over through LDS
+    if constexpr (PAIR) {  // the odd tiles' half hands its (max, sum, output) over through LDS
         float *xo = reinterpret_cast<float *>(smem) + w4 * 64 * 64 + lane;
         float *xm = reinterpret_cast<float *>(smem) + 4 * 64 * 64 + w4 * 128 + lane;
         if (half) {
@@ -1812,9 +1805,8 @@ hipError_t raise_lds_limits() {
 #define ST_RING_LIMIT(D, H)                                                                                 \
     take(raise_one(k_gemm_ring<D, H, 1, false>)), take(raise_one(k_gemm_ring<D, H, 1, true>)), \
         take(raise_one(k_gemm_ring<D, H, 2, false>));
-    take(raise_one(k_flash_long<false, kFlashSingle>)), take(raise_one(k_flash_long<true, kFlashSingle>));
-    take(raise_one(k_flash_long<false, kFlashSplit>)), take(raise_one(k_flash_long<true, kFlashSplit>));
-    take(raise_one(k_flash_long<false, kFlashShared>));
+    take(raise_one(k_flash_long<false, false>)), take(raise_one(k_flash_long<true, false>));
+    take(raise_one(k_flash_long<false, true>)), take(raise_one(k_flash_long<true, true>));
     ST_RING_LIMIT(false, false) ST_RING_LIMIT(false, true) ST_RING_LIMIT(true, false) ST_RING_LIMIT(true, true)
 #undef ST_RING_LIMIT
     take(raise_one(k_gemm_stream<1, 64, true, 1, true>)), take(raise_one(k_gemm_stream<2, 64, true, 1, true>));
@@ -2246,6 +2238,44 @@ int flash_row_blocks(const st_config &c, int len) {
     return (len * G + 127) / 128;  // both attention kernels take 128 folded rows per block
 }
 
+// Block form and key splits of the attention of `rows` query rows in `rblocks` blocks of 128 folded rows, the longest on
+// n_tiles key tiles.  Pure host arithmetic.
+struct FlashPlan {
+    bool pair;
+    int splits;
+};
+static FlashPlan flash_plan(const st_config &c, bool two_term, int rows, int rblocks, int n_tiles) {
+    const int d = c.head_dim, nq = c.n_q_heads, nkv = c.n_kv_heads;
+    const size_t cap = partial_floats(c);
+    FlashPlan p = {false, 1};
+    if (d == 128) {
+        // k_flash_long: of the block forms and the split counts, the one that minimises (rounds of resident blocks) x
+        // (iterations per block x the time of one + what a block spends before and after them) + the partial results
+        // written, and the merge pass that reads them.  From four rounds on the unequal (causal) blocks balance out,
+        // longest first.  Microseconds, fitted to rocprofv3 times at 2 to 4096 rows of the three model shapes.
+        const double two = two_term ? 1.0 : 0.8, rows_bytes = (double)rows * nq * d * 4;
+        const int sp_max = rblocks * nkv >= 1024 ? 1 : (n_tiles < 32 ? n_tiles : 32);
+        double best = -1;
+        for (int pair = 0; pair < 2; ++pair)
+            for (int sp = 1; sp <= sp_max; ++sp) {
+                if (sp > 1 && (size_t)sp * rows * nq * (d + 2) > cap) break;
+                const int tps = (n_tiles + sp - 1) / sp, used = (n_tiles + tps - 1) / tps;
+                if (used != sp) continue;  // the same blocks as a smaller count
+                const int blocks = rblocks * nkv * sp, slots = pair ? 256 : 512, its = pair ? (tps + 1) / 2 : tps;
+                const double rounds = blocks <= 4 * slots ? (double)((blocks + slots - 1) / slots) : (double)blocks / slots;
+                const double merge = sp > 1 ? sp * rows_bytes / 4e6 + 3.0 + (sp + 1) * rows_bytes / 4e6 : 0.0;
+                const double cost = rounds * (its * 2.6 * two + (pair ? 10.0 : 6.5)) + merge;
+                if (best < 0 || cost < best) best = cost, p.splits = sp, p.pair = pair;
+            }
+    } else {  // k_flash_prefill: enough blocks for every CU, bounded by the tiles and by the partial buffer
+        p.splits = (512 + rblocks * nkv - 1) / (rblocks * nkv);
+        if (p.splits > n_tiles) p.splits = n_tiles;
+        if (p.splits > 32) p.splits = 32;
+    }
+    while (p.splits > 1 && (size_t)p.splits * rows * nq * (d + 2) > cap) --p.splits;
+    return p;
+}
+
 // Causal attention of n query rows at positions pos0 .. pos0+n-1 over one sequence's cache (kc / vc of one layer) --
 // or, with `ragged`, of the R rows of several sequences in one launch (kc / vc are then sequence 0's caches).
 struct RaggedPass {
@@ -2259,60 +2289,27 @@ static void launch_flash(const Model &m, const bf16_t *qb, const bf16_t *qb_lo, 
     const st_config &c = m.c;
     const int d = c.head_dim, nq = c.n_q_heads, nkv = c.n_kv_heads;
     const Workspace &w = m.ws;
-    const bool long_chunk = d == 128;  // head_dim 128: k_flash_long at every chunk length
     const int G = nq / nkv;
     const int rblocks = ragged ? ragged->total_blocks : flash_row_blocks(c, n);
     const int n_tiles = ragged ? ragged->max_tiles : (pos0 + n + kFlashKeys - 1) / kFlashKeys;
     const int n_rows_all = ragged ? ragged->R : n;  // rows the partial buffers are sized for
-    // key splits: enough blocks for every CU, bounded by the tiles and by the partial buffer
-    int splits = (512 + rblocks * nkv - 1) / (rblocks * nkv);
-    if (splits > n_tiles) splits = n_tiles;
-    if (splits > 32) splits = 32;
-    const size_t cap = partial_floats(c);
-    int form = kFlashSingle, nbx = rblocks;
-    if (long_chunk) {
-        // k_flash_long: of the block forms and the split counts, the one that minimises (rounds of resident blocks) x
-        // (iterations per block x the time of one + what a block spends before and after them) + the partial results
-        // written, and the merge pass that reads them.  From four rounds on the unequal (causal) blocks balance out,
-        // longest first.  Microseconds, fitted to rocprofv3 times at 2 to 4096 rows of the three model shapes.
-        const double two = qb_lo ? 1.0 : 0.8;
-        double best = -1;
-        for (int f = kFlashSingle; f <= kFlashShared; ++f) {
-            if (f == kFlashShared && (ragged || qb_lo)) continue;  // (two-term queries leave it no registers)
-            const int nb = f == kFlashShared ? (rblocks + 1) / 2 : rblocks;
-            const int sp_max = nb * nkv >= 1024 ? 1 : (n_tiles < 32 ? n_tiles : 32);
-            for (int sp = 1; sp <= sp_max; ++sp) {
-                if (sp > 1 && (size_t)sp * n_rows_all * nq * (d + 2) > cap) break;
-                const int tps = (n_tiles + sp - 1) / sp, used = (n_tiles + tps - 1) / tps;
-                if (used != sp) continue;  // the same blocks as a smaller count
-                const int blocks = nb * nkv * sp, slots = f == kFlashSingle ? 512 : 256;
-                const int its = f == kFlashSplit ? (tps + 1) / 2 : tps;
-                const double rounds = blocks <= 4 * slots ? (double)((blocks + slots - 1) / slots) : (double)blocks / slots;
-                const double rows_bytes = (double)n_rows_all * nq * d * 4;
-                const double merge = sp > 1 ? sp * rows_bytes / 4e6 + 3.0 + (sp + 1) * rows_bytes / 4e6 : 0.0;
-                const double cost = rounds * (its * 2.6 * two + (f == kFlashSingle ? 6.5 : 10.0)) + merge;
-                if (best < 0 || cost < best) best = cost, splits = sp, form = f, nbx = nb;
-            }
-        }
-    }
-    while (splits > 1 && (size_t)splits * n_rows_all * nq * (d + 2) > cap) --splits;
+    const FlashPlan plan = flash_plan(c, qb_lo != nullptr, n_rows_all, rblocks, n_tiles);
+    const int splits = plan.splits;
     float *part_o = w.qkv, *part_ml = w.qkv + (size_t)splits * n_rows_all * nq * d;
     const FlashSeg *segs = ragged ? ragged->segs_dev : nullptr;
     const int n_seg = ragged ? ragged->n_seg : 0;
     const size_t seq_stride = ragged ? ragged->seq_stride : 0;
-#define ST_FLASH(TWOV, FORMV)                                                                                              \
-    hipLaunchKernelGGL((k_flash_long<TWOV, FORMV>), dim3(nbx * nkv * splits), dim3(FORMV == kFlashSingle ? 256 : 512),     \
-                       FORMV == kFlashSingle ? kFlashLds / 2 : kFlashLds, m.stream, qb, qb_lo, kc, vc, attn, attn_lo,      \
-                       part_o, part_ml, n, pos0, nq, nkv, c.max_seq, segs, n_seg, seq_stride, n_rows_all, (int)f16_out, nbx, \
-                       splits)
-    if (!long_chunk)
+#define ST_FLASH(TWOV, PAIRV)                                                                                               \
+    hipLaunchKernelGGL((k_flash_long<TWOV, PAIRV>), dim3(rblocks * nkv * splits), dim3(PAIRV ? 512 : 256),                  \
+                       PAIRV ? kFlashLds : kFlashLds / 2, m.stream, qb, qb_lo, kc, vc, attn, attn_lo, part_o, part_ml, n,   \
+                       pos0, nq, nkv, c.max_seq, segs, n_seg, seq_stride, n_rows_all, (int)f16_out, rblocks, splits)
+    if (d != 128)
         hipLaunchKernelGGL(k_flash_prefill<64>, dim3(rblocks, nkv, splits), dim3(256), 0, m.stream, qb, kc, vc, attn, attn_lo,
                            part_o, part_ml, n, pos0, nq, G, c.max_seq, segs, n_seg, seq_stride, n_rows_all, (int)f16_out);
-    else if (qb_lo && form == kFlashSingle) ST_FLASH(true, kFlashSingle);
-    else if (qb_lo) ST_FLASH(true, kFlashSplit);
-    else if (form == kFlashSingle) ST_FLASH(false, kFlashSingle);
-    else if (form == kFlashSplit) ST_FLASH(false, kFlashSplit);
-    else ST_FLASH(false, kFlashShared);
+    else if (qb_lo && plan.pair) ST_FLASH(true, true);
+    else if (qb_lo) ST_FLASH(true, false);
+    else if (plan.pair) ST_FLASH(false, true);
+    else ST_FLASH(false, false);
 #undef ST_FLASH
     if (splits > 1) {
         const int n_rows = n_rows_all * nq;
@@ -2326,6 +2323,25 @@ static void launch_flash(const Model &m, const bf16_t *qb, const bf16_t *qb_lo, 
         else ST_COMBINE(64, 1);
 #undef ST_COMBINE
     }
+}
+
+void prefill_plan_forms(const st_config &c, int rows, int pos0, bool two_term, int32_t *forms) {
+    const int h = c.hidden, I = c.intermediate, qd = c.n_q_heads * c.head_dim, G = c.n_q_heads / c.n_kv_heads;
+    const struct {
+        bool dual;
+        int N, K;
+    } g[4] = {{false, (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim, h}, {false, h, qd}, {true, I, h}, {false, h, I}};
+    for (int i = 0; i < 4; ++i) {
+        forms[i] = 0;
+        if (rows < ring_min_rows(two_term) || g[i].K % kRingBK || g[i].K < 2 * kRingBK) continue;
+        const RingPlan p = ring_plan(g[i].dual, two_term, rows, g[i].N, g[i].K, partial_floats(c), !g[i].dual);
+        for (int l = 0; l < p.n; ++l) forms[i] |= p.half[l] ? 2 : 1;
+        forms[i] |= (p.tail.n > 0 ? 4 : 0) | p.slices << 8;
+    }
+    const FlashPlan f = flash_plan(c, two_term && c.head_dim == 128, rows, (rows * G + 127) / 128,
+                                   (pos0 + rows + kFlashKeys - 1) / kFlashKeys);
+    forms[4] = c.head_dim != 128 ? 0 : f.pair ? 2 : 1;
+    forms[5] = f.splits;
 }
 
 void launch_prefill_layers(const Model &m, int32_t pos0, int32_t n) {

@@ -198,6 +198,7 @@ void launch_decode_persist(const Model &m, const st_trigger_rule *rule, int32_t 
 // every partial-sum tile inside cap_floats; negative = which check failed).
 int ring_plan_check(int dual, int two_term, int M, int N, int K, long long cap_floats, int allow_tail, int *launches_out,
                     int *blocks_out, int *ids_out);
+void prefill_plan_forms(const st_config &c, int rows, int pos0, bool two_term, int32_t *forms);  // st_prefill_plan_forms
 size_t partial_floats(const st_config &c);  // floats of Workspace::qkv (the split-K / split-key partial results)
 hipError_t raise_lds_limits();              // once per process, before the first ring / streaming GEMM launch
 // fp16 operand mode: element-wise copy of n bf16 numbers as fp16 (counts the ones no half can hold in *bad), and

@@ -157,6 +157,25 @@ def test_long_chunk_launch_plan_on_random_shapes(L):
             B.st_prefill_plan_check(cfg, rows)   # raises StError naming the projection if a plan is inconsistent
 
 
+def test_every_attention_form_is_reached(L):
+    """Passes of the three paper shapes take both block forms of the attention, each with one and with several key ranges, in one
+    and in two query terms; head_dim 64 has no such forms; arguments out of range are refused."""
+    seen = set()
+    for name in ("qwen1p5b", "qwen7b", "qwen32b"):
+        cfg = synth.model_config(name, max_seq=8448, max_chunk=4096)
+        for rows in (1, 21, 86, 126, 250, 300, 512, 1000, 4096):
+            for pos0 in (0, 60, 1000, 4096):
+                for two in (False, True):
+                    gemms, waves, ranges = B.st_prefill_plan_forms(cfg, rows, pos0, two)
+                    seen.add((two, waves, ranges > 1))
+                    assert all((g is not None) == (rows >= (97 if two else 161)) for g in gemms)
+    assert seen == {(t, w, r) for t in (False, True) for w in (4, 8) for r in (False, True)}
+    assert B.st_prefill_plan_forms(synth.model_config("tiny_small", 128), 5, 0)[1] is None
+    for rows, pos0 in ((0, 0), (4097, 0), (1, -1), (1, 8448), (4096, 4353)):
+        with pytest.raises(B.StError):
+            B.st_prefill_plan_forms(cfg, rows, pos0)
+
+
 def test_bench_refuses_more_than_one_gpu():
     """The path is a single-GPU one: the benchmark says so instead of starting ranks."""
     import subprocess

@@ -1,6 +1,6 @@
-"""The catch-up attention (head_dim 128) at the edges of its block forms on the GPU: one tile, odd and even tile counts, several
-key splits, rows that fill a wave or leave most of a block idle, one- and two-term queries, one and eight query heads per
-kv head.
+"""The catch-up attention (head_dim 128) in both its block forms on the GPU, with one and several key ranges: one tile, odd and
+even tile counts of a range, rows that fill a wave or leave most of a block idle, one- and two-term queries, one and eight query
+heads per kv head, ragged passes.
 
 The last row's logits of a one-layer model with a zero MLP depend on the last query row only, so every row is checked
 instead through the K/V rows of the layer above it: a pass of m rows on kv0 cached keys against the same tokens fed one
@@ -19,15 +19,24 @@ pytestmark = pytest.mark.gpu
 TOL = {"default": 1e-2, "fast": 3e-2}
 
 
-@pytest.mark.parametrize("G,nkv,kv0,m,mode", [
-    (1, 1, 0, 1, "default"), (1, 1, 0, 64, "default"), (1, 2, 63, 2, "default"), (8, 1, 64, 17, "default"),
-    (4, 2, 127, 65, "default"), (5, 8, 700, 40, "default"), (7, 4, 1990, 33, "default"), (6, 2, 0, 200, "default"),
-    (5, 8, 10, 300, "default"), (6, 2, 0, 200, "fast"), (5, 8, 500, 260, "fast"), (8, 8, 0, 520, "fast")])
-def test_attention_of_every_row(G, nkv, kv0, m, mode):
+# form: waves per block and key ranges; the comment says how many tiles the longest row has, and the last of its ranges
+@pytest.mark.parametrize("G,nkv,kv0,m,mode,form", [
+    (1, 1, 0, 1, "default", (4, 1)), (1, 1, 0, 64, "default", (4, 1)), (1, 2, 63, 2, "default", (4, 1)),
+    (8, 1, 64, 17, "default", (4, 1)), (4, 2, 127, 65, "default", (4, 3)), (5, 8, 700, 40, "default", (4, 12)),
+    (7, 4, 1990, 33, "default", (4, 16)), (6, 2, 0, 200, "default", (4, 4)), (5, 8, 10, 300, "default", (8, 1)),
+    (6, 2, 0, 200, "fast", (8, 1)), (5, 8, 500, 260, "fast", (8, 1)), (8, 8, 0, 520, "fast", (4, 1)),
+    (7, 4, 2050, 126, "default", (8, 6)),   # 34: six tiles, last four
+    (5, 8, 3001, 250, "default", (8, 3)),   # 51: seventeen (nine and eight to a half)
+    (5, 8, 4096, 86, "default", (8, 7)),    # 66: ten, last six
+    (7, 4, 2050, 64, "default", (8, 9)),    # 34: four, last two
+    (5, 8, 1900, 150, "fast", (8, 5)),      # 33: seven, last five
+    (7, 4, 1200, 200, "fast", (8, 4))])     # 22: six, last four
+def test_attention_of_every_row(G, nkv, kv0, m, mode, form):
     print_case(f"2 layers, {G} x {nkv} heads: pass of {m} rows on {kv0} keys ({mode}) against decode steps")
     seq = kv0 + m
     cfg = synth.model_config("tiny_small", max_seq=seq, max_chunk=seq, n_layers=2)
     cfg.update(hidden=256, n_q_heads=G * nkv, n_kv_heads=nkv, head_dim=128, intermediate=128, vocab=512)
+    assert B.st_prefill_plan_forms(cfg, m, kv0, mode != "fast")[1:] == form
     g = B.Model(cfg, synth.make_weights(cfg, 31, device="cuda"))
     toks = synth.make_prompt(seq, cfg["vocab"], 32)
     kv = g.kv.view(torch.bfloat16).view(2, 2, nkv, seq, 128)
@@ -113,4 +122,33 @@ def test_attention_weights_are_rounded_below_their_maximum(G, nkv, kv0, m):
     err **= 0.5
     print_case("worst of the weights: rms error", err)
     assert err <= 1e-3
+    g.close()
+
+
+def test_ragged_segments_shorter_than_the_key_ranges():
+    """One pass over segments of very different contexts: the ranges are those of the longest (33 tiles, about nine), so the
+    short segments have ranges without a tile and ranges with one.  Against the decode steps of each sequence."""
+    G, nkv, ctx, new = 7, 4, [2050, 3, 130, 640], [33, 5, 21, 17]
+    print_case(f"2 layers, {G} x {nkv} heads: ragged pass of {new} rows on {ctx} keys against decode steps")
+    cfg = synth.model_config("tiny_small", max_seq=2112, max_chunk=2112, n_layers=2)
+    cfg.update(hidden=256, n_q_heads=G * nkv, n_kv_heads=nkv, head_dim=128, intermediate=128, vocab=512)
+    assert B.st_prefill_plan_forms(cfg, sum(new), 2083 - sum(new))[1:] == (8, 9)  # the same rows as one segment
+    w = synth.make_weights(cfg, 31, device="cuda")
+    b, g = B.Batch(cfg, w, len(ctx)), B.Model(cfg, w)
+    seqs = [synth.make_prompt(c + k, cfg["vocab"], 40 + i) for i, (c, k) in enumerate(zip(ctx, new))]
+    bkv = b.kv.view(torch.bfloat16).view(len(ctx), 2, 2, nkv, cfg["max_seq"], 128)
+    kv = g.kv.view(torch.bfloat16).view(2, 2, nkv, cfg["max_seq"], 128)
+    for i, c in enumerate(ctx):
+        b.prefill(i, seqs[i][:c], want_logits=False)
+    b.prefill_many(list(range(len(ctx))), [s[c:] for s, c in zip(seqs, ctx)], want_logits=False)
+    for i, c in enumerate(ctx):
+        g.truncate(0)
+        g.prefill(seqs[i][:c], want_logits=False)
+        for t in seqs[i][c:]:
+            g.decode_step(int(t), want_logits=False)
+        ref, one = kv[:, 1, :, c:len(seqs[i])].float(), bkv[i, :, 1, :, c:len(seqs[i])].float()
+        worst = float(((one - ref).norm(dim=-1) / ref.norm(dim=-1)).max())
+        print_case("segment", i, "worst row", worst)
+        assert worst <= TOL["default"]
+    b.close()
     g.close()
