@@ -183,7 +183,7 @@ struct GemmGrid {
 // BM x BNR block tile (BNR = rows of the weight tile), WGM x WGN waves, wave tile (BM/WGM) x (BNR/WGN).
 // The general-shape kernel (any K that is a multiple of 8): 128 x 128 with 2 x 2 waves, or 32- / 64-row tiles with
 // two waves for the shortest chunks.  Where K is a multiple of 64 -- every model shape of the paper -- chunks of
-// up to 256 rows go to k_gemm_stream and longer ones to k_gemm_ring below.
+// up to 96 rows (one activation term: 160) go to k_gemm_stream and longer ones to k_gemm_ring below.
 template <int BM, int BNR, int WGM, int WGN, bool DUAL, bool SPLITA>
 __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(const bf16_t *__restrict__ A, const bf16_t *__restrict__ Alo,
                                                          int lda, const bf16_t *__restrict__ B, int M, int N, int K,
@@ -467,7 +467,8 @@ __host__ __device__ inline bool ring_block(const RingGrid &gg, int bid, int M, i
 }
 
 // Rows of tile y: the rows of a launch are dealt to the My row tiles in units of kUnit (32 rows with two terms, 64 with
-// one), as evenly as they go: the first h_extra tiles have h_base + 1 units, the others h_base (at most four).
+// one), as evenly as they go: the first h_extra tiles have h_base + 1 units, the others h_base (two to four: the shortest pass has
+// four units, with one term three).
 __host__ __device__ inline int ring_units(const RingGrid &gg, int y) { return gg.h_base + (y < gg.h_extra ? 1 : 0); }
 __host__ __device__ inline int ring_row0(const RingGrid &gg, int y, int unit) {
     return unit * (y * gg.h_base + (y < gg.h_extra ? y : gg.h_extra));
@@ -766,7 +767,6 @@ __global__ __launch_bounds__(TERMS == 2 ? 512 : 256) void k_gemm_ring(const bf16
     ring_tile<NFV, DUAL, HALF, TERMS, F16>(ring, A, Alo, lda, B, M, N, K, pz, rb.ldp, outb, outlo, ldo, m0, n0, kbeg, nk, \
                                            out_f16)
     switch (__builtin_amdgcn_readfirstlane(ring_units(gg, rb.y))) {
-        case 1: ST_RING_TILE(2); break;
         case 2: ST_RING_TILE(4); break;
         case 3: ST_RING_TILE(6); break;
         default: ST_RING_TILE(8); break;
@@ -775,18 +775,17 @@ __global__ __launch_bounds__(TERMS == 2 ? 512 : 256) void k_gemm_ring(const bf16
 }
 
 // ---------------------------------------------------------------------------------------
-// Weight-streaming GEMM for chunks of at most 256 rows (two-term activations).  A block owns nt <= 8 tiles of 32
-// weight rows and a K slice; K advances BK columns per stage.  Every block re-reads the activation rows from L2,
+// Weight-streaming GEMM for chunks of at most 96 rows (one activation term: 160).  A block owns nt <= 8 tiles of 32
+// weight rows and a K slice; K advances 64 columns per stage.  Every block re-reads the activation rows from L2,
 // and direct loads of L2-resident data cost as much load-path time as the weights from HBM do (measured: adding
 // 24 KB of activations to 16 KB of weights per stage takes the weight stream from 6.0 to 4.2 TB/s), so the block
 // is made tall -- 256 weight rows per activation fetch -- and LDS is split into two rings: weights, nw stages,
 // filled by waves 0-1, and activations, na stages, filled by waves 2-3.  The two kinds of loads sit in different
 // waves because a wave's load counter retires in order: one wave cannot wait for a recent activation load
-// without also waiting for every older weight load.  BK = 64 (128-byte row segments, which HBM streams a fifth
-// faster than 64-byte ones) up to 128 rows; BK = 32 above, where the activation stages would not leave room for
-// three weight stages.  All four waves multiply: wave w owns weight tiles w and w + 4 against every 32-row
+// without also waiting for every older weight load.  A stage is 64 columns: HBM streams 128-byte row segments a fifth
+// faster than 64-byte ones.  All four waves multiply: wave w owns weight tiles w and w + 4 against every 32-row
 // activation tile (C^T = W A^T, a lane owns an activation row); raw fp32 partial sums of the K slice go to
-// part[z][M][N].  Needs K % BK == 0 and (nw - 2) * (loads per weight wave per stage) <= 63.
+// part[z][M][N].  Needs K % 64 == 0 and (nw - 2) * (loads per weight wave per stage) <= 63.
 // ---------------------------------------------------------------------------------------
 __device__ __forceinline__ void wait_loads_rt(int n) {  // s_waitcnt takes an immediate only
 #define ST_W1(v) case v: wait_loads<v>(); break;
@@ -799,27 +798,26 @@ __device__ __forceinline__ void wait_loads_rt(int n) {  // s_waitcnt takes an im
 #undef ST_W1
 }
 
-template <int BK>
 struct StreamGeom {
+    static constexpr int BK = 64;
     static constexpr int kSeg = BK * 2;          // bytes of a row per stage
     static constexpr int kLpr = kSeg / 16;       // lanes per row in a direct load
     static constexpr int kRpi = 64 / kLpr;       // rows per 1 KB instruction
     static constexpr int kWTile = 32 * kSeg;     // bytes of one 32-row weight tile per stage
     static constexpr int kARows = 32 * kSeg;     // bytes of 32 activation rows per stage (a tile holds one such block
                                                  // per term: high, low)
-    // 16-byte chunk swizzle of LDS row `row` (conflict-free fragment reads)
-    __device__ static int swz(int row) { return BK == 32 ? (row >> 2) & 3 : ring_swz(row); }
 };
 
 // TERMS = 2: activations as two bf16 terms (A + Alo).  TERMS = 1 with F16: single fp16 activations against the
 // model's fp16 copy of the weights on the f16 MFMA (half the activation traffic and half the MFMAs per weight byte).
-template <int MT, int BK, bool SPEC, int TERMS = 2, bool F16 = false>
+template <int MT, bool SPEC, int TERMS = 2, bool F16 = false>
 __global__ __launch_bounds__(SPEC ? 512 : 256) void k_gemm_stream(const bf16_t *__restrict__ A,
                                                                   const bf16_t *__restrict__ Alo, int lda,
                                                                   const bf16_t *__restrict__ B, int M, int N, int K,
                                                                   int kps, int nt, int nw, int na,
                                                                   float *__restrict__ part) {
-    using G = StreamGeom<BK>;
+    using G = StreamGeom;
+    constexpr int BK = G::BK;
     static_assert(TERMS == 1 || TERMS == 2, "one or two activation terms");
     constexpr int RT = 32 * TERMS;                   // LDS rows of one activation tile
     constexpr int kAStage = MT * TERMS * G::kARows;
@@ -854,7 +852,7 @@ __global__ __launch_bounds__(SPEC ? 512 : 256) void k_gemm_stream(const bf16_t *
     for (int i = 0; i < NL; ++i) {
         const int inst = (w_loader ? lw : lw - 2) * n_loads + i;
         const int row = inst * G::kRpi + lane / G::kLpr;
-        const int piece = ((lane % G::kLpr) ^ G::swz(row)) * 8;
+        const int piece = ((lane % G::kLpr) ^ ring_swz(row)) * 8;
         if (w_loader) {
             pl[i] = B + (size_t)min(n0 + row, N - 1) * K + kbeg + piece;
         } else {
@@ -883,7 +881,7 @@ __global__ __launch_bounds__(SPEC ? 512 : 256) void k_gemm_stream(const bf16_t *
             for (int r = 0; r < 16; ++r) acc[j][t][r] = 0.f;
     const bool second = wave + 4 < nt;  // this (multiplying) wave's second weight tile exists
     // swizzles of LDS rows 32*b + l32 for even / odd b (weight tile w and w + 4 have the parity of w)
-    const int sw_even = G::swz(l32), sw_odd = G::swz(32 + l32), sw_w = (wave & 1) ? sw_odd : sw_even;
+    const int sw_even = ring_swz(l32), sw_odd = ring_swz(32 + l32), sw_w = (wave & 1) ? sw_odd : sw_even;
 
     if (loads)
         for (int st = 0; st < depth - 1 && st < nk; ++st) {
@@ -1765,8 +1763,6 @@ size_t partial_floats(const st_config &c) {
 
 // Launches one GEMM; returns the number of K slices written to ws.qkv (0 for the fused SwiGLU form).
 // Alo != nullptr selects the two-term activation form.
-constexpr int kSplitRows = 256;  // most rows the weight-streaming kernel takes (eight 32-row activation tiles)
-
 template <int BM, int BNR, int WGM, int WGN, bool DUAL, bool SPLITA>
 static void gemm_launch(const Model &m, dim3 grid, const bf16_t *A, const bf16_t *Alo, int lda, const bf16_t *B, int M,
                         int N, int K, int kps, bf16_t *outb, bf16_t *outlo, int ldo, const GemmGrid &gg) {
@@ -1789,6 +1785,10 @@ static void ring_launch(const Model &m, bool f16, bool out_f16, dim3 grid, const
 #undef ST_RING_GO
 }
 
+// Most activation tiles of the streaming kernel's form with loading waves of their own (eight waves fit the register file
+// up to three: a few percent faster there, slower with four).
+constexpr int kSpecTiles = 3;
+
 // The ring and streaming kernels use more dynamic LDS than a kernel gets by default; the limit is raised once per
 // process for every instantiation (called under std::call_once when the first model is created, so the launchers,
 // which may run on several host threads, never touch it).
@@ -1809,35 +1809,25 @@ hipError_t raise_lds_limits() {
     take(raise_one(k_flash_long<false, true>)), take(raise_one(k_flash_long<true, true>));
     ST_RING_LIMIT(false, false) ST_RING_LIMIT(false, true) ST_RING_LIMIT(true, false) ST_RING_LIMIT(true, true)
 #undef ST_RING_LIMIT
-    take(raise_one(k_gemm_stream<1, 64, true, 1, true>)), take(raise_one(k_gemm_stream<2, 64, true, 1, true>));
-    take(raise_one(k_gemm_stream<3, 64, true, 1, true>)), take(raise_one(k_gemm_stream<4, 64, false, 1, true>));
-    take(raise_one(k_gemm_stream<5, 64, false, 1, true>)), take(raise_one(k_gemm_stream<6, 64, false, 1, true>));
-    take(raise_one(k_gemm_stream<7, 64, false, 1, true>)), take(raise_one(k_gemm_stream<8, 64, false, 1, true>));
-    take(raise_one(k_gemm_stream<1, 64, true, 1, false>)), take(raise_one(k_gemm_stream<2, 64, true, 1, false>));
-    take(raise_one(k_gemm_stream<3, 64, true, 1, false>)), take(raise_one(k_gemm_stream<4, 64, false, 1, false>));
-    take(raise_one(k_gemm_stream<5, 64, false, 1, false>)), take(raise_one(k_gemm_stream<6, 64, false, 1, false>));
-    take(raise_one(k_gemm_stream<7, 64, false, 1, false>)), take(raise_one(k_gemm_stream<8, 64, false, 1, false>));
-    take(raise_one(k_gemm_stream<1, 64, true>)), take(raise_one(k_gemm_stream<2, 64, true>));
-    take(raise_one(k_gemm_stream<3, 64, true>)), take(raise_one(k_gemm_stream<4, 64, false>));
-    take(raise_one(k_gemm_stream<5, 32, false>)), take(raise_one(k_gemm_stream<6, 32, false>));
-    take(raise_one(k_gemm_stream<7, 32, false>)), take(raise_one(k_gemm_stream<8, 32, false>));
+#define ST_STREAM_LIMIT(MT) \
+    take(raise_one(k_gemm_stream<MT, MT <= kSpecTiles, 1, false>)), take(raise_one(k_gemm_stream<MT, MT <= kSpecTiles, 1, true>));
+    ST_STREAM_LIMIT(1) ST_STREAM_LIMIT(2) ST_STREAM_LIMIT(3) ST_STREAM_LIMIT(4) ST_STREAM_LIMIT(5)
+    take(raise_one(k_gemm_stream<1, true>)), take(raise_one(k_gemm_stream<2, true>)), take(raise_one(k_gemm_stream<3, true>));
+#undef ST_STREAM_LIMIT
     return e;
 }
 
 // Shape of a streaming GEMM launch: K columns per stage, weight tiles per block (2..8), K slices, ring depths.
 struct StreamShape {
-    int bk, nt, splits, kps, nw, na;
+    int nt, splits, kps, nw, na;
 };
 
-constexpr int kSpecTiles = 3;  // most activation tiles of the streaming kernel's form with loading waves of their own
-
-template <int MT, int BK, int TERMS = 2, bool F16 = false>
+template <int MT, int TERMS = 2, bool F16 = false>
 static void stream_launch(const Model &m, const StreamShape &sh, const bf16_t *A, const bf16_t *Alo, int lda,
                           const bf16_t *B, int M, int N, int K) {
-    constexpr bool SPEC = MT <= kSpecTiles;  // eight waves fit the register file up to three activation tiles (measured: a
-                                    // few percent faster there, slower with four)
-    auto kern = k_gemm_stream<MT, BK, SPEC, TERMS, F16>;
-    using G = StreamGeom<BK>;
+    constexpr bool SPEC = MT <= kSpecTiles;
+    auto kern = k_gemm_stream<MT, SPEC, TERMS, F16>;
+    using G = StreamGeom;
     const int lds = sh.na * MT * TERMS * G::kARows + sh.nw * sh.nt * G::kWTile;
     dim3 grid((N + 32 * sh.nt - 1) / (32 * sh.nt), sh.splits);
     hipLaunchKernelGGL(kern, grid, dim3(SPEC ? 512 : 256), lds, m.stream, A, Alo, lda, B, M, N, K, sh.kps, sh.nt, sh.nw,
@@ -1847,21 +1837,22 @@ static void stream_launch(const Model &m, const StreamShape &sh, const bf16_t *A
 // One block per CU at a time, so the time is (rounds of 256 blocks) x (bytes a block loads, weights and activations
 // alike, + a fixed cost per block); the partial sums written and read again are charged per CU as well.
 // Up to three activation tiles (loading waves of their own): down to two weight tiles per block and two stages per slice,
-// because the small projections of the 1.5B shape are latency, not bytes (with at least four tiles and four stages its batched step of 3 / 16 / 40 rows took 339 / 393 / 452 us for four
-// layers, now 320 / 377 / 435; a pass of 21 rows 1957 -> 1921 us; the 7B and 32B shapes the same within 0.6 %).
+// because the small projections of the 1.5B shape are latency, not bytes (with at least four tiles and four stages its
+// batched step of 3 / 16 / 40 rows took 339 / 393 / 452 us for four layers, now 320 / 377 / 435; a pass of 21 rows 1957 -> 1921 us; the 7B and 32B shapes the same within 0.6 %).
 // Up to kInvariantRows rows (the most a batched decode step holds) the K slices are those of a 16-row launch whatever
 // M is, and only the tile count per block follows M: a row's sums are then formed in the same order in every batch,
 // so its logits do not depend on which or how many other rows share the step.
 static StreamShape stream_shape(const Model &m, int M, int N, int K, int terms = 2) {
     const int MT = (M + 31) / 32;
     const bool spec = MT <= kSpecTiles && terms == 2;  // (with one term the smaller blocks measured 1-2 % slower)
-    const int bk = MT * terms <= 8 ? 64 : 32, seg = bk * 2, nk = K / bk;  // 128-byte row segments while the tiles fit
+    constexpr int bk = StreamGeom::BK, seg = StreamGeom::kSeg;
+    const int nk = K / bk;
     const int fixed = 640 / seg;  // stages' worth of time a block spends filling its ring and storing its tile
     const size_t cap = partial_floats(m.c);
     // cheapest (tiles per block, K slices) for cost_rows rows in mt activation tiles; cap_rows rows must fit the
     // partial buffer; only_steps > 0 admits only slices of that many stages
     auto search = [&](int cost_rows, int mt, int cap_rows, int only_steps) {
-        StreamShape best = {bk, 8, 1, K, 2, 2};
+        StreamShape best = {8, 1, K, 2, 2};
         double best_cost = -1;
         for (int nt = 8; nt >= (spec ? 2 : 4); --nt) {
             const int tiles = (N + 32 * nt - 1) / (32 * nt);
@@ -2049,7 +2040,7 @@ int ring_plan_check(int dual, int two_term, int M, int N, int K, long long cap_f
             ++working;
             const int n0 = (rb.x + p.g[l].x0) * width;
             const int units = ring_units(p.g[l], rb.y), r0 = ring_row0(p.g[l], rb.y, unit);
-            if (rb.y < 0 || rb.y >= my || n0 < 0 || n0 >= N || units < 1 || units > 4 || r0 >= M) return -2;
+            if (rb.y < 0 || rb.y >= my || n0 < 0 || n0 >= N || units < 2 || units > 4 || r0 >= M) return -2;
             if (rb.y == my - 1 && r0 + units * unit < M) return -2;  // the last row tile ends at or past the last row
             if (rb.kbeg < 0 || rb.kend > K || (rb.kend - rb.kbeg) % kRingBK || rb.kend - rb.kbeg < 2 * kRingBK) return -3;
             for (int c = 0; c < per_tile; ++c) {
@@ -2080,12 +2071,13 @@ int ring_plan_check(int dual, int two_term, int M, int N, int K, long long cap_f
     return 0;
 }
 
-// Chunks below the model's ring threshold (two-term, at most kSplitRows rows) use the streaming kernel and an unfused
-// SwiGLU wherever K is a multiple of 64; otherwise the register-staged kernel, with many K slices and an unfused
+// Chunks below the ring threshold use the streaming kernel and an unfused SwiGLU wherever K is a multiple of 64; otherwise
+// (also longer chunks with K = 64 or an operand of 4 GB) the register-staged kernel, with many K slices and an unfused
 // SwiGLU up to kSmallRows rows.
 constexpr int kSmallRows = 64;
 
-// f16: the operands hold fp16 numbers (only the ring kernel has that form: the caller has made sure this GEMM takes it).
+// f16: the operands hold fp16 numbers (the streaming and ring kernels have that form: the caller has made sure this GEMM takes
+// one of them).
 template <bool DUAL>
 static int gemm(const Model &m, const bf16_t *A, const bf16_t *Alo, int lda, const bf16_t *B, int M, int N, int K,
                 bf16_t *outb, bf16_t *outlo, int ldo, PartTail *tail = nullptr, bool f16 = false, bool out_f16 = false) {
@@ -2094,35 +2086,31 @@ static int gemm(const Model &m, const bf16_t *A, const bf16_t *Alo, int lda, con
     const bool fits32 = (size_t)M * lda * sizeof(bf16_t) < ((size_t)1 << 32) &&
                         (size_t)(DUAL ? 2 : 1) * N * K * sizeof(bf16_t) < ((size_t)1 << 32);
     const bool big = M >= ring_min_rows(Alo != nullptr) && K % kRingBK == 0 && K >= 2 * kRingBK && fits32;
-    if (!big && !DUAL && !Alo && M <= kSplitRows && K % kRingBK == 0) {
-        // one activation term below the ring threshold: fp16 operands, or single bf16 (ST_PREFILL_FAST)
-        const StreamShape sh = stream_shape(m, M, N, K, 1);
-#define ST_STREAM1(MTV)                                                                   \
-    case MTV:                                                                             \
-        if (f16)                                                                          \
-            stream_launch<MTV, 64, 1, true>(m, sh, A, nullptr, lda, B, M, N, K);          \
-        else                                                                              \
-            stream_launch<MTV, 64, 1, false>(m, sh, A, nullptr, lda, B, M, N, K);         \
+    if (!DUAL && M < ring_min_rows(Alo != nullptr) && K % StreamGeom::BK == 0) {
+        const StreamShape sh = stream_shape(m, M, N, K, Alo ? 2 : 1);
+        const int tiles = (M + 31) / 32;
+        static_assert(kRingMinRows <= 3 * 32 + 1 && kRingMinRowsFast <= 5 * 32 + 1, "tiles the switches below know");
+        if (Alo) {
+            switch (tiles) {
+                case 1: stream_launch<1>(m, sh, A, Alo, lda, B, M, N, K); break;
+                case 2: stream_launch<2>(m, sh, A, Alo, lda, B, M, N, K); break;
+                default: stream_launch<3>(m, sh, A, Alo, lda, B, M, N, K); break;
+            }
+            return sh.splits;
+        }
+        // one activation term: fp16 operands, or single bf16 (ST_PREFILL_FAST)
+#define ST_STREAM1(MTV)                                                           \
+    case MTV:                                                                     \
+        if (f16)                                                                  \
+            stream_launch<MTV, 1, true>(m, sh, A, nullptr, lda, B, M, N, K);      \
+        else                                                                      \
+            stream_launch<MTV, 1, false>(m, sh, A, nullptr, lda, B, M, N, K);     \
         break;
-        switch ((M + 31) / 32) {
-            ST_STREAM1(1) ST_STREAM1(2) ST_STREAM1(3) ST_STREAM1(4) ST_STREAM1(5) ST_STREAM1(6) ST_STREAM1(7)
-            default: ST_STREAM1(8)
+        switch (tiles) {
+            ST_STREAM1(1) ST_STREAM1(2) ST_STREAM1(3) ST_STREAM1(4)
+            default: ST_STREAM1(5)
         }
 #undef ST_STREAM1
-        return sh.splits;
-    }
-    if (!big && !DUAL && Alo && M <= kSplitRows && K % kRingBK == 0) {
-        const StreamShape sh = stream_shape(m, M, N, K);
-        switch ((M + 31) / 32) {
-            case 1: stream_launch<1, 64>(m, sh, A, Alo, lda, B, M, N, K); break;
-            case 2: stream_launch<2, 64>(m, sh, A, Alo, lda, B, M, N, K); break;
-            case 3: stream_launch<3, 64>(m, sh, A, Alo, lda, B, M, N, K); break;
-            case 4: stream_launch<4, 64>(m, sh, A, Alo, lda, B, M, N, K); break;
-            case 5: stream_launch<5, 32>(m, sh, A, Alo, lda, B, M, N, K); break;
-            case 6: stream_launch<6, 32>(m, sh, A, Alo, lda, B, M, N, K); break;
-            case 7: stream_launch<7, 32>(m, sh, A, Alo, lda, B, M, N, K); break;
-            default: stream_launch<8, 32>(m, sh, A, Alo, lda, B, M, N, K); break;
-        }
         return sh.splits;
     }
     if (big) return ring_gemm<DUAL>(m, f16, out_f16, A, Alo, lda, B, M, N, K, outb, outlo, ldo, tail);

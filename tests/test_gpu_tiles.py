@@ -6,7 +6,7 @@ QKV 640 rows (two and a half column tiles), intermediate 448 (three and a half).
 import pytest
 import torch
 
-from paper_2504_12329_amd import synth
+from paper_2504_12329_amd import binding as B, synth
 from tests.gpu_common import LOGIT_TOL, make_pair, print_case, rel_err
 
 pytestmark = pytest.mark.gpu
@@ -41,4 +41,20 @@ def test_row_tiles_of_every_height(mode, m):
     print_case("worst row", worst, "logits against the oracle", err)
     assert worst <= ROW_TOL[mode]
     assert err <= (2 * LOGIT_TOL if mode == "fast" else LOGIT_TOL)
+    g.close()
+
+
+@pytest.mark.parametrize("m,fast", [(96, False), (97, False), (128, False), (200, False), (256, False), (257, False),
+                                    (129, True), (160, True), (161, True), (256, True)])
+def test_contractions_of_64(m, fast):
+    """Every contraction 64 long, too short for the ring kernel: the streaming kernel up to 96 rows (one term: 160), the
+    general one above, against the oracle."""
+    print_case(f"2 layers, hidden 64: pass of {m} rows" + (" (single-term inputs)" if fast else ""))
+    cfg, g, o = make_pair("tiny_small", 23, max_seq=300, max_chunk=300, n_layers=2, hidden=64, intermediate=64, n_q_heads=1,
+                          n_kv_heads=1, head_dim=64, vocab=512)
+    assert B.st_prefill_plan_forms(cfg, m, 0, not fast)[0] == [None] * 4
+    toks = synth.make_prompt(m, cfg["vocab"], 24)
+    err = rel_err(g.prefill(toks, fast=fast)[0], o.feed(toks))
+    print_case("logits against the oracle", err)
+    assert err <= (2 * LOGIT_TOL if fast else LOGIT_TOL)
     g.close()
