@@ -49,21 +49,21 @@ __global__ __launch_bounds__(1024) void k_trigger_scan(const int32_t *__restrict
     auto fetch = [&](int start, int (&id)[kScanPer]) {
 #pragma unroll
         for (int e = 0; e < kScanPer; ++e) {
-            const int p = start + (int)threadIdx.x * kScanPer + e;
-            id[e] = p < hi ? tokens[p] : -1;  // -1 belongs to no set
+            const uint32_t p = (uint32_t)start + threadIdx.x * kScanPer + e;  // (a tile may end past 2^31)
+            id[e] = p < (uint32_t)hi ? tokens[p] : -1;  // -1 belongs to no set
         }
     };
     int id[kScanPer];
     if (scan_from < hi) fetch(scan_from, id);
     for (long start = scan_from; start < hi; start += kScanTile) {
-        const int p0 = (int)start + (int)threadIdx.x * kScanPer;
+        const uint32_t p0 = (uint32_t)start + threadIdx.x * kScanPer;  // positions past `hi` hold no token and never fire
         bool is_k[kScanPer], is_d[kScanPer];
         int own_d = -1, own_k = -1;
 #pragma unroll
         for (int e = 0; e < kScanPer; ++e) {
             is_k[e] = in_set(kw, id[e], vocab), is_d[e] = w > 0 && in_set(delim, id[e], vocab);
-            if (is_d[e]) own_d = p0 + e;
-            if (is_k[e]) own_k = p0 + e;
+            if (is_d[e]) own_d = (int)(p0 + e);
+            if (is_k[e]) own_k = (int)(p0 + e);
         }
         if (start + kScanTile < hi) fetch((int)start + kScanTile, id);  // under this tile's reductions
         const int run_d = wave_running_max(own_d, lane), run_k = wave_running_max(own_k, lane);
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(1024) void k_trigger_scan(const int32_t *__restrict
         unsigned fire = 0;
 #pragma unroll
         for (int e = 0; e < kScanPer; ++e) {
-            const int p = p0 + e;
+            const int p = (int)(p0 + e);  // below `lo` if it has wrapped
             if (is_k[e]) last_k = p;
             // here last_d is the last delimiter before p, last_k the last keyword up to p
             const bool f = p >= lo && p < hi && (w == 0 ? is_k[e] : (p - w >= 0 && last_d == p - w && last_k > p - w));
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(1024) void k_trigger_scan(const int32_t *__restrict
 #pragma unroll
         for (int e = 0; e < kScanPer; ++e)
             if (fire >> e & 1u) {
-                if (off < cap) positions[off] = p0 + e;
+                if (off < cap) positions[off] = (int)(p0 + e);
                 ++off;
             }
         // (wave_d and wave_k were read before the second barrier, and wave_n is next written behind the next tile's first)

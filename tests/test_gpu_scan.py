@@ -42,3 +42,22 @@ def test_scan_tile_edges(window, lo, hi):
         assert n == len(want) and pos.tolist() == want[:cap]
     n, pos = B.st_trigger_scan(rule, dev, lo, hi, 9001)
     assert n == len(want) and pos.tolist() == want
+
+
+@pytest.mark.parametrize("window", [1, 4])
+def test_scan_ends_at_the_last_position(window):
+    """The last 40 positions of 2^31 - 1 tokens: the tile ends past 2^31."""
+    n, first = 2**31 - 1, 2**31 - 1 - 200
+    print(f"scan [{n - 40}, {n}) window {window}", flush=True)
+    toks = np.random.Generator(np.random.PCG64(5)).integers(0, 16, size=200, dtype=np.int32)
+    dev = torch.empty(n, dtype=torch.int32, device="cuda")
+    dev[first:] = torch.from_numpy(toks).cuda()
+    kw, dl = {1, 2, 3, 4, 5}, {6, 7}
+    rule = B.TriggerRule(16, B.host_bitmap(16, kw), B.host_bitmap(16, dl) if window > 1 else None, window)
+    want = [first + p for p in _rule_written_out(toks.tolist(), kw, dl, 160, 200, window)]
+    assert want
+    for scan in (B.st_trigger_scan, B.st_trigger_scan_static):
+        found, pos = scan(rule, dev, n - 40, n, 64)
+        assert found == len(want) and pos.tolist() == want
+    del dev
+    torch.cuda.empty_cache()
