@@ -1842,13 +1842,13 @@ static void stream_launch(const Model &m, const StreamShape &sh, const bf16_t *A
 // Up to kInvariantRows rows (the most a batched decode step holds) the K slices are those of a 16-row launch whatever
 // M is, and only the tile count per block follows M: a row's sums are then formed in the same order in every batch,
 // so its logits do not depend on which or how many other rows share the step.
-static StreamShape stream_shape(const Model &m, int M, int N, int K, int terms = 2) {
+static StreamShape stream_shape(const st_config &c, int M, int N, int K, int terms) {
     const int MT = (M + 31) / 32;
     const bool spec = MT <= kSpecTiles && terms == 2;  // (with one term the smaller blocks measured 1-2 % slower)
     constexpr int bk = StreamGeom::BK, seg = StreamGeom::kSeg;
     const int nk = K / bk;
     const int fixed = 640 / seg;  // stages' worth of time a block spends filling its ring and storing its tile
-    const size_t cap = partial_floats(m.c);
+    const size_t cap = partial_floats(c);
     // cheapest (tiles per block, K slices) for cost_rows rows in mt activation tiles; cap_rows rows must fit the
     // partial buffer; only_steps > 0 admits only slices of that many stages
     auto search = [&](int cost_rows, int mt, int cap_rows, int only_steps) {
@@ -2087,7 +2087,7 @@ static int gemm(const Model &m, const bf16_t *A, const bf16_t *Alo, int lda, con
                         (size_t)(DUAL ? 2 : 1) * N * K * sizeof(bf16_t) < ((size_t)1 << 32);
     const bool big = M >= ring_min_rows(Alo != nullptr) && K % kRingBK == 0 && K >= 2 * kRingBK && fits32;
     if (!DUAL && M < ring_min_rows(Alo != nullptr) && K % StreamGeom::BK == 0) {
-        const StreamShape sh = stream_shape(m, M, N, K, Alo ? 2 : 1);
+        const StreamShape sh = stream_shape(m.c, M, N, K, Alo ? 2 : 1);
         const int tiles = (M + 31) / 32;
         static_assert(kRingMinRows <= 3 * 32 + 1 && kRingMinRowsFast <= 5 * 32 + 1, "tiles the switches below know");
         if (Alo) {
@@ -2321,7 +2321,13 @@ void prefill_plan_forms(const st_config &c, int rows, int pos0, bool two_term, i
     } g[4] = {{false, (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim, h}, {false, h, qd}, {true, I, h}, {false, h, I}};
     for (int i = 0; i < 4; ++i) {
         forms[i] = 0;
-        if (rows < ring_min_rows(two_term) || g[i].K % kRingBK || g[i].K < 2 * kRingBK) continue;
+        if (g[i].K % kRingBK) continue;
+        if (rows < ring_min_rows(two_term)) {  // gate/up unfused, over all 2I rows
+            const StreamShape sh = stream_shape(c, rows, g[i].dual ? 2 * I : g[i].N, g[i].K, two_term ? 2 : 1);
+            forms[i] = sh.nt << 16 | sh.splits << 8;
+            continue;
+        }
+        if (g[i].K < 2 * kRingBK) continue;
         const RingPlan p = ring_plan(g[i].dual, two_term, rows, g[i].N, g[i].K, partial_floats(c), !g[i].dual);
         for (int l = 0; l < p.n; ++l) forms[i] |= p.half[l] ? 2 : 1;
         forms[i] |= (p.tail.n > 0 ? 4 : 0) | p.slices << 8;

@@ -168,7 +168,7 @@ def test_every_attention_form_is_reached(L):
                 for two in (False, True):
                     gemms, waves, ranges = B.st_prefill_plan_forms(cfg, rows, pos0, two)
                     seen.add((two, waves, ranges > 1))
-                    assert all((g is not None) == (rows >= (97 if two else 161)) for g in gemms)
+                    assert all(g[0] == ("ring" if rows >= (97 if two else 161) else "stream") for g in gemms)
     assert seen == {(t, w, r) for t in (False, True) for w in (4, 8) for r in (False, True)}
     assert B.st_prefill_plan_forms(synth.model_config("tiny_small", 128), 5, 0)[1] is None
     for rows, pos0 in ((0, 0), (4097, 0), (1, -1), (1, 8448), (4096, 4353)):

@@ -106,14 +106,14 @@ def test_split_attention_matches_oracle_over_many_ranges():
     g.close()
 
 
-@pytest.mark.parametrize("m,fast", [(32, False), (33, False), (64, False), (65, False), (128, False), (129, False),
-                                    (200, False), (256, False), (257, False), (512, False), (513, False),
-                                    (129, True), (192, True), (193, True), (257, True), (513, True)])
+@pytest.mark.parametrize("m,fast", [(32, False), (33, False), (64, False), (65, False), (96, False), (97, False), (128, False),
+                                    (129, False), (200, False), (256, False), (257, False), (512, False), (513, False),
+                                    (129, True), (160, True), (161, True), (192, True), (193, True), (257, True), (513, True)])
 def test_prefill_kernel_regime_boundaries(m, fast):
-    """Chunk lengths on both sides of every kernel switch (one more 32-row activation tile, 128- to 64-byte row
-    segments above 128 rows, the streaming kernel up to 240 rows, 256x256 tiles above -- with two-term inputs by
-    default; with single bf16 inputs on request: one-term streaming kernel from 129 rows, tiles from 193), on top of
-    100 cached keys, against the oracle (2 layers)."""
+    """Chunk lengths on both sides of every kernel switch (one more 32-row activation tile; the streaming kernel up to 96
+    rows and the ring kernel from 97, with another row tile after every 128 rows -- two-term inputs, the default;
+    with single bf16 inputs on request from 129 rows: streaming up to 160, ring from 161), on top of 100 cached keys,
+    against the oracle (2 layers)."""
     print_case(f"1.5B shape, 2 layers: 100 cached + chunk of {m}" + (" (single-term inputs)" if fast else ""))
     cfg, g, o = make_pair("qwen1p5b", 11, max_seq=640, max_chunk=520, n_layers=2, gen_device="cuda")
     prompt = synth.make_prompt(100 + m, cfg["vocab"], 12)
@@ -173,8 +173,8 @@ def test_prefill_is_bit_reproducible():
     outs = []
     for _ in range(3):
         g.truncate(0)
-        g.prefill(toks[:900], want_logits=False)          # 256x256 tiles
-        a, _ = g.prefill(toks[900:1121])                  # 221 rows: two-term path, key splits
+        g.prefill(toks[:900], want_logits=False)          # ring kernel, eight row tiles
+        a, _ = g.prefill(toks[900:1121])                  # 221 rows: two row tiles, K slices, key ranges
         b, _ = g.prefill(toks[1121:1142])                 # 21 rows: small tiles, many K slices
         outs.append((a, b))
     for a, b in outs[1:]:
@@ -212,8 +212,8 @@ def test_qwen32b_full_depth_paths_agree():
     w = synth.make_weights(cfg, 2, device="cuda")
     g = B.Model(cfg, w)
     toks = synth.make_prompt(201, cfg["vocab"], 21)
-    g.prefill(toks[:120], want_logits=False)               # 120 rows: four activation tiles
-    g.prefill(toks[120:200], want_logits=False)            # 80 rows: three
+    g.prefill(toks[:120], want_logits=False)               # 120 rows: one row tile of the ring kernel
+    g.prefill(toks[120:200], want_logits=False)            # 80 rows: three activation tiles of the streaming kernel
     a, tok_a = g.decode_step(int(toks[200]))               # GEMV path
     g.truncate(200)
     b, tok_b = g.prefill(toks[200:201])                    # one-row catch-up
@@ -224,7 +224,7 @@ def test_qwen32b_full_depth_paths_agree():
     assert max(rel_err(b, a), rel_err(c, a), rel_err(c, b)) <= LOGIT_TOL
     if _margin(a) >= MIN_MARGIN:
         assert tok_a == tok_b == tok_c
-    # A 260-row catch-up at full depth, four ways: two bf16 terms (ring kernels), passes of at most 128 rows
+    # A 260-row catch-up at full depth, four ways: two bf16 terms (ring kernels), passes of at most 96 rows
     # (streaming kernel, two terms), fp16 operands (the fp16 weight copy; the QKV input stays in two bf16 terms) and
     # single bf16 operands (ST_PREFILL_FAST).  They share the first 21 cached rows and are compared with the decode
     # step's logits for the same position (the oracle cannot reach this depth).  The three default-precision forms
@@ -237,8 +237,8 @@ def test_qwen32b_full_depth_paths_agree():
     g.truncate(280)
     dec, _ = g.decode_step(int(toks[280]))
     g.truncate(21)
-    g.prefill(toks[21:149], want_logits=False)
-    g.prefill(toks[149:277], want_logits=False)
+    for lo, hi in ((21, 117), (117, 213), (213, 277)):
+        g.prefill(toks[lo:hi], want_logits=False)
     short, _ = g.prefill(toks[277:281])
     g.truncate(21)
     fast, _ = g.prefill(toks[21:281], fast=True)
@@ -309,11 +309,11 @@ def test_long_pass_through_64_layers_of_a_narrow_model():
     g.close()
 
 
-@pytest.mark.parametrize("m", [1, 21, 32, 33, 86, 128, 129, 160, 192, 193, 257, 513])
+@pytest.mark.parametrize("m", [1, 21, 32, 33, 86, 96, 97, 128, 129, 160, 161, 192, 193, 257, 513])
 def test_f16_operand_mode_regime_boundaries(m):
     """With the fp16 weight copy attached, default passes run their O, gate/up and down GEMMs on the fp16 MFMA (single
-    fp16 activations; the QKV input and the queries stay in two bf16 terms) -- in the streaming kernel up to 128 rows,
-    in the ring kernel above: chunk lengths around the kernel switches, on top of 100 cached keys, against the oracle
+    fp16 activations; the QKV input and the queries stay in two bf16 terms) -- in the streaming kernel up to 160 rows
+    (the two-term QKV: 96), in the ring kernel above: chunk lengths around the kernel switches, on top of 100 cached keys, against the oracle
     (2 layers); the decode step is unchanged."""
     print_case(f"1.5B shape, 2 layers, fp16 operand mode: 100 cached + chunk of {m}")
     cfg, g, o = make_pair("qwen1p5b", 11, max_seq=640, max_chunk=520, n_layers=2, gen_device="cuda")

@@ -1,8 +1,10 @@
-"""Row tiles of the long-chunk GEMMs on the GPU: every tile height, ragged last rows and columns, each operand form.
+"""The GEMMs of catch-up passes on the GPU: row tiles of every height, ragged last rows and columns, both tile widths, each operand
+form; the streaming kernel's small blocks; contractions of 64.
 
-A pass of m rows is compared row by row with the same tokens fed in passes of 48 rows, which take another kernel (the
-streaming one), through the K/V rows of every layer, and its logits with the oracle's.  Shape: hidden 320 (five K steps),
-QKV 640 rows (two and a half column tiles), intermediate 448 (three and a half)."""
+test_row_tiles_of_every_height: a pass of m rows is compared row by row with the same tokens fed in passes of 48 rows, which
+take another kernel (the streaming one), through the K/V rows of every layer, and its logits with the oracle's.  Shape: hidden
+320 (five K steps), QKV 640 rows (two and a half column tiles), intermediate 448 (three and a half); all its tiles are of half
+width.  Full-width ones are in test_full_width_tiles_below_full_height."""
 import pytest
 import torch
 
@@ -52,9 +54,74 @@ def test_contractions_of_64(m, fast):
     print_case(f"2 layers, hidden 64: pass of {m} rows" + (" (single-term inputs)" if fast else ""))
     cfg, g, o = make_pair("tiny_small", 23, max_seq=300, max_chunk=300, n_layers=2, hidden=64, intermediate=64, n_q_heads=1,
                           n_kv_heads=1, head_dim=64, vocab=512)
-    assert B.st_prefill_plan_forms(cfg, m, 0, not fast)[0] == [None] * 4
+    streams = m <= (160 if fast else 96)
+    assert all((f is not None and f[0] == "stream") == streams for f in B.st_prefill_plan_forms(cfg, m, 0, not fast)[0])
     toks = synth.make_prompt(m, cfg["vocab"], 24)
     err = rel_err(g.prefill(toks, fast=fast)[0], o.feed(toks))
     print_case("logits against the oracle", err)
     assert err <= (2 * LOGIT_TOL if fast else LOGIT_TOL)
+    g.close()
+
+
+@pytest.mark.parametrize("name,m,mode,widths", [
+    ("qwen7b", 129, "default", "H H FH F"),   # heights 96 + 64
+    ("qwen32b", 129, "default", "F H F F"),
+    ("qwen32b", 300, "default", "F F F F"),   # 128 + 96 + 96
+    ("qwen7b", 386, "default", "F H FH F"),   # 128 + 96 + 96 + 96
+    ("qwen1p5b", 700, "default", "H H F F"),  # four of 128, two of 96
+    ("qwen32b", 200, "f16", "F H F H"),       # one tile of 256 (QKV: two terms, 128 + 96)
+    ("qwen7b", 257, "f16", "H H FH F"),       # 192 + 128 (QKV: 96 + 96 + 96)
+    ("qwen32b", 520, "fast", "F H F F")])     # 192 + 192 + 192
+def test_full_width_tiles_below_full_height(name, m, mode, widths):
+    """The tile widths the three paper shapes take at 129 to 700 rows, full ones among them: two layers, the second layer's K/V
+    rows of one pass against those of the same tokens in passes of 48 rows (streaming kernel, two terms).  Layer 0's O,
+    gate/up and down and layer 1's QKV stand behind every row."""
+    print_case(f"{name} shape, 2 layers: one pass of {m} rows ({mode}) against passes of 48")
+    cfg = synth.model_config(name, max_seq=768, max_chunk=768, n_layers=2)
+    cfg["vocab"] = 2048
+    forms, one_term = (B.st_prefill_plan_forms(cfg, m, 0, two)[0] for two in (mode == "default", False))
+    if mode == "f16":
+        forms = B.st_prefill_plan_forms(cfg, m, 0, True)[0][:1] + one_term[1:]
+    assert " ".join(f[1] for f in forms) == widths
+    g = B.Model(cfg, synth.make_weights(cfg, 25, device="cuda"))
+    if mode == "f16":
+        g.attach_f16()
+    toks = synth.make_prompt(m, cfg["vocab"], 26)
+    g.prefill(toks, want_logits=False, fast=mode == "fast")
+    kv = g.kv.view(torch.bfloat16).view(2, 2, cfg["n_kv_heads"], 768, 128)[:, 1, :, :m]
+    one = kv.float().clone()
+    g.truncate(0)
+    if mode == "f16":
+        g.attach_f16(False)
+    for a in range(0, m, 48):
+        g.prefill(toks[a:a + 48], want_logits=False)
+    ref = kv.float()
+    worst = float(((one - ref).norm(dim=-1) / ref.norm(dim=-1)).max())
+    print_case("worst row", worst)
+    assert worst <= ROW_TOL[mode]
+    g.close()
+
+
+@pytest.mark.parametrize("h,I,nq,nkv", [(320, 448, 3, 1), (1024, 1408, 6, 2), (1536, 2048, 6, 2)])
+@pytest.mark.parametrize("m", [1, 32, 33, 64, 65, 96])
+def test_streaming_blocks_of_two_and_three_weight_tiles(h, I, nq, nkv, m):
+    """The streaming kernel with fewer weight tiles than multiplying waves, slices of two stages (hidden 320: the last slice has
+    one), one to three activation tiles: the second layer's K/V rows of a pass against decode steps."""
+    print_case(f"2 layers, hidden {h}, intermediate {I}: pass of {m} rows against decode steps")
+    cfg = synth.model_config("tiny_small", max_seq=96, max_chunk=96, n_layers=2)
+    cfg.update(hidden=h, intermediate=I, n_q_heads=nq, n_kv_heads=nkv, head_dim=128, vocab=512)
+    tiles = [f[1] for f in B.st_prefill_plan_forms(cfg, m, 0)[0]]
+    assert all(f in (2, 3) for f in tiles) and (3 in tiles) == (h > 320 and m > 64)
+    g = B.Model(cfg, synth.make_weights(cfg, 27, device="cuda"))
+    toks = synth.make_prompt(m, cfg["vocab"], 28)
+    kv = g.kv.view(torch.bfloat16).view(2, 2, nkv, 96, 128)[:, 1, :, :m]
+    g.prefill(toks, want_logits=False)
+    one = kv.float().clone()
+    g.truncate(0)
+    for t in toks:
+        g.decode_step(int(t), want_logits=False)
+    ref = kv.float()
+    worst = float(((one - ref).norm(dim=-1) / ref.norm(dim=-1)).max())
+    print_case("worst row", worst)
+    assert worst <= ROW_TOL["default"]
     g.close()
