@@ -50,16 +50,17 @@ enum {
     ST_OUT_DEVICE = 2u,    /* output pointers are device memory; the call does not synchronise */
     ST_TOKEN_CHAINED = 4u, /* st_decode_step: ignore `token`, feed the model's own last greedy token
                               (kept on the device), so steps can be queued without a host round trip */
-    ST_PREFILL_TWO_TERM = 8u, /* st_prefill: feed a long run of tokens in passes of at most 256 rows (the length up
-                              to which the second bf16 term of the GEMM inputs costs no time) */
+    ST_PREFILL_TWO_TERM = 8u, /* st_prefill: feed a long run of tokens in passes of at most 256 rows, all GEMM and
+                              attention inputs in two bf16 terms (also where the fp16 weight copy is attached) */
     ST_PREFILL_FAST = 16u    /* st_prefill: in passes of more than 128 rows round every GEMM and attention input to
                               one bf16.  By default every pass carries those inputs as two bf16 terms (16 mantissa
                               bits), which leaves the bf16 K/V cache as its only rounding: its logits are then as
                               close to an fp32 evaluation as the decode step's.  Up to about 100 rows the second
                               term costs no time (the weight stream sets it); longer passes are bound by the MFMA
                               rate and pay twice the MFMA work.  With this flag passes of 129 rows and more take
-                              single bf16 inputs: 1.3x (129 rows) to 1.8x (1024 rows and more) faster, at about
-                              twice the logit error at the depths the CPU oracle reaches (1.7e-2 against 0.8e-2
+                              single bf16 inputs: at 1.5B / 7B / 32B (four layers on 512 keys) 0.96x / 1.17x / 1.36x
+                              as fast as the default at 129 to 160 rows, 1.05x / 1.29x / 1.41x at 256 and 1.22x /
+                              1.55x / 1.69x at 1024, at about twice the logit error at the depths the CPU oracle reaches (1.7e-2 against 0.8e-2
                               through 28 layers of the 1.5B shape) and more beyond (6.8e-2 from the decode step
                               through 64 layers of the 32B shape, where the default pass is at 1.3e-2).  Excludes
                               ST_PREFILL_TWO_TERM. */

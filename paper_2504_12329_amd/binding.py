@@ -256,7 +256,7 @@ class Model:
 
     def prefill(self, tokens, want_logits=True, two_term=False, fast=False):
         """tokens: host int array; two_term: passes of at most 256 rows (ST_PREFILL_TWO_TERM); fast: single-bf16 GEMM
-        inputs in passes of more than 256 rows (ST_PREFILL_FAST).  Returns (logits ndarray or None, greedy token)."""
+        inputs in passes of more than 128 rows (ST_PREFILL_FAST).  Returns (logits ndarray or None, greedy token)."""
         t = np.ascontiguousarray(tokens, dtype=np.int32)
         lg = np.empty(self.cfg["vocab"], dtype=np.float32) if want_logits else None
         nt = C.c_int32()

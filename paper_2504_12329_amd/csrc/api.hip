@@ -132,7 +132,7 @@ static int prefill_impl(Model *m, const int32_t *tokens, int32_t n, bool tokens_
         for (int32_t i = 0; i < n; ++i)
             if (tokens[i] < 0 || tokens[i] >= c.vocab)
                 return fail(ST_ERANGE, "token id %d at index %d is outside the vocabulary [0,%d)", tokens[i], i, c.vocab);
-    // passes of at most max_chunk rows; 256 rows on request: the longest pass that keeps every GEMM input in two terms
+    // passes of at most max_chunk rows, or of 256 on request (ST_PREFILL_TWO_TERM)
     const int32_t step = mode == kPassTwoTerm && c.max_chunk > 256 ? 256 : c.max_chunk;
     set_pass_mode(m, mode);
     for (int32_t done = 0; done < n; done += step) {

@@ -677,7 +677,9 @@ __device__ __forceinline__ void ring_tile(unsigned char *ring, const bf16_t *__r
     kstep(ic<0>{});
 
     // epilogue: register r of a 32x32 tile is row 8*(r/4) + 4*(lane/32) + r%4, column lane%32
-    auto silu_mul = [](float gt, float up) {  // hardware exp2 and reciprocal (1 ulp each, far below bf16)
+    // hardware exp2 and reciprocal, 1 ulp each: expf and a division take 1.1 to 3.2 % of a pass and leave its error against
+    // 64 bits what it is, to four digits over ten seeds
+    auto silu_mul = [](float gt, float up) {
         return gt * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gt)) * up;
     };
     // stores columns col, col + 1 of one row (col even) as 16-bit numbers, with the second bf16 term where it is wanted
@@ -1754,7 +1756,7 @@ size_t partial_floats(const st_config &c) {
     size_t rows = c.max_chunk > 1024 ? c.max_chunk : 1024;
     size_t qkv = (size_t)(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
     size_t cols = qkv > (size_t)c.hidden ? qkv : (size_t)c.hidden;
-    size_t short_chunk = (size_t)1024 * 2 * c.intermediate;  // gate/up slices of chunks up to 256 rows
+    size_t short_chunk = (size_t)1024 * 2 * c.intermediate;  // gate/up slices of the streaming passes
     size_t long_chunk = rows * cols + rows * cols / 4;         // one full-width slice + the extra slices of tail columns
     size_t head_rows = (size_t)kInvariantRows * c.vocab;       // LM-head GEMM of a batched step / ragged pass (one slice)
     size_t need = long_chunk > short_chunk ? long_chunk : short_chunk;
@@ -2159,7 +2161,7 @@ static int gemm(const Model &m, const bf16_t *A, const bf16_t *Alo, int lda, con
 // (only the bf16 K/V cache is left), and measured against the CPU oracle its logit error is the decode step's at
 // every depth tried.  Up to about 100 rows the second term is free (the weight stream sets the time); longer
 // passes are MFMA-bound and pay twice the MFMA work.  m.long_terms == 0 (ST_PREFILL_FAST) drops the second terms
-// of those longer passes: single bf16 inputs, about 1.8x faster, about twice the logit error.
+// of those longer passes: single bf16 inputs, up to 1.7x faster (see ST_PREFILL_FAST), about twice the logit error.
 struct PassTerms {
     bf16_t *xn_lo, *attn_lo, *act_lo, *qb_lo;  // where the producers write the low terms (nullptr: not needed)
     bool qkv_two, gu_two;                      // xn_lo feeds the QKV / the gate-up projection
@@ -2169,7 +2171,7 @@ struct PassTerms {
 };
 static PassTerms pass_terms(const Model &m, int n) {
     const Workspace &w = m.ws;
-    int terms = n <= 128 ? kTermAll : m.long_terms;  // up to 128 rows the second term is free in every mode
+    int terms = n <= 128 ? kTermAll : m.long_terms;  // (ST_PREFILL_FAST starts at 129 rows)
     PassTerms t;
     // Default-precision passes of a model that has its fp16 weight copy: at every pass length the inputs of the
     // gate/up, O and down projections are single fp16 numbers.  The input of the QKV projection and the queries keep

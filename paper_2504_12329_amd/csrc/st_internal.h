@@ -93,7 +93,7 @@ struct AttnRows {
     bf16_t *out_hi, *out_lo;
 };
 
-// Inputs that may carry a second bf16 term in a pass of more than 256 rows (Model::long_terms): the activations of
+// Inputs that may carry a second bf16 term in a pass of more than 128 rows (Model::long_terms): the activations of
 // the four projections and the rotated queries of the attention
 enum LongTerms { kTermQKV = 1, kTermO = 2, kTermGateUp = 4, kTermDown = 8, kTermQuery = 16, kTermAll = 31 };
 constexpr int kDefaultLongTerms = kTermAll;
