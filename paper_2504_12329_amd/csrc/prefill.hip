@@ -388,11 +388,18 @@ __device__ __forceinline__ void load_to_lds16(const void *g, uint32_t lds_off) {
                  "s"(__builtin_amdgcn_readfirstlane(lds_off))
                  : "memory");
 }
-// the same from a wave-uniform base and a 32-bit byte offset per lane (half the address registers to read)
+// the same from a wave-uniform base and a 32-bit byte offset per lane (half the address registers to read); NT: the line is
+// not kept in the caches
+template <bool NT = false>
 __device__ __forceinline__ void load_to_lds16(const void *base, uint32_t byte_off, uint32_t lds_off) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base),
-                 "s"(__builtin_amdgcn_readfirstlane(lds_off))
-                 : "memory");
+    if constexpr (NT)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(byte_off), "s"(base),
+                     "s"(__builtin_amdgcn_readfirstlane(lds_off))
+                     : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base),
+                     "s"(__builtin_amdgcn_readfirstlane(lds_off))
+                     : "memory");
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() {  // until at most N of this wave's direct loads are outstanding
@@ -778,28 +785,17 @@ __global__ __launch_bounds__(TERMS == 2 ? 512 : 256) void k_gemm_ring(const bf16
 
 // ---------------------------------------------------------------------------------------
 // Weight-streaming GEMM for chunks of at most 96 rows (one activation term: 160).  A block owns nt <= 8 tiles of 32
-// weight rows and a K slice; K advances 64 columns per stage.  Every block re-reads the activation rows from L2,
-// and direct loads of L2-resident data cost as much load-path time as the weights from HBM do (measured: adding
-// 24 KB of activations to 16 KB of weights per stage takes the weight stream from 6.0 to 4.2 TB/s), so the block
-// is made tall -- 256 weight rows per activation fetch -- and LDS is split into two rings: weights, nw stages,
-// filled by waves 0-1, and activations, na stages, filled by waves 2-3.  The two kinds of loads sit in different
-// waves because a wave's load counter retires in order: one wave cannot wait for a recent activation load
-// without also waiting for every older weight load.  A stage is 64 columns: HBM streams 128-byte row segments a fifth
-// faster than 64-byte ones.  All four waves multiply: wave w owns weight tiles w and w + 4 against every 32-row
-// activation tile (C^T = W A^T, a lane owns an activation row); raw fp32 partial sums of the K slice go to
-// part[z][M][N].  Needs K % 64 == 0 and (nw - 2) * (loads per weight wave per stage) <= 63.
+// weight rows and a K slice; K advances 64 columns per stage (HBM streams 128-byte row segments a fifth faster than 64-byte
+// ones).  Every block re-reads the activation rows from L2, so it is made tall -- up to 256 weight rows per activation fetch.
+// Eight waves: 0-3 multiply, 4 and 5 load weights, 6 and 7 activations, into two LDS rings of nw and na stages (a wave's
+// load counter retires in order: one wave could not wait for a recent activation load without also waiting for every older
+// weight load).  The loading waves' loop is unrolled for their load count, with wave-uniform bases and 32-bit lane offsets:
+// with 64-bit pointers, a branch per pair of loads and waves that did both above three activation tiles, a pass of 21 rows at
+// 1.5B took 1974 us (now 1843), one of 86 rows at 32B 1.50 ms (now 1.43), a step of 16 sequences at 32B 1.03 ms (now 0.95).
+// stream_once: see kStreamOnceBytes.  Wave w multiplies weight tiles w and w + 4 against every 32-row activation tile (C^T = W A^T, a lane owns
+// an activation row); raw fp32 partial sums of the K slice go to part[z][M][N].  Needs K % 64 == 0 and
+// (nw - 2) * (loads per weight wave per stage) <= 63.
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ void wait_loads_rt(int n) {  // s_waitcnt takes an immediate only
-#define ST_W1(v) case v: wait_loads<v>(); break;
-#define ST_W8(v) ST_W1(v) ST_W1(v + 1) ST_W1(v + 2) ST_W1(v + 3) ST_W1(v + 4) ST_W1(v + 5) ST_W1(v + 6) ST_W1(v + 7)
-    switch (n) {
-        ST_W8(0) ST_W8(8) ST_W8(16) ST_W8(24) ST_W8(32) ST_W8(40) ST_W8(48) ST_W8(56)
-        default: wait_loads<0>(); break;
-    }
-#undef ST_W8
-#undef ST_W1
-}
-
 struct StreamGeom {
     static constexpr int BK = 64;
     static constexpr int kSeg = BK * 2;          // bytes of a row per stage
@@ -808,116 +804,147 @@ struct StreamGeom {
     static constexpr int kWTile = 32 * kSeg;     // bytes of one 32-row weight tile per stage
     static constexpr int kARows = 32 * kSeg;     // bytes of 32 activation rows per stage (a tile holds one such block
                                                  // per term: high, low)
+    static constexpr int kMaxDepth = 17;         // stages of a ring (wait_stages)
 };
+
+// until at most `stages` stages of N loads each are outstanding (s_waitcnt takes an immediate only)
+template <int N>
+__device__ __forceinline__ void wait_stages(int stages) {
+#define ST_WS(v) case v: wait_loads<(N * (v) <= 63 ? N * (v) : 0)>(); break;
+    switch (stages) {
+        ST_WS(1) ST_WS(2) ST_WS(3) ST_WS(4) ST_WS(5) ST_WS(6) ST_WS(7) ST_WS(8)
+        ST_WS(9) ST_WS(10) ST_WS(11) ST_WS(12) ST_WS(13) ST_WS(14) ST_WS(15)
+        default: wait_loads<0>(); break;
+    }
+#undef ST_WS
+}
+
+// A loading wave of k_gemm_stream: N direct loads a stage at wave-uniform base + off[i], into a ring of `depth` stages of
+// `stage` bytes from LDS offset lds on (the wave's share of a stage is N KB).  TWO: every other group of four loads reads
+// base1, the first one if `odd`.  One barrier per stage: stage st is whole, and stage st - 1 has been read.
+template <int N, bool NT, bool TWO = false>
+__device__ __forceinline__ void stream_load(const bf16_t *base, const bf16_t *base1, int odd, const uint32_t (&off)[N], uint32_t lds,
+                                            uint32_t stage, int depth, int nk) {
+    const uint32_t ring_bytes = stage * depth;
+    const bf16_t *even_p = TWO && odd ? base1 : base, *odd_p = TWO && !odd ? base1 : base;
+    uint32_t slot = 0;
+    int issued = 0;
+    auto issue = [&]() {
+        static_for<N>([&](auto i_c) {
+            constexpr int i = decltype(i_c)::value;
+            load_to_lds16<NT>(i / 4 % 2 ? odd_p : even_p, off[i], lds + slot + i * 1024);
+        });
+        even_p += StreamGeom::BK, odd_p += StreamGeom::BK;
+        slot += stage;
+        if (slot == ring_bytes) slot = 0;
+        ++issued;
+    };
+    while (issued < depth - 1 && issued < nk) issue();
+    for (int st = 0; st < nk; ++st) {
+        wait_stages<N>(min(depth - 2, nk - 1 - st));  // only the stages after st are outstanding
+        __builtin_amdgcn_s_barrier();
+        if (issued < nk) issue();
+    }
+}
+
+// The weights' share of a stage for nt tiles: instruction q fills LDS rows 8q .. 8q + 7, lane -> (row lane / 8, 16-byte
+// position lane % 8 holding chunk position ^ swizzle(row)).  Rows past the edge re-read the last valid row and are never stored.
+template <int N>
+__device__ __forceinline__ void stream_load_w(const bf16_t *__restrict__ B, int lw, int lane, int n0, int N_rows, int K, int kbeg,
+                                              uint32_t lds, uint32_t stage, int depth, int nk, bool stream_once) {
+    uint32_t off[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int row = (lw * N + i) * StreamGeom::kRpi + lane / StreamGeom::kLpr;
+        off[i] = (uint32_t)(min(n0 + row, N_rows - 1) - n0) * (uint32_t)K * 2u + (((lane % StreamGeom::kLpr) ^ ring_swz(row)) << 4);
+    }
+    const bf16_t *base = B + (size_t)n0 * K + kbeg;
+    if (stream_once)
+        stream_load<N, true>(base, base, 0, off, lds + lw * N * 1024, stage, depth, nk);
+    else
+        stream_load<N, false>(base, base, 0, off, lds + lw * N * 1024, stage, depth, nk);
+}
 
 // TERMS = 2: activations as two bf16 terms (A + Alo).  TERMS = 1 with F16: single fp16 activations against the
 // model's fp16 copy of the weights on the f16 MFMA (half the activation traffic and half the MFMAs per weight byte).
-template <int MT, bool SPEC, int TERMS = 2, bool F16 = false>
-__global__ __launch_bounds__(SPEC ? 512 : 256) void k_gemm_stream(const bf16_t *__restrict__ A,
-                                                                  const bf16_t *__restrict__ Alo, int lda,
-                                                                  const bf16_t *__restrict__ B, int M, int N, int K,
-                                                                  int kps, int nt, int nw, int na,
-                                                                  float *__restrict__ part) {
+template <int MT, int TERMS = 2, bool F16 = false>
+__global__ __launch_bounds__(512) void k_gemm_stream(const bf16_t *__restrict__ A, const bf16_t *__restrict__ Alo, int lda,
+                                                     const bf16_t *__restrict__ B, int M, int N, int K, int kps, int nt, int nw,
+                                                     int na, int stream_once, float *__restrict__ part) {
     using G = StreamGeom;
-    constexpr int BK = G::BK;
     static_assert(TERMS == 1 || TERMS == 2, "one or two activation terms");
     constexpr int RT = 32 * TERMS;                   // LDS rows of one activation tile
     constexpr int kAStage = MT * TERMS * G::kARows;
     constexpr int kALoads = MT * RT / G::kRpi / 2;   // activation instructions per stage of each activation wave
-    constexpr int kWLoadsMax = 8 * 32 / G::kRpi / 2; // weight instructions per stage of each weight wave at nt = 8
-    constexpr int NL = kALoads > kWLoadsMax ? kALoads : kWLoadsMax;
     extern __shared__ __align__(16) unsigned char ring[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, kg = lane >> 5;
     const int n0 = blockIdx.x * nt * 32;
     const int kbeg = blockIdx.y * kps;
-    const int nk = (min(K, kbeg + kps) - kbeg) / BK;
+    const int nk = (min(K, kbeg + kps) - kbeg) / G::BK;
     const uint32_t ring0 = (uint32_t)(uintptr_t)ring;
     const int wstage = nt * G::kWTile, a_ring = na * kAStage;
-    // SPEC: eight waves, 0-3 multiply and 4-7 load (a wave is held ~70 clocks at every direct load it issues, time
-    // the multiplying waves then do not lose); otherwise four waves do both.
-    // (SPEC: nt may be below four, the multiplying waves past the last weight tile then idle; otherwise nt >= 4, because
-    // a wave that does both issues its loads between its MFMAs)
-    const bool computes = !SPEC || wave < min(4, nt), loads = !SPEC || wave >= 4;
-    const int lw = SPEC ? (wave - 4) & 3 : wave;  // loader index: 0, 1 weights; 2, 3 activations
 
-    // direct loads: a 1 KB instruction fills kRpi LDS rows; lane -> (row lane/kLpr, 16-byte position lane%kLpr
-    // holding global chunk position ^ swz(row)).  Activations: LDS row RT*t + 32*term + r is row 32*t + r of term
-    // (0 = high, 1 = low); rows past the edge re-read the last valid row and are never stored.
-    const bool w_loader = lw < 2;
-    const int n_loads = w_loader ? nt * 32 / G::kRpi / 2 : kALoads;
-    const int depth = w_loader ? nw : na;
-    const uint32_t my_ring = ring0 + (w_loader ? a_ring : 0), my_stage = w_loader ? wstage : kAStage;
-    const bf16_t *pl[NL];
-    int l_off[NL];
+    if (wave >= 6) {
+        // LDS row RT*t + 32*term + r is row 32*t + r of term (0 = high, 1 = low); rows past the edge re-read the last valid
+        // one and are never stored
+        const int q = wave - 6;
+        uint32_t off[kALoads];
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-        const int inst = (w_loader ? lw : lw - 2) * n_loads + i;
-        const int row = inst * G::kRpi + lane / G::kLpr;
-        const int piece = ((lane % G::kLpr) ^ ring_swz(row)) * 8;
-        if (w_loader) {
-            pl[i] = B + (size_t)min(n0 + row, N - 1) * K + kbeg + piece;
-        } else {
-            const int t = min(row / RT, MT - 1), term = (row >> 5) % TERMS, r = row & 31;
-            pl[i] = (term ? Alo : A) + (size_t)min(t * 32 + r, M - 1) * lda + kbeg + piece;
+        for (int i = 0; i < kALoads; ++i) {
+            const int row = (q * kALoads + i) * G::kRpi + lane / G::kLpr;
+            off[i] = (uint32_t)min(row / RT * 32 + (row & 31), M - 1) * (uint32_t)lda * 2u + (((lane % G::kLpr) ^ ring_swz(row)) << 4);
         }
-        l_off[i] = inst * 1024;
+        // 32-row block b of a stage is of term b % TERMS; wave q starts at block q * kALoads / 4
+        stream_load<kALoads, false, TERMS == 2>(A + kbeg, (TERMS == 2 ? Alo : A) + kbeg, kALoads / 4 % 2 ? q : 0, off,
+                                                ring0 + q * kALoads * 1024, kAStage, na, nk);
+        return;
     }
-    int iss_st = 0, iss_slot = 0;  // next stage this wave loads and its ring slot
-    auto issue_one = [&](auto i_c) {
-        constexpr int i = decltype(i_c)::value;
-        if constexpr (i < NL)
-            if (i < n_loads) load_to_lds16(pl[i] + iss_st * BK, my_ring + iss_slot * my_stage + l_off[i]);
-    };
-    auto issued = [&]() {
-        ++iss_st;
-        if (++iss_slot == depth) iss_slot = 0;
-    };
+    if (wave >= 4) {
+#define ST_SW(NTV) case NTV: stream_load_w<2 * NTV>(B, wave - 4, lane, n0, N, K, kbeg, ring0 + a_ring, wstage, nw, nk, stream_once); break;
+        switch (nt) {
+            ST_SW(2) ST_SW(3) ST_SW(4) ST_SW(5) ST_SW(6) ST_SW(7) ST_SW(8)
+        }
+#undef ST_SW
+        return;
+    }
+    if (wave >= nt) {  // no weight tile of its own
+        for (int st = 0; st < nk; ++st) __builtin_amdgcn_s_barrier();
+        return;
+    }
 
-    f32x16 acc[2][MT];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int t = 0; t < MT; ++t)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[j][t][r] = 0.f;
-    const bool second = wave + 4 < nt;  // this (multiplying) wave's second weight tile exists
     // swizzles of LDS rows 32*b + l32 for even / odd b (weight tile w and w + 4 have the parity of w)
     const int sw_even = ring_swz(l32), sw_odd = ring_swz(32 + l32), sw_w = (wave & 1) ? sw_odd : sw_even;
-
-    if (loads)
-        for (int st = 0; st < depth - 1 && st < nk; ++st) {
-            static_for<NL>([&](auto i_c) { issue_one(i_c); });
-            issued();
-        }
-    int wslot = 0, aslot = 0;
-    constexpr int KS = BK / 16, GROUPS = 2 * KS, PER = (NL + GROUPS - 1) / GROUPS;
-    for (int st = 0; st < nk; ++st) {
-        // stage st has landed once only the stages this wave issued after it are outstanding
-        if (loads) wait_loads_rt((iss_st - (st + 1)) * n_loads);
-        __builtin_amdgcn_s_barrier();  // stage st complete for every wave; every wave is done with stage st-1
-        const bool more = loads && iss_st < nk;
-        if (SPEC && more) static_for<NL>([&](auto i_c) { issue_one(i_c); });
-        if (computes) {
+    auto multiply = [&](auto nj_c) {
+        constexpr int NJ = decltype(nj_c)::value;  // weight tiles of this wave
+        f32x16 acc[NJ][MT];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[j][t][r] = 0.f;
+        int wslot = 0, aslot = 0;
+        constexpr int KS = G::BK / 16;
+        for (int st = 0; st < nk; ++st) {
+            __builtin_amdgcn_s_barrier();  // stage st complete for every wave; every wave is done with stage st-1
             const unsigned char *wb = ring + a_ring + wslot * wstage, *ab = ring + aslot * kAStage;
             // fragments of K step ks + 1 are read while the MFMAs of step ks run: one 16-byte read behind each of the
             // first MFMAs, pinned there -- issued as one run ahead of the MFMAs they cost the matrix pipe their issue
             // time
-            u32x4 wf[2][2], af[2][TERMS][MT];
-            constexpr int NR = 2 + TERMS * MT, NM = 2 * TERMS * MT;  // reads and MFMAs of a 16-wide step
-            // read r of a step: 0 = the first weight tile, 1 .. TERMS = activation tile 0 (high, low), TERMS + 1 = the
-            // second weight tile, then the other activation tiles
+            u32x4 wf[2][NJ], af[2][TERMS][MT];
+            constexpr int NR = NJ + TERMS * MT, NM = NJ * TERMS * MT;  // reads and MFMAs of a 16-wide step
+            // read r of a step: 0 = the first weight tile, 1 .. TERMS = activation tile 0 (high, low), then the second
+            // weight tile, then the other activation tiles
             auto frag = [&](auto ks_c, auto r_c) {
                 constexpr int ks = decltype(ks_c)::value, b = ks & 1, r = decltype(r_c)::value;
                 const int c = 2 * ks + kg;
                 if constexpr (r == 0) {
                     wf[b][0] = *reinterpret_cast<const u32x4 *>(wb + (wave * 32 + l32) * G::kSeg + (c ^ sw_w) * 16);
-                } else if constexpr (r == TERMS + 1) {
-                    if (second)
-                        wf[b][1] =
-                            *reinterpret_cast<const u32x4 *>(wb + ((wave + 4) * 32 + l32) * G::kSeg + (c ^ sw_w) * 16);
+                } else if constexpr (NJ == 2 && r == TERMS + 1) {
+                    wf[b][1] = *reinterpret_cast<const u32x4 *>(wb + ((wave + 4) * 32 + l32) * G::kSeg + (c ^ sw_w) * 16);
                 } else {
-                    constexpr int q = r <= TERMS ? r - 1 : r - 2, t = q / TERMS, term = q % TERMS;
+                    constexpr int q = r <= TERMS ? r - 1 : r - NJ, t = q / TERMS, term = q % TERMS;
                     constexpr int blk = t * TERMS + term;  // 32-row block of the activation stage
                     af[b][term][t] = *reinterpret_cast<const u32x4 *>(
                         ab + (blk * 32 + l32) * G::kSeg + (c ^ ((blk & 1) ? sw_odd : sw_even)) * 16);
@@ -929,55 +956,49 @@ __global__ __launch_bounds__(SPEC ? 512 : 256) void k_gemm_stream(const bf16_t *
                 static_for<NM>([&](auto m_c) {
                     constexpr int m = decltype(m_c)::value, j = m / (TERMS * MT), t = (m % (TERMS * MT)) / TERMS;
                     constexpr int term = m % TERMS;
-                    // a share of this wave's loads for the stage it fills, ahead of each weight tile's MFMAs
-                    if constexpr (m % (TERMS * MT) == 0)
-                        if (!SPEC && more)
-                            static_for<PER>([&](auto q_c) { issue_one(ic<(2 * ks + j) * PER + decltype(q_c)::value>{}); });
-                    if (j == 0 || second) {
-                        if constexpr (F16)
-                            acc[j][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(wf[b][j]), as_f16x8(af[b][term][t]),
-                                                                               acc[j][t], 0, 0, 0);
-                        else
-                            acc[j][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                as_bf16x8(wf[b][j]), as_bf16x8(af[b][term][t]), acc[j][t], 0, 0, 0);
-                    }
+                    if constexpr (F16)
+                        acc[j][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(wf[b][j]), as_f16x8(af[b][term][t]),
+                                                                           acc[j][t], 0, 0, 0);
+                    else
+                        acc[j][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(wf[b][j]), as_bf16x8(af[b][term][t]),
+                                                                            acc[j][t], 0, 0, 0);
                     if constexpr (ks + 1 < KS && m < NR) frag(ic<ks + 1>{}, m_c);
                     __builtin_amdgcn_sched_barrier(0);
                 });
-                // (one activation tile in one term has more reads than MFMAs: the rest follow the last MFMA)
+                // (where a step has more reads than MFMAs the rest follow the last MFMA)
                 if constexpr (ks + 1 < KS && NR > NM)
                     static_for<NR - NM>([&](auto e_c) { frag(ic<ks + 1>{}, ic<NM + decltype(e_c)::value>{}); });
             });
+            if (++wslot == nw) wslot = 0;
+            if (++aslot == na) aslot = 0;
         }
-        if (more) issued();
-        if (++wslot == nw) wslot = 0;
-        if (++aslot == na) aslot = 0;
-    }
-    if (!computes) return;
-    // C^T tile: lane = activation row (column of the MFMA result), register r = weight row 8*(r/4) + 4*kg + r%4
-    float *pz = part + (size_t)blockIdx.y * M * N;
+        // C^T tile: lane = activation row (column of the MFMA result), register r = weight row 8*(r/4) + 4*kg + r%4
+        float *pz = part + (size_t)blockIdx.y * M * N;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        if (j == 1 && !second) break;
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int t = 0; t < MT; ++t) {
-            const int m = t * 32 + l32;
-            if (m >= M) continue;
+            for (int t = 0; t < MT; ++t) {
+                const int m = t * 32 + l32;
+                if (m >= M) continue;
 #pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                const int n = n0 + (wave + 4 * j) * 32 + 8 * rq + 4 * kg;
-                float *dst = pz + (size_t)m * N + n;
-                if (n + 3 < N && (N & 3) == 0) {
-                    *reinterpret_cast<float4 *>(dst) = make_float4(acc[j][t][4 * rq + 0], acc[j][t][4 * rq + 1],
-                                                                   acc[j][t][4 * rq + 2], acc[j][t][4 * rq + 3]);
-                } else {
+                for (int rq = 0; rq < 4; ++rq) {
+                    const int n = n0 + (wave + 4 * j) * 32 + 8 * rq + 4 * kg;
+                    float *dst = pz + (size_t)m * N + n;
+                    if (n + 3 < N && (N & 3) == 0) {
+                        *reinterpret_cast<float4 *>(dst) = make_float4(acc[j][t][4 * rq + 0], acc[j][t][4 * rq + 1],
+                                                                       acc[j][t][4 * rq + 2], acc[j][t][4 * rq + 3]);
+                    } else {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (n + e < N) dst[e] = acc[j][t][4 * rq + e];
+                        for (int e = 0; e < 4; ++e)
+                            if (n + e < N) dst[e] = acc[j][t][4 * rq + e];
+                    }
                 }
             }
-        }
-    }
+    };
+    if (wave + 4 < nt)
+        multiply(ic<2>{});
+    else
+        multiply(ic<1>{});
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1787,10 +1808,6 @@ static void ring_launch(const Model &m, bool f16, bool out_f16, dim3 grid, const
 #undef ST_RING_GO
 }
 
-// Most activation tiles of the streaming kernel's form with loading waves of their own (eight waves fit the register file
-// up to three: a few percent faster there, slower with four).
-constexpr int kSpecTiles = 3;
-
 // The ring and streaming kernels use more dynamic LDS than a kernel gets by default; the limit is raised once per
 // process for every instantiation (called under std::call_once when the first model is created, so the launchers,
 // which may run on several host threads, never touch it).
@@ -1812,12 +1829,17 @@ hipError_t raise_lds_limits() {
     ST_RING_LIMIT(false, false) ST_RING_LIMIT(false, true) ST_RING_LIMIT(true, false) ST_RING_LIMIT(true, true)
 #undef ST_RING_LIMIT
 #define ST_STREAM_LIMIT(MT) \
-    take(raise_one(k_gemm_stream<MT, MT <= kSpecTiles, 1, false>)), take(raise_one(k_gemm_stream<MT, MT <= kSpecTiles, 1, true>));
+    take(raise_one(k_gemm_stream<MT, 1, false>)), take(raise_one(k_gemm_stream<MT, 1, true>));
     ST_STREAM_LIMIT(1) ST_STREAM_LIMIT(2) ST_STREAM_LIMIT(3) ST_STREAM_LIMIT(4) ST_STREAM_LIMIT(5)
-    take(raise_one(k_gemm_stream<1, true>)), take(raise_one(k_gemm_stream<2, true>)), take(raise_one(k_gemm_stream<3, true>));
+    take(raise_one(k_gemm_stream<1>)), take(raise_one(k_gemm_stream<2>)), take(raise_one(k_gemm_stream<3>));
 #undef ST_STREAM_LIMIT
     return e;
 }
+
+// Weight matrices larger than the L2s of the eight XCDs together (32 MB) are read with non-temporal loads: gate/up of the 32B
+// shape at 16 rows 96 -> 88 us (6.4 TB/s).  Four layers at 600 cached keys, limit 20 / 42 / 60 / 200 MB: 64 rows at 7B
+// 811 / 790 / 790 / 803 us, 40 rows at 1.5B 360 / 350 / 361 / 363 us; with none 64 rows at 32B 1311 -> 1248 us.
+constexpr size_t kStreamOnceBytes = (size_t)40 << 20;
 
 // Shape of a streaming GEMM launch: K columns per stage, weight tiles per block (2..8), K slices, ring depths.
 struct StreamShape {
@@ -1827,26 +1849,25 @@ struct StreamShape {
 template <int MT, int TERMS = 2, bool F16 = false>
 static void stream_launch(const Model &m, const StreamShape &sh, const bf16_t *A, const bf16_t *Alo, int lda,
                           const bf16_t *B, int M, int N, int K) {
-    constexpr bool SPEC = MT <= kSpecTiles;
-    auto kern = k_gemm_stream<MT, SPEC, TERMS, F16>;
+    auto kern = k_gemm_stream<MT, TERMS, F16>;
     using G = StreamGeom;
     const int lds = sh.na * MT * TERMS * G::kARows + sh.nw * sh.nt * G::kWTile;
     dim3 grid((N + 32 * sh.nt - 1) / (32 * sh.nt), sh.splits);
-    hipLaunchKernelGGL(kern, grid, dim3(SPEC ? 512 : 256), lds, m.stream, A, Alo, lda, B, M, N, K, sh.kps, sh.nt, sh.nw,
-                       sh.na, m.ws.qkv);
+    const int stream_once = (size_t)N * K * sizeof(bf16_t) >= kStreamOnceBytes;
+    hipLaunchKernelGGL(kern, grid, dim3(512), lds, m.stream, A, Alo, lda, B, M, N, K, sh.kps, sh.nt, sh.nw, sh.na, stream_once,
+                       m.ws.qkv);
 }
 
 // One block per CU at a time, so the time is (rounds of 256 blocks) x (bytes a block loads, weights and activations
-// alike, + a fixed cost per block); the partial sums written and read again are charged per CU as well.
-// Up to three activation tiles (loading waves of their own): down to two weight tiles per block and two stages per slice,
-// because the small projections of the 1.5B shape are latency, not bytes (with at least four tiles and four stages its
-// batched step of 3 / 16 / 40 rows took 339 / 393 / 452 us for four layers, now 320 / 377 / 435; a pass of 21 rows 1957 -> 1921 us; the 7B and 32B shapes the same within 0.6 %).
+// alike, + a fixed cost per block); the partial sums written and read again are charged per CU as well.  Down to two weight
+// tiles per block and two stages per slice, because the small projections of the 1.5B shape are latency, not bytes (with at
+// least four tiles and four stages its batched step of 3 / 16 / 40 rows took 339 / 393 / 452 us for four layers, now 320 /
+// 377 / 435; one term, 86 / 120 / 155 rows: 412 / 461 / 482, now 404 / 447 / 471; the 7B and 32B shapes the same within 0.6 %).
 // Up to kInvariantRows rows (the most a batched decode step holds) the K slices are those of a 16-row launch whatever
 // M is, and only the tile count per block follows M: a row's sums are then formed in the same order in every batch,
 // so its logits do not depend on which or how many other rows share the step.
 static StreamShape stream_shape(const st_config &c, int M, int N, int K, int terms) {
     const int MT = (M + 31) / 32;
-    const bool spec = MT <= kSpecTiles && terms == 2;  // (with one term the smaller blocks measured 1-2 % slower)
     constexpr int bk = StreamGeom::BK, seg = StreamGeom::kSeg;
     const int nk = K / bk;
     const int fixed = 640 / seg;  // stages' worth of time a block spends filling its ring and storing its tile
@@ -1856,11 +1877,11 @@ static StreamShape stream_shape(const st_config &c, int M, int N, int K, int ter
     auto search = [&](int cost_rows, int mt, int cap_rows, int only_steps) {
         StreamShape best = {8, 1, K, 2, 2};
         double best_cost = -1;
-        for (int nt = 8; nt >= (spec ? 2 : 4); --nt) {
+        for (int nt = 8; nt >= 2; --nt) {
             const int tiles = (N + 32 * nt - 1) / (32 * nt);
             for (int s = 1; s <= 32; ++s) {
                 const int steps = (nk + s - 1) / s;
-                if (s > 1 && (steps * bk < (spec ? 128 : 256) || (size_t)s * cap_rows * N > cap)) break;
+                if (s > 1 && (steps * bk < 128 || (size_t)s * cap_rows * N > cap)) break;
                 if (only_steps > 0 && steps != only_steps) continue;
                 const int used = (nk + steps - 1) / steps;  // slices that are not empty
                 const int rounds = (tiles * used + 255) / 256;
@@ -1886,6 +1907,7 @@ static StreamShape stream_shape(const st_config &c, int M, int N, int K, int ter
     int nw = (kRingLds - best.na * a_stage) / w_stage;
     const int w_loads = best.nt * 32 / (64 / (seg / 16)) / 2;  // per weight wave per stage
     if (nw > 2 + 63 / w_loads) nw = 2 + 63 / w_loads;
+    if (nw > StreamGeom::kMaxDepth) nw = StreamGeom::kMaxDepth;
     best.nw = nw;
     return best;
 }
