@@ -427,6 +427,7 @@ __device__ __forceinline__ void static_for(F &&f) {  // f(ic<0>{}), ..., f(ic<N-
 struct RingGrid {
     int My, Nx, x0, TY, TX, S, kps, per, blocks;  // x0: column tile of the launch's first column (in its own tiles)
     int h_base, h_extra;                          // heights of the row tiles (see ring_units)
+    int once;                                     // every weight is read by one block, from HBM (see ring_rot)
     int tail_x0, tail_tiles, tail_s, tail_kps;
 };
 // What block `bid` of a launch works on: tile (x, y) in the launch's own tiles (x before adding x0), K range
@@ -481,17 +482,25 @@ __host__ __device__ inline int ring_row0(const RingGrid &gg, int y, int unit) {
     return unit * (y * gg.h_base + (y < gg.h_extra ? y : gg.h_extra));
 }
 
+// A launch of one row tile reads every weight once, at the rate of HBM: matrices larger than the L2s (kStreamOnceBytes) are
+// then read non-temporally, and the column tiles start at eight different K steps of their range, going round its end, so
+// that the blocks, which run in step, do not all read the same columns of their rows at once.  Four layers on 600 cached
+// keys, neither / non-temporal / both: 128 rows at 7B 942 / 935 / 920 us, 256 fp16 rows at 32B 1680 / 1627 / 1602 (four starts
+// 1612), 128 rows at 1.5B 480 / 460 / 460.  Smaller matrices the same way: 100 to 256 rows at 1.5B 2-4 % slower than without.
+// Two row tiles and more share their weights in L2: 400 fp16 rows at 32B 2471 -> 2555 us with it.
+__host__ __device__ inline int ring_rot(int x, int nk) { return (x & 7) * nk >> 3; }
+
 // The block's tile: NF activation fragments of 32 LDS rows (one term: NF * 32 rows; two terms: NF * 16 rows, the high
 // terms in the first NF / 2 fragments, the low terms in the rest) against 256 weight rows (HALF: 128).  Full height:
 // four multiplying waves as 2 x 2; lower tiles: as 1 x 4, every wave all activation rows against a quarter of the weight
 // rows, so that all of them get shorter with the tile (at full height 2 x 2 reads fewer fragments per MFMA: 3-4 % faster).
 // HALF: half the columns and half the MFMAs per fragment of activations, for launches that full tiles would leave
 // short of blocks, and for the tiles left over after whole rounds of full tiles.
-template <int NF, bool DUAL, bool HALF, int TERMS, bool F16>
+template <int NF, bool DUAL, bool HALF, int TERMS, bool F16, bool ONCE>
 __device__ __forceinline__ void ring_tile(unsigned char *ring, const bf16_t *__restrict__ A, const bf16_t *__restrict__ Alo,
                                           int lda, const bf16_t *__restrict__ B, int M, int N, int K, float *__restrict__ pz,
                                           int ldp, bf16_t *__restrict__ outb, bf16_t *__restrict__ outlo, int ldo, int m0,
-                                          int n0, int kbeg, int nk, int out_f16) {
+                                          int n0, int kbeg, int nk, int rot, int out_f16) {
     static_assert(TERMS == 1 || !F16, "two terms are bf16");
     constexpr bool SPEC = TERMS == 2;  // waves 4-7 load, waves 0-3 multiply
     constexpr int WM = NF == 8 ? 2 : 1, WN = 4 / WM, TB = HALF ? 128 : 256;
@@ -536,26 +545,32 @@ __device__ __forceinline__ void ring_tile(unsigned char *ring, const bf16_t *__r
     };
     auto loadB = [&](auto i_c, int slot, const bf16_t *base) {
         constexpr int i = decltype(i_c)::value;
-        load_to_lds16(base, pb[i], ring0 + slot * kRingSlot + (wave * NLB + i) * 1024);
+        load_to_lds16<ONCE>(base, pb[i], ring0 + slot * kRingSlot + (wave * NLB + i) * 1024);
     };
+    // K positions: steps rot, rot + 1, ... round the end of the range (rot = 0 unless ONCE)
+    const bf16_t *const Aend = Aw + nk * kRingBK, *const Bend = Bw + nk * kRingBK;
+    auto stepA = [&](const bf16_t *p) { p += kRingBK; return ONCE && p == Aend ? Aw : p; };
+    auto stepB = [&](const bf16_t *p) { p += kRingBK; return ONCE && p == Bend ? Bw : p; };
+    const bf16_t *const A0 = ONCE ? Aw + rot * kRingBK : Aw, *const B0 = ONCE ? Bw + rot * kRingBK : Bw;
+    const bf16_t *const A1 = stepA(A0), *const B1 = stepB(B0), *const B2 = stepB(B1);
     auto next_slot = [](int s, int d) { return s + d >= kRingSlots ? s + d - kRingSlots : s + d; };
 
     // Ring order B0 A0 B1 A1 B2 ...: after K step kt the slots of B(kt) and A(kt) take A(kt+2) and B(kt+3) (loading
     // waves), or A(kt+2) and, under the next step, B(kt+3) (waves that do both).
     if constexpr (SPEC) {
         if (loader) {
-            static_for<NLB>([&](auto i_c) { loadB(i_c, 0, Bw); });
-            static_for<NLA>([&](auto i_c) { loadA(i_c, 1, Aw); });
-            static_for<NLB>([&](auto i_c) { loadB(i_c, 2, Bw + kRingBK); });
-            static_for<NLA>([&](auto i_c) { loadA(i_c, 3, Aw + kRingBK); });
+            static_for<NLB>([&](auto i_c) { loadB(i_c, 0, B0); });
+            static_for<NLA>([&](auto i_c) { loadA(i_c, 1, A0); });
+            static_for<NLB>([&](auto i_c) { loadB(i_c, 2, B1); });
+            static_for<NLA>([&](auto i_c) { loadA(i_c, 3, A1); });
             if (nk > 2) {
-                static_for<NLB>([&](auto i_c) { loadB(i_c, 4, Bw + 2 * kRingBK); });
+                static_for<NLB>([&](auto i_c) { loadB(i_c, 4, B2); });
                 wait_loads<2 * NLB + NLA>();  // B0 and A0 are in
             } else {
                 wait_loads<NLB + NLA>();
             }
             __builtin_amdgcn_s_barrier();
-            const bf16_t *an = Aw + 2 * kRingBK, *bn = Bw + 3 * kRingBK;
+            const bf16_t *an = stepA(A1), *bn = stepB(B2);
             int slot = 0;
             for (int kt = 0; kt + 1 < nk; ++kt) {
                 if (kt >= 1) {  // A(kt+1), B(kt+2) into the slots of B(kt-1), A(kt-1)
@@ -563,7 +578,7 @@ __device__ __forceinline__ void ring_tile(unsigned char *ring, const bf16_t *__r
                     slot = next_slot(slot, 1);
                     if (kt + 2 < nk) static_for<NLB>([&](auto i_c) { loadB(i_c, slot, bn); });
                     slot = next_slot(slot, 1);
-                    an += kRingBK, bn += kRingBK;
+                    an = stepA(an), bn = stepB(bn);
                 }
                 if (kt + 2 < nk) wait_loads<NLB>(); else wait_loads<0>();  // A(kt+1) and B(kt+1) are in
                 __builtin_amdgcn_s_barrier();
@@ -643,17 +658,17 @@ __device__ __forceinline__ void ring_tile(unsigned char *ring, const bf16_t *__r
 
     // prologue (waves that do both): B0 A0 B1 whole and the first half of A1 (nk >= 2)
     if constexpr (!SPEC) {
-        static_for<NLB>([&](auto i_c) { loadB(i_c, 0, Bw); });
-        static_for<NLA>([&](auto i_c) { loadA(i_c, 1, Aw); });
-        static_for<NLB>([&](auto i_c) { loadB(i_c, 2, Bw + kRingBK); });
-        static_for<HA>([&](auto i_c) { loadA(i_c, 3, Aw + kRingBK); });
+        static_for<NLB>([&](auto i_c) { loadB(i_c, 0, B0); });
+        static_for<NLA>([&](auto i_c) { loadA(i_c, 1, A0); });
+        static_for<NLB>([&](auto i_c) { loadB(i_c, 2, B1); });
+        static_for<HA>([&](auto i_c) { loadA(i_c, 3, A1); });
         wait_loads<NLB + HA>();  // B0 and A0 are in
     }
     __builtin_amdgcn_s_barrier();
     static_for<NR>([&](auto q_c) { fetch(ic<0>{}, q_c, 1, 0, 0); });
     __builtin_amdgcn_sched_barrier(0);
 
-    const bf16_t *an1 = Aw + kRingBK, *an2 = Aw + 2 * kRingBK, *bn2 = Bw + 2 * kRingBK;  // bases of A(kt+1), A(kt+2), B(kt+2)
+    const bf16_t *an1 = A1, *an2 = stepA(A1), *bn2 = B2;  // bases of A(kt+1), A(kt+2), B(kt+2)
     int sB = 0;  // ring slot of this K step's weights; its activations sit in the next slot, and so on round
     // AHEAD: 2 = K steps kt+1 and kt+2 exist, 1 = only kt+1, 0 = this is the last
     auto kstep = [&](auto ahead_c) {
@@ -676,7 +691,7 @@ __device__ __forceinline__ void ring_tile(unsigned char *ring, const bf16_t *__r
             step(ic<1>{}, ic<0>{}, sA1, sB1, 0, ic<0>{}, ic<0>{}, ic<0>{}, sB, an2);
         }
         sB = sB1;
-        an1 = an2, an2 += kRingBK, bn2 += kRingBK;  // A(kt+2) becomes A(kt+1)
+        an1 = an2, an2 = stepA(an2), bn2 = stepB(bn2);  // A(kt+2) becomes A(kt+1)
     };
     int kt = 0;
     for (; kt + 2 < nk; ++kt) kstep(ic<2>{});
@@ -758,7 +773,7 @@ __device__ __forceinline__ void ring_tile(unsigned char *ring, const bf16_t *__r
 
 // F16: A and B hold fp16 numbers (single-term activations, the model's fp16 copy of the weights).  out_f16: the
 // fused epilogue writes fp16 (one term) instead of bf16 (+ its low term).
-template <bool DUAL, bool HALF, int TERMS, bool F16>
+template <bool DUAL, bool HALF, int TERMS, bool F16, bool ONCE>
 __global__ __launch_bounds__(TERMS == 2 ? 512 : 256) void k_gemm_ring(const bf16_t *__restrict__ A,
                                                                       const bf16_t *__restrict__ Alo, int lda,
                                                                       const bf16_t *__restrict__ B, int M, int N, int K,
@@ -772,9 +787,10 @@ __global__ __launch_bounds__(TERMS == 2 ? 512 : 256) void k_gemm_ring(const bf16
     const int m0 = ring_row0(gg, rb.y, 64 / TERMS), n0 = (rb.x + gg.x0) * ((HALF ? 128 : 256) / (DUAL ? 2 : 1));
     const int kbeg = __builtin_amdgcn_readfirstlane(rb.kbeg);  // wave-uniform: the load bases live in scalar registers
     const int nk = __builtin_amdgcn_readfirstlane((rb.kend - rb.kbeg) / kRingBK);
+    const int rot = ONCE ? __builtin_amdgcn_readfirstlane(ring_rot(rb.x, nk)) : 0;
 #define ST_RING_TILE(NFV)                                                                                                  \
-    ring_tile<NFV, DUAL, HALF, TERMS, F16>(ring, A, Alo, lda, B, M, N, K, pz, rb.ldp, outb, outlo, ldo, m0, n0, kbeg, nk, \
-                                           out_f16)
+    ring_tile<NFV, DUAL, HALF, TERMS, F16, ONCE>(ring, A, Alo, lda, B, M, N, K, pz, rb.ldp, outb, outlo, ldo, m0, n0, kbeg, \
+                                                 nk, rot, out_f16)
     switch (__builtin_amdgcn_readfirstlane(ring_units(gg, rb.y))) {
         case 2: ST_RING_TILE(4); break;
         case 3: ST_RING_TILE(6); break;
@@ -1799,12 +1815,16 @@ static void gemm_launch(const Model &m, dim3 grid, const bf16_t *A, const bf16_t
 template <bool DUAL, bool HALF>
 static void ring_launch(const Model &m, bool f16, bool out_f16, dim3 grid, const bf16_t *A, const bf16_t *Alo, int lda,
                         const bf16_t *B, int M, int N, int K, bf16_t *outb, bf16_t *outlo, int ldo, const RingGrid &gg) {
-#define ST_RING_GO(TERMSV, F16V)                                                                                            \
-    hipLaunchKernelGGL((k_gemm_ring<DUAL, HALF, TERMSV, F16V>), grid, dim3(TERMSV == 2 ? 512 : 256), kRingLds, m.stream, A, \
-                       Alo, lda, B, M, N, K, m.ws.qkv, outb, outlo, ldo, gg, (int)out_f16)
-    if (Alo) ST_RING_GO(2, false);
-    else if (f16) ST_RING_GO(1, true);
-    else ST_RING_GO(1, false);
+#define ST_RING_GO(TERMSV, F16V, ONCEV)                                                                                         \
+    hipLaunchKernelGGL((k_gemm_ring<DUAL, HALF, TERMSV, F16V, ONCEV>), grid, dim3(TERMSV == 2 ? 512 : 256), kRingLds,        \
+                       m.stream, A, Alo, lda, B, M, N, K, m.ws.qkv, outb, outlo, ldo, gg, (int)out_f16)
+#define ST_RING_GO2(TERMSV, F16V)                       \
+    if (gg.once) ST_RING_GO(TERMSV, F16V, true);        \
+    else ST_RING_GO(TERMSV, F16V, false);
+    if (Alo) { ST_RING_GO2(2, false) }
+    else if (f16) { ST_RING_GO2(1, true) }
+    else { ST_RING_GO2(1, false) }
+#undef ST_RING_GO2
 #undef ST_RING_GO
 }
 
@@ -1821,12 +1841,13 @@ hipError_t raise_lds_limits() {
     auto take = [&](hipError_t r) {
         if (e == hipSuccess) e = r;
     };
-#define ST_RING_LIMIT(D, H)                                                                                 \
-    take(raise_one(k_gemm_ring<D, H, 1, false>)), take(raise_one(k_gemm_ring<D, H, 1, true>)), \
-        take(raise_one(k_gemm_ring<D, H, 2, false>));
+#define ST_RING_LIMIT(D, H, O)                                                                              \
+    take(raise_one(k_gemm_ring<D, H, 1, false, O>)), take(raise_one(k_gemm_ring<D, H, 1, true, O>)), \
+        take(raise_one(k_gemm_ring<D, H, 2, false, O>));
     take(raise_one(k_flash_long<false, false>)), take(raise_one(k_flash_long<true, false>));
     take(raise_one(k_flash_long<false, true>)), take(raise_one(k_flash_long<true, true>));
-    ST_RING_LIMIT(false, false) ST_RING_LIMIT(false, true) ST_RING_LIMIT(true, false) ST_RING_LIMIT(true, true)
+    ST_RING_LIMIT(false, false, false) ST_RING_LIMIT(false, true, false) ST_RING_LIMIT(true, false, false) ST_RING_LIMIT(true, true, false)
+    ST_RING_LIMIT(false, false, true) ST_RING_LIMIT(false, true, true) ST_RING_LIMIT(true, false, true) ST_RING_LIMIT(true, true, true)
 #undef ST_RING_LIMIT
 #define ST_STREAM_LIMIT(MT) \
     take(raise_one(k_gemm_stream<MT, 1, false>)), take(raise_one(k_gemm_stream<MT, 1, true>));
@@ -1950,6 +1971,7 @@ static RingPlan ring_plan(bool dual, bool two_term, int M, int N, int K, size_t 
     while (gg.TY * 2 <= gg.My && gg.TY < 8) gg.TY *= 2;
     gg.TX = 32 / gg.TY;
     gg.S = 1, gg.kps = K, gg.x0 = 0;
+    gg.once = gg.My == 1 && (size_t)N * K * (dual ? 4 : 2) >= kStreamOnceBytes;
     gg.tail_x0 = gg.tail_tiles = 0, gg.tail_s = 1, gg.tail_kps = K;
     const int width = dual ? 128 : 256;                          // output columns of a full tile
     const int nx = (N + width - 1) / width, nxh = (N + width / 2 - 1) / (width / 2);

@@ -102,6 +102,15 @@ def test_full_width_tiles_below_full_height(name, m, mode, widths):
     g.close()
 
 
+@pytest.mark.parametrize("name,m,mode,widths", [
+    ("qwen7b", 97, "default", "H H F H"), ("qwen32b", 128, "default", "H H F F"), ("qwen1p5b", 110, "default", "H H H H"),
+    ("qwen32b", 161, "f16", "F H F F"), ("qwen7b", 250, "f16", "H H F H"), ("qwen32b", 193, "fast", "H H F F")])
+def test_one_row_tile_with_weights_larger_than_the_l2(name, m, mode, widths):
+    """Passes of one row tile: matrices above 40 MB (gate/up of every shape, down of the 7B and all of the 32B shape) are read
+    round the end of their K range from eight starting steps; K slices of unequal lengths among them."""
+    test_full_width_tiles_below_full_height(name, m, mode, widths)
+
+
 @pytest.mark.parametrize("h,I,nq,nkv", [(320, 448, 3, 1), (1024, 1408, 6, 2), (1536, 2048, 6, 2)])
 @pytest.mark.parametrize("m", [1, 32, 33, 64, 65, 96])
 def test_streaming_blocks_of_two_and_three_weight_tiles(h, I, nq, nkv, m):
