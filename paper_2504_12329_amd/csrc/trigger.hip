@@ -21,24 +21,32 @@ __device__ __forceinline__ bool in_set(const uint32_t *bm, int id, int vocab) {
     return id >= 0 && id < vocab && ((bm[id >> 5] >> (id & 31)) & 1u);
 }
 
-// inclusive running maximum over the lanes of a wave
-__device__ __forceinline__ int wave_running_max(int v, int lane) {
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int u = __shfl_up(v, o, kWave);
-        if (lane >= o) v = max(v, u);
-    }
-    return v;
+// inclusive running maximum over the lanes of a wave: shifts inside the rows of 16 lanes, then the last lane of a row to the
+// rows after it (a lane without a source keeps its value)
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int dpp_max(int v) {
+    return max(v, __builtin_amdgcn_update_dpp(v, v, CTRL, ROW_MASK, 0xf, false));
+}
+__device__ __forceinline__ int wave_running_max(int v) {
+    v = dpp_max<0x111, 0xf>(v);  // row_shr:1
+    v = dpp_max<0x112, 0xf>(v);  // row_shr:2
+    v = dpp_max<0x114, 0xf>(v);  // row_shr:4
+    v = dpp_max<0x118, 0xf>(v);  // row_shr:8
+    v = dpp_max<0x142, 0xa>(v);  // row_bcast15 into rows 1 and 3
+    return dpp_max<0x143, 0xc>(v);  // row_bcast31 into rows 2 and 3
 }
 
-// A thread owns four consecutive positions of a 4096-token tile: one block's chain of tiles is bound by the latency of a
-// tile (token load, two dependent bitmap loads, three barriers), not by its work.  4608 / 18000 tokens, kernel alone:
-// 14.4 / 47.2 us with one position per thread, 10.4 / 24.8 us with four.
-constexpr int kScanPer = 4, kScanTile = 1024 * kScanPer;
+// A thread owns eight consecutive positions of an 8192-token tile: one block's chain of tiles is bound by the latency of a
+// tile (token load, bitmap look-ups, two barriers) and by the look-ups, random 4-byte reads that a CU serves one lane a clock.
+// STAGED: both bitmaps are copied to LDS first, beside the token load (a vocabulary of 152 k ids takes 19 KB each), and looked
+// up there.  4608 / 18000 tokens, kernel alone: one position per thread 14.4 / 47.2 us, four 9.3 / 24.7, eight with the bitmaps in LDS
+// 7.7 / 18.4 (300 tokens: 4.1 with four, 5.4 now, which the call does not show: its 22 us are launch and wait).
+constexpr int kScanPer = 8, kScanTile = 1024 * kScanPer;
+constexpr size_t kScanLds = 60 << 10;  // with the kernel's own arrays below the 64 KB every kernel may use
 
+template <bool STAGED>
 __global__ __launch_bounds__(1024) void k_trigger_scan(const int32_t *__restrict__ tokens, int lo, int hi,
-                                                       const uint32_t *__restrict__ kw,
-                                                       const uint32_t *__restrict__ delim, int window, int vocab,
+                                                       const uint32_t *kw, const uint32_t *delim, int window, int vocab,
                                                        int32_t *__restrict__ positions, int cap,
                                                        int32_t *__restrict__ n_found) {
     __shared__ int wave_d[16], wave_k[16], wave_n[16];
@@ -55,6 +63,22 @@ __global__ __launch_bounds__(1024) void k_trigger_scan(const int32_t *__restrict
     };
     int id[kScanPer];
     if (scan_from < hi) fetch(scan_from, id);
+    extern __shared__ __align__(16) uint32_t bitmaps[];
+    if constexpr (STAGED) {
+        const int words = (vocab + 31) >> 5, pad = (words + 3) & ~3;
+        auto stage = [&](const uint32_t *src, uint32_t *dst) {
+            const int n4 = ((uintptr_t)src & 15) == 0 ? words >> 2 : 0;
+            for (int i = threadIdx.x; i < n4; i += 1024) reinterpret_cast<u32x4 *>(dst)[i] = reinterpret_cast<const u32x4 *>(src)[i];
+            for (int i = 4 * n4 + threadIdx.x; i < words; i += 1024) dst[i] = src[i];
+        };
+        stage(kw, bitmaps);
+        kw = bitmaps;
+        if (w > 0) {
+            stage(delim, bitmaps + pad);
+            delim = bitmaps + pad;
+        }
+        __syncthreads();
+    }
     for (long start = scan_from; start < hi; start += kScanTile) {
         const uint32_t p0 = (uint32_t)start + threadIdx.x * kScanPer;  // positions past `hi` hold no token and never fire
         bool is_k[kScanPer], is_d[kScanPer];
@@ -66,7 +90,7 @@ __global__ __launch_bounds__(1024) void k_trigger_scan(const int32_t *__restrict
             if (is_k[e]) own_k = (int)(p0 + e);
         }
         if (start + kScanTile < hi) fetch((int)start + kScanTile, id);  // under this tile's reductions
-        const int run_d = wave_running_max(own_d, lane), run_k = wave_running_max(own_k, lane);
+        const int run_d = wave_running_max(own_d), run_k = wave_running_max(own_k);
         int last_d = __shfl_up(run_d, 1, kWave), last_k = __shfl_up(run_k, 1, kWave);  // of the lanes before this one
         if (lane == 0) last_d = last_k = -1;
         if (lane == kWave - 1) wave_d[wave] = run_d, wave_k[wave] = run_k;
@@ -88,12 +112,17 @@ __global__ __launch_bounds__(1024) void k_trigger_scan(const int32_t *__restrict
             fire |= (unsigned)f << e;
             if (is_d[e]) last_d = p;
         }
-        const int cnt = __popc(fire);  // 0 .. 4: its three bits are summed over the lower lanes by ballots
-        const unsigned long long b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2), b2 = __ballot(cnt & 4);
-        if (lane == 0) wave_n[wave] = __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
-        __syncthreads();
+        const int cnt = __popc(fire);  // 0 .. 8: its four bits are summed over the lower lanes by ballots
         const unsigned long long below = (1ull << lane) - 1ull;
-        int off = __popcll(b0 & below) + 2 * __popcll(b1 & below) + 4 * __popcll(b2 & below), all_n = base;
+        int off = 0, wave_total = 0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const unsigned long long m = __ballot(cnt >> b & 1);
+            off += __popcll(m & below) << b, wave_total += __popcll(m) << b;
+        }
+        if (lane == 0) wave_n[wave] = wave_total;
+        __syncthreads();
+        int all_n = base;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             if (v == wave) off += all_n;
@@ -135,36 +164,56 @@ int deliver_scan(const int32_t *dev, int32_t range, int32_t *positions, int32_t 
 
 void launch_trigger_scan(const st_trigger_rule &rule, const int32_t *tokens, int32_t lo, int32_t hi,
                          int32_t *positions, int32_t cap, int32_t *n_found, hipStream_t stream) {
-    hipLaunchKernelGGL(k_trigger_scan, dim3(1), dim3(1024), 0, stream, tokens, lo, hi, rule.kw_bitmap,
-                       rule.delim_bitmap, rule.window, rule.vocab, positions, cap, n_found);
+    const size_t lds = (size_t)(((rule.vocab + 31ll) / 32 + 3) & ~3ll) * sizeof(uint32_t) * (rule.window > 1 ? 2 : 1);
+    if (lds <= kScanLds)
+        hipLaunchKernelGGL(k_trigger_scan<true>, dim3(1), dim3(1024), lds, stream, tokens, lo, hi, rule.kw_bitmap,
+                           rule.delim_bitmap, rule.window, rule.vocab, positions, cap, n_found);
+    else
+        hipLaunchKernelGGL(k_trigger_scan<false>, dim3(1), dim3(1024), 0, stream, tokens, lo, hi, rule.kw_bitmap,
+                           rule.delim_bitmap, rule.window, rule.vocab, positions, cap, n_found);
 }
 
 // ---------------------------------------------------------------------------------------
-// The scan for callers that cannot allocate device memory: the result staging (count + positions) lives in a
-// file-scope device array instead of a caller-provided scratch buffer.  Every GPU the library runs on holds its
-// own copy of the array until the process ends; its address is looked up once per device.
+// The scan for callers that cannot allocate device memory: the result staging (count + positions) belongs to the library --
+// pinned host memory the kernel writes straight into, so that no copy follows it (4608 tokens with their call: 33.5 us with a
+// device array and a copy, 22.8 us this way; 18000 tokens 49 and 35 us).  One per GPU the library has been called on, allocated by the first call, held
+// until the process ends.  Where it cannot be had, a file-scope device array and a copy take its place.
 // ---------------------------------------------------------------------------------------
 static __device__ __align__(256) int32_t scratch[1 + ST_SCAN_STATIC_MAX_CAP];
 
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mutex;
-static int32_t *g_scratch_ptr[kMaxDevices];  // device address of `scratch` on each device (nullptr: not looked up yet)
+struct ScanStage {
+    int32_t *dev, *host;  // where the kernel writes; the same memory as the host reads it (nullptr: device array)
+};
+static ScanStage g_stage[kMaxDevices];  // dev == nullptr: not looked up yet
 
-// Device address of this device's copy of the staging array (the array's name is only a host-side handle).
-static int scratch_address(int32_t **out) {
+static int scan_stage(ScanStage *out) {
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return fail(ST_EHIP, "hipGetDevice: %s", hipGetErrorString(e));
     if (dev < 0 || dev >= kMaxDevices) return fail(ST_EHIP, "device index %d outside [0, %d)", dev, kMaxDevices);
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
-    if (!g_scratch_ptr[dev]) {
-        void *p = nullptr;
-        e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (e != hipSuccess || !p)
-            return fail(ST_EHIP, "hipGetSymbolAddress(scratch): %s", hipGetErrorString(e));
-        g_scratch_ptr[dev] = static_cast<int32_t *>(p);
+    ScanStage &st = g_stage[dev];
+    if (!st.dev) {
+        // (an allocation must not disturb a capture this thread may have under way on some stream)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        void *host = nullptr, *p = nullptr;
+        e = hipHostMalloc(&host, sizeof(scratch), hipHostMallocDefault);
+        if (e == hipSuccess) e = hipHostGetDevicePointer(&p, host, 0);
+        if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (e == hipSuccess && p) {
+            st.dev = static_cast<int32_t *>(p), st.host = static_cast<int32_t *>(host);
+        } else {
+            (void)hipGetLastError();
+            e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+            if (e != hipSuccess || !p)
+                return fail(ST_EHIP, "hipGetSymbolAddress(scratch): %s", hipGetErrorString(e));
+            st.dev = static_cast<int32_t *>(p), st.host = nullptr;
+        }
     }
-    *out = g_scratch_ptr[dev];
+    *out = st;
     return ST_OK;
 }
 
@@ -182,13 +231,19 @@ extern "C" int st_trigger_scan_static(const st_trigger_rule *rule, const int32_t
     if (cap > ST_SCAN_STATIC_MAX_CAP)
         return fail(ST_ERANGE, "cap %d exceeds the static staging array (%d positions)", cap, ST_SCAN_STATIC_MAX_CAP);
     if (lo < 0 || hi < lo) return fail(ST_ERANGE, "bad range [%d,%d)", lo, hi);
-    int32_t *stage = nullptr;
-    if (int rc = scratch_address(&stage)) return rc;
+    ScanStage stage;
+    if (int rc = scan_stage(&stage)) return rc;
     hipStream_t s = (hipStream_t)stream;
     // the kernel writes the count and the first min(count, cap) positions on every call: nothing of the previous
     // call's contents is read, so nothing has to be cleared
-    launch_trigger_scan(*rule, tokens, lo, hi, stage + 1, cap, stage, s);
+    launch_trigger_scan(*rule, tokens, lo, hi, stage.dev + 1, cap, stage.dev, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ST_EHIP, "trigger scan: %s", hipGetErrorString(e));
-    return deliver_scan(stage, hi - lo, positions, cap, n_found, s);
+    if (!stage.host) return deliver_scan(stage.dev, hi - lo, positions, cap, n_found, s);
+    e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return fail(ST_EHIP, "trigger scan: %s", hipGetErrorString(e));
+    *n_found = stage.host[0];
+    const int32_t k = stage.host[0] < cap ? stage.host[0] : cap;
+    if (k > 0) memcpy(positions, stage.host + 1, sizeof(int32_t) * (size_t)k);
+    return ST_OK;
 }

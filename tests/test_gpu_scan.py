@@ -61,3 +61,28 @@ def test_scan_ends_at_the_last_position(window):
         assert found == len(want) and pos.tolist() == want
     del dev
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("vocab,window", [(33, 1), (151936, 2), (245760, 21), (245792, 2), (491520, 1), (600001, 1), (600001, 3)])
+def test_scan_tiles_of_8192_with_bitmaps_staged_or_not(vocab, window):
+    """Eight positions per thread, 8192 to a tile; bitmaps of up to 60 KB together are looked up in LDS, larger ones in global
+    memory, also from addresses that are not 16-byte aligned."""
+    rng = np.random.Generator(np.random.PCG64(vocab + window))
+    toks = rng.integers(-2, vocab + 2, size=16500, dtype=np.int32)
+    kw, dl = set(range(0, vocab, 2)), set(range(3, vocab, 7))
+    bits = [np.zeros((vocab + 31) // 32, dtype=np.uint32) for _ in range(2)]
+    for bm, ids in zip(bits, (kw, dl)):
+        np.bitwise_or.at(bm, np.fromiter(ids, np.int64) >> 5, np.uint32(1) << (np.fromiter(ids, np.int64) & 31).astype(np.uint32))
+    dev = torch.from_numpy(toks).cuda()
+    for shift in (0, 1):
+        held = [torch.cat([torch.zeros(shift, dtype=torch.int32), torch.from_numpy(b.view(np.int32))]).cuda() for b in bits]
+        rule = B.TriggerRule(vocab, bits[0], bits[1] if window > 1 else None, window)
+        rule.kw, rule.delim = held[0][shift:], held[1][shift:]
+        rule.c.kw_bitmap, rule.c.delim_bitmap = rule.kw.data_ptr(), rule.delim.data_ptr() if window > 1 else 0
+        for lo, hi in ((0, 8191), (0, 8192), (1, 8194), (8190, 16385), (0, 16500)):
+            print(f"scan [{lo}, {hi}) vocab {vocab} window {window} shift {shift}", flush=True)
+            want = _rule_written_out(toks.tolist(), kw, dl, lo, hi, window)
+            n, pos = B.st_trigger_scan(rule, dev, lo, hi, 16500)
+            assert n == len(want) and pos.tolist() == want
+            n, pos = B.st_trigger_scan_static(rule, dev, lo, hi, 4096)
+            assert n == len(want) and pos.tolist() == want[:4096]
