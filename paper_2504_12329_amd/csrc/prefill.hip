@@ -835,6 +835,18 @@ __device__ __forceinline__ void wait_stages(int stages) {
 #undef ST_WS
 }
 
+// silu(gate) * up, and four neighbouring ones stored as two bf16 terms or (f16) as one fp16 number each
+__device__ __forceinline__ float swiglu(float gate, float up) { return gate / (1.0f + expf(-gate)) * up; }
+__device__ __forceinline__ void put_act4(bf16_t *hi, bf16_t *lo, int f16, float v0, float v1, float v2, float v3) {
+    if (f16) {  // fp16 operand mode: one fp16 number, no low term
+        *reinterpret_cast<u32x2 *>(hi) = u32x2{pack_f16x2(v0, v1), pack_f16x2(v2, v3)};
+        return;
+    }
+    const u32x2 h = {pack_bf16x2(v0, v1), pack_bf16x2(v2, v3)};
+    *reinterpret_cast<u32x2 *>(hi) = h;
+    *reinterpret_cast<u32x2 *>(lo) = u32x2{pack_bf16x2(v0 - bf16_lo(h.x), v1 - bf16_hi(h.x)), pack_bf16x2(v2 - bf16_lo(h.y), v3 - bf16_hi(h.y))};
+}
+
 // A loading wave of k_gemm_stream: N direct loads a stage at wave-uniform base + off[i], into a ring of `depth` stages of
 // `stage` bytes from LDS offset lds on (the wave's share of a stage is N KB).  TWO: every other group of four loads reads
 // base1, the first one if `odd`.  One barrier per stage: stage st is whole, and stage st - 1 has been read.
@@ -865,14 +877,17 @@ __device__ __forceinline__ void stream_load(const bf16_t *base, const bf16_t *ba
 
 // The weights' share of a stage for nt tiles: instruction q fills LDS rows 8q .. 8q + 7, lane -> (row lane / 8, 16-byte
 // position lane % 8 holding chunk position ^ swizzle(row)).  Rows past the edge re-read the last valid row and are never stored.
-template <int N>
+// DUAL: n0 and N_rows count output columns; a tile of 32 rows holds 16 gate rows, then the matching 16 up rows.
+template <int N, bool DUAL>
 __device__ __forceinline__ void stream_load_w(const bf16_t *__restrict__ B, int lw, int lane, int n0, int N_rows, int K, int kbeg,
                                               uint32_t lds, uint32_t stage, int depth, int nk, bool stream_once) {
     uint32_t off[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         const int row = (lw * N + i) * StreamGeom::kRpi + lane / StreamGeom::kLpr;
-        off[i] = (uint32_t)(min(n0 + row, N_rows - 1) - n0) * (uint32_t)K * 2u + (((lane % StreamGeom::kLpr) ^ ring_swz(row)) << 4);
+        const int col = DUAL ? (row >> 5) * 16 + (row & 15) : row, up = DUAL ? row >> 4 & 1 : 0;
+        off[i] = (uint32_t)(min(n0 + col, N_rows - 1) - n0 + up * N_rows) * (uint32_t)K * 2u +
+                 (((lane % StreamGeom::kLpr) ^ ring_swz(row)) << 4);
     }
     const bf16_t *base = B + (size_t)n0 * K + kbeg;
     if (stream_once)
@@ -883,10 +898,12 @@ __device__ __forceinline__ void stream_load_w(const bf16_t *__restrict__ B, int 
 
 // TERMS = 2: activations as two bf16 terms (A + Alo).  TERMS = 1 with F16: single fp16 activations against the
 // model's fp16 copy of the weights on the f16 MFMA (half the activation traffic and half the MFMAs per weight byte).
-template <int MT, int TERMS = 2, bool F16 = false>
+// DUAL: the fused gate/up form (one K slice): N counts output columns and silu(gate) * up goes to outb (+ outlo, or as fp16).
+template <int MT, int TERMS, bool F16, bool DUAL>
 __global__ __launch_bounds__(512) void k_gemm_stream(const bf16_t *__restrict__ A, const bf16_t *__restrict__ Alo, int lda,
                                                      const bf16_t *__restrict__ B, int M, int N, int K, int kps, int nt, int nw,
-                                                     int na, int stream_once, float *__restrict__ part) {
+                                                     int na, int stream_once, float *__restrict__ part, bf16_t *__restrict__ outb,
+                                                     bf16_t *__restrict__ outlo, int out_f16) {
     using G = StreamGeom;
     static_assert(TERMS == 1 || TERMS == 2, "one or two activation terms");
     constexpr int RT = 32 * TERMS;                   // LDS rows of one activation tile
@@ -895,7 +912,7 @@ __global__ __launch_bounds__(512) void k_gemm_stream(const bf16_t *__restrict__ 
     extern __shared__ __align__(16) unsigned char ring[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, kg = lane >> 5;
-    const int n0 = blockIdx.x * nt * 32;
+    const int n0 = blockIdx.x * nt * (DUAL ? 16 : 32);
     const int kbeg = blockIdx.y * kps;
     const int nk = (min(K, kbeg + kps) - kbeg) / G::BK;
     const uint32_t ring0 = (uint32_t)(uintptr_t)ring;
@@ -917,7 +934,7 @@ __global__ __launch_bounds__(512) void k_gemm_stream(const bf16_t *__restrict__ 
         return;
     }
     if (wave >= 4) {
-#define ST_SW(NTV) case NTV: stream_load_w<2 * NTV>(B, wave - 4, lane, n0, N, K, kbeg, ring0 + a_ring, wstage, nw, nk, stream_once); break;
+#define ST_SW(NTV) case NTV: stream_load_w<2 * NTV, DUAL>(B, wave - 4, lane, n0, N, K, kbeg, ring0 + a_ring, wstage, nw, nk, stream_once); break;
         switch (nt) {
             ST_SW(2) ST_SW(3) ST_SW(4) ST_SW(5) ST_SW(6) ST_SW(7) ST_SW(8)
         }
@@ -989,6 +1006,26 @@ __global__ __launch_bounds__(512) void k_gemm_stream(const bf16_t *__restrict__ 
             if (++aslot == na) aslot = 0;
         }
         // C^T tile: lane = activation row (column of the MFMA result), register r = weight row 8*(r/4) + 4*kg + r%4
+        if constexpr (DUAL) {  // registers 0-7 are gate rows, 8-15 the matching up rows
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int t = 0; t < MT; ++t) {
+                    const int m = t * 32 + l32;
+                    if (m >= M) continue;
+#pragma unroll
+                    for (int rq = 0; rq < 2; ++rq) {
+                        const int n = n0 + (wave + 4 * j) * 16 + 8 * rq + 4 * kg;  // N is a multiple of eight
+                        if (n >= N) continue;
+                        float v[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            v[e] = swiglu(acc[j][t][4 * rq + e], acc[j][t][4 * (rq + 2) + e]);
+                        put_act4(outb + (size_t)m * N + n, outlo + (size_t)m * N + n, out_f16, v[0], v[1], v[2], v[3]);
+                    }
+                }
+            return;
+        }
         float *pz = part + (size_t)blockIdx.y * M * N;
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
@@ -1107,17 +1144,8 @@ __global__ __launch_bounds__(256) void k_swiglu_rows(const float *__restrict__ p
             up.x += b[u].x; up.y += b[u].y; up.z += b[u].z; up.w += b[u].w;
         }
     }
-    const float v0 = gt.x / (1.0f + expf(-gt.x)) * up.x, v1 = gt.y / (1.0f + expf(-gt.y)) * up.y;
-    const float v2 = gt.z / (1.0f + expf(-gt.z)) * up.z, v3 = gt.w / (1.0f + expf(-gt.w)) * up.w;
-    if (f16) {  // fp16 operand mode: one fp16 number, no low term
-        const u32x2 h16 = {pack_f16x2(v0, v1), pack_f16x2(v2, v3)};
-        reinterpret_cast<u32x2 *>(act + (size_t)row * I)[i4] = h16;
-        return;
-    }
-    u32x2 hi = {pack_bf16x2(v0, v1), pack_bf16x2(v2, v3)};
-    u32x2 lo = {pack_bf16x2(v0 - bf16_lo(hi.x), v1 - bf16_hi(hi.x)), pack_bf16x2(v2 - bf16_lo(hi.y), v3 - bf16_hi(hi.y))};
-    reinterpret_cast<u32x2 *>(act + (size_t)row * I)[i4] = hi;
-    reinterpret_cast<u32x2 *>(act_lo + (size_t)row * I)[i4] = lo;
+    const size_t at = (size_t)row * I + 4 * i4;
+    put_act4(act + at, act_lo + at, f16, swiglu(gt.x, up.x), swiglu(gt.y, up.y), swiglu(gt.z, up.z), swiglu(gt.w, up.w));
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1849,10 +1877,13 @@ hipError_t raise_lds_limits() {
     ST_RING_LIMIT(false, false, false) ST_RING_LIMIT(false, true, false) ST_RING_LIMIT(true, false, false) ST_RING_LIMIT(true, true, false)
     ST_RING_LIMIT(false, false, true) ST_RING_LIMIT(false, true, true) ST_RING_LIMIT(true, false, true) ST_RING_LIMIT(true, true, true)
 #undef ST_RING_LIMIT
-#define ST_STREAM_LIMIT(MT) \
-    take(raise_one(k_gemm_stream<MT, 1, false>)), take(raise_one(k_gemm_stream<MT, 1, true>));
+#define ST_STREAM_LIMIT(MT)                                                                                  \
+    take(raise_one(k_gemm_stream<MT, 1, false, false>)), take(raise_one(k_gemm_stream<MT, 1, true, false>)), \
+        take(raise_one(k_gemm_stream<MT, 1, false, true>)), take(raise_one(k_gemm_stream<MT, 1, true, true>));
     ST_STREAM_LIMIT(1) ST_STREAM_LIMIT(2) ST_STREAM_LIMIT(3) ST_STREAM_LIMIT(4) ST_STREAM_LIMIT(5)
-    take(raise_one(k_gemm_stream<1>)), take(raise_one(k_gemm_stream<2>)), take(raise_one(k_gemm_stream<3>));
+    take(raise_one(k_gemm_stream<1, 2, false, false>)), take(raise_one(k_gemm_stream<1, 2, false, true>));
+    take(raise_one(k_gemm_stream<2, 2, false, false>)), take(raise_one(k_gemm_stream<2, 2, false, true>));
+    take(raise_one(k_gemm_stream<3, 2, false, false>)), take(raise_one(k_gemm_stream<3, 2, false, true>));
 #undef ST_STREAM_LIMIT
     return e;
 }
@@ -1867,16 +1898,50 @@ struct StreamShape {
     int nt, splits, kps, nw, na;
 };
 
-template <int MT, int TERMS = 2, bool F16 = false>
+// dual: the fused gate/up form; N counts output columns (weight rows: 2 N)
+struct StreamOut {
+    bf16_t *act, *act_lo;
+    bool f16;
+};
+template <int MT, int TERMS, bool F16>
 static void stream_launch(const Model &m, const StreamShape &sh, const bf16_t *A, const bf16_t *Alo, int lda,
-                          const bf16_t *B, int M, int N, int K) {
-    auto kern = k_gemm_stream<MT, TERMS, F16>;
+                          const bf16_t *B, int M, int N, int K, const StreamOut *dual) {
     using G = StreamGeom;
-    const int lds = sh.na * MT * TERMS * G::kARows + sh.nw * sh.nt * G::kWTile;
-    dim3 grid((N + 32 * sh.nt - 1) / (32 * sh.nt), sh.splits);
-    const int stream_once = (size_t)N * K * sizeof(bf16_t) >= kStreamOnceBytes;
-    hipLaunchKernelGGL(kern, grid, dim3(512), lds, m.stream, A, Alo, lda, B, M, N, K, sh.kps, sh.nt, sh.nw, sh.na, stream_once,
-                       m.ws.qkv);
+    const int lds = sh.na * MT * TERMS * G::kARows + sh.nw * sh.nt * G::kWTile, cols = (dual ? 16 : 32) * sh.nt;
+    const dim3 grid((N + cols - 1) / cols, sh.splits);
+    const int stream_once = (size_t)N * K * sizeof(bf16_t) * (dual ? 2 : 1) >= kStreamOnceBytes;
+    if (dual)
+        hipLaunchKernelGGL((k_gemm_stream<MT, TERMS, F16, true>), grid, dim3(512), lds, m.stream, A, Alo, lda, B, M, N, K,
+                           sh.kps, sh.nt, sh.nw, sh.na, stream_once, (float *)nullptr, dual->act, dual->act_lo, (int)dual->f16);
+    else
+        hipLaunchKernelGGL((k_gemm_stream<MT, TERMS, F16, false>), grid, dim3(512), lds, m.stream, A, Alo, lda, B, M, N, K,
+                           sh.kps, sh.nt, sh.nw, sh.na, stream_once, m.ws.qkv, (bf16_t *)nullptr, (bf16_t *)nullptr, 0);
+}
+static void stream_dispatch(const Model &m, const StreamShape &sh, const bf16_t *A, const bf16_t *Alo, int lda, const bf16_t *B,
+                            int M, int N, int K, bool f16, const StreamOut *dual) {
+    const int tiles = (M + 31) / 32;
+    static_assert(kRingMinRows <= 3 * 32 + 1 && kRingMinRowsFast <= 5 * 32 + 1, "tiles the switches below know");
+    if (Alo) {
+        switch (tiles) {
+            case 1: stream_launch<1, 2, false>(m, sh, A, Alo, lda, B, M, N, K, dual); break;
+            case 2: stream_launch<2, 2, false>(m, sh, A, Alo, lda, B, M, N, K, dual); break;
+            default: stream_launch<3, 2, false>(m, sh, A, Alo, lda, B, M, N, K, dual); break;
+        }
+        return;
+    }
+    // one activation term: fp16 operands, or single bf16 (ST_PREFILL_FAST)
+#define ST_STREAM1(MTV)                                                                \
+    case MTV:                                                                          \
+        if (f16)                                                                       \
+            stream_launch<MTV, 1, true>(m, sh, A, nullptr, lda, B, M, N, K, dual);     \
+        else                                                                           \
+            stream_launch<MTV, 1, false>(m, sh, A, nullptr, lda, B, M, N, K, dual);    \
+        break;
+    switch (tiles) {
+        ST_STREAM1(1) ST_STREAM1(2) ST_STREAM1(3) ST_STREAM1(4)
+        default: ST_STREAM1(5)
+    }
+#undef ST_STREAM1
 }
 
 // One block per CU at a time, so the time is (rounds of 256 blocks) x (bytes a block loads, weights and activations
@@ -1887,7 +1952,9 @@ static void stream_launch(const Model &m, const StreamShape &sh, const bf16_t *A
 // Up to kInvariantRows rows (the most a batched decode step holds) the K slices are those of a 16-row launch whatever
 // M is, and only the tile count per block follows M: a row's sums are then formed in the same order in every batch,
 // so its logits do not depend on which or how many other rows share the step.
-static StreamShape stream_shape(const st_config &c, int M, int N, int K, int terms) {
+// one_slice: the cheapest shape with a single K slice (the fused gate/up form); *cost_out: the modelled time in bytes per CU.
+static StreamShape stream_shape(const st_config &c, int M, int N, int K, int terms, bool one_slice = false,
+                                double *cost_out = nullptr) {
     const int MT = (M + 31) / 32;
     constexpr int bk = StreamGeom::BK, seg = StreamGeom::kSeg;
     const int nk = K / bk;
@@ -1900,7 +1967,7 @@ static StreamShape stream_shape(const st_config &c, int M, int N, int K, int ter
         double best_cost = -1;
         for (int nt = 8; nt >= 2; --nt) {
             const int tiles = (N + 32 * nt - 1) / (32 * nt);
-            for (int s = 1; s <= 32; ++s) {
+            for (int s = 1; s <= (one_slice ? 1 : 32); ++s) {
                 const int steps = (nk + s - 1) / s;
                 if (s > 1 && (steps * bk < 128 || (size_t)s * cap_rows * N > cap)) break;
                 if (only_steps > 0 && steps != only_steps) continue;
@@ -1911,6 +1978,7 @@ static StreamShape stream_shape(const st_config &c, int M, int N, int K, int ter
                 if (best_cost < 0 || cost < best_cost) {
                     best_cost = cost;
                     best.nt = nt, best.splits = used, best.kps = steps * bk;
+                    if (cost_out) *cost_out = cost;
                 }
             }
         }
@@ -1918,7 +1986,7 @@ static StreamShape stream_shape(const st_config &c, int M, int N, int K, int ter
     };
     StreamShape best;
     if (M <= kInvariantRows) {
-        const StreamShape canon = search(16, 1, kInvariantRows, 0);
+        const StreamShape canon = search(16, 1, kInvariantRows, 0);  // (one_slice: K)
         best = search(M, MT, kInvariantRows, canon.kps / bk);
     } else {
         best = search(M, MT, M, 0);
@@ -1931,6 +1999,20 @@ static StreamShape stream_shape(const st_config &c, int M, int N, int K, int ter
     if (nw > StreamGeom::kMaxDepth) nw = StreamGeom::kMaxDepth;
     best.nw = nw;
     return best;
+}
+
+// The gate/up projection of a short pass (2I rows of weights): with one K slice and the SwiGLU in its epilogue where that costs
+// less than the K slices that load the chip best plus a kernel that adds them -- about 4 us, in which a CU loads 110 KB.
+// Sliced / fused, four layers (1.5B: 28) on 600 cached keys: 50 rows 2073 / 2038, 762 / 744, 1196 / 1162 us at 1.5B / 7B / 32B, 155
+// fp16 rows at 7B and 32B 923 / 895, 1436 / 1376 us; 86 rows at 1.5B, which stay sliced, 2500.
+// Batches (up to kInvariantRows rows) decide by 16 rows whatever they hold, so that a row's sums do not depend on the others.
+static bool stream_fuses(const st_config &c, int M, int I, int K, int terms) {
+    if ((size_t)(I + 256) * K * sizeof(bf16_t) >= (size_t)1 << 32) return false;  // (32-bit offsets between gate and up rows)
+    double one = 0, sliced = 0;
+    const int rows = M <= kInvariantRows ? 16 : M;
+    stream_shape(c, rows, 2 * I, K, terms, true, &one);
+    stream_shape(c, rows, 2 * I, K, terms, false, &sliced);
+    return one <= sliced + 110e3;
 }
 
 // Launches of the ring kernel for one GEMM of a long chunk: tile width, K slices, leftover tiles and block numbering.
@@ -2134,29 +2216,7 @@ static int gemm(const Model &m, const bf16_t *A, const bf16_t *Alo, int lda, con
     const bool big = M >= ring_min_rows(Alo != nullptr) && K % kRingBK == 0 && K >= 2 * kRingBK && fits32;
     if (!DUAL && M < ring_min_rows(Alo != nullptr) && K % StreamGeom::BK == 0) {
         const StreamShape sh = stream_shape(m.c, M, N, K, Alo ? 2 : 1);
-        const int tiles = (M + 31) / 32;
-        static_assert(kRingMinRows <= 3 * 32 + 1 && kRingMinRowsFast <= 5 * 32 + 1, "tiles the switches below know");
-        if (Alo) {
-            switch (tiles) {
-                case 1: stream_launch<1>(m, sh, A, Alo, lda, B, M, N, K); break;
-                case 2: stream_launch<2>(m, sh, A, Alo, lda, B, M, N, K); break;
-                default: stream_launch<3>(m, sh, A, Alo, lda, B, M, N, K); break;
-            }
-            return sh.splits;
-        }
-        // one activation term: fp16 operands, or single bf16 (ST_PREFILL_FAST)
-#define ST_STREAM1(MTV)                                                           \
-    case MTV:                                                                     \
-        if (f16)                                                                  \
-            stream_launch<MTV, 1, true>(m, sh, A, nullptr, lda, B, M, N, K);      \
-        else                                                                      \
-            stream_launch<MTV, 1, false>(m, sh, A, nullptr, lda, B, M, N, K);     \
-        break;
-        switch (tiles) {
-            ST_STREAM1(1) ST_STREAM1(2) ST_STREAM1(3) ST_STREAM1(4)
-            default: ST_STREAM1(5)
-        }
-#undef ST_STREAM1
+        stream_dispatch(m, sh, A, Alo, lda, B, M, N, K, f16, nullptr);
         return sh.splits;
     }
     if (big) return ring_gemm<DUAL>(m, f16, out_f16, A, Alo, lda, B, M, N, K, outb, outlo, ldo, tail);
@@ -2198,6 +2258,20 @@ static int gemm(const Model &m, const bf16_t *A, const bf16_t *Alo, int lda, con
     else
         gemm_launch<128, 128, 2, 2, DUAL, false>(m, grid, A, Alo, lda, B, M, N, K, kps, outb, outlo, ldo, gg);
     return DUAL ? 0 : splits;
+}
+
+// Gate/up projection and SwiGLU of a pass too short for the ring kernel: w.act (+ w.act_lo, or fp16) from n rows A (+ Alo).
+static void gate_up_short(const Model &m, const bf16_t *A, const bf16_t *Alo, const bf16_t *B, int n, bool f16, bool out_f16) {
+    const int h = m.c.hidden, I = m.c.intermediate, terms = Alo ? 2 : 1;
+    const Workspace &w = m.ws;
+    if (n < ring_min_rows(Alo != nullptr) && h % StreamGeom::BK == 0 && stream_fuses(m.c, n, I, h, terms)) {
+        const StreamOut out = {w.act, w.act_lo, out_f16};
+        stream_dispatch(m, stream_shape(m.c, n, 2 * I, h, terms, true), A, Alo, h, B, n, I, h, f16, &out);
+        return;
+    }
+    const int sg = gemm<false>(m, A, Alo, h, B, n, 2 * I, h, nullptr, nullptr, 0, nullptr, f16);
+    hipLaunchKernelGGL(k_swiglu_rows, dim3((I / 4 + 255) / 256, n), dim3(256), 0, m.stream, w.qkv, sg, (size_t)n * 2 * I, I,
+                       w.act, w.act_lo, (int)out_f16);
 }
 
 // Which GEMM and attention inputs of a pass over n rows carry a second bf16 term (x = hi + lo, 16 mantissa bits).
@@ -2369,7 +2443,9 @@ void prefill_plan_forms(const st_config &c, int rows, int pos0, bool two_term, i
         forms[i] = 0;
         if (g[i].K % kRingBK) continue;
         if (rows < ring_min_rows(two_term)) {  // gate/up unfused, over all 2I rows
-            const StreamShape sh = stream_shape(c, rows, g[i].dual ? 2 * I : g[i].N, g[i].K, two_term ? 2 : 1);
+            const int terms = two_term ? 2 : 1;
+            const StreamShape sh = stream_shape(c, rows, g[i].dual ? 2 * I : g[i].N, g[i].K, terms,
+                                                g[i].dual && stream_fuses(c, rows, I, g[i].K, terms));
             forms[i] = sh.nt << 16 | sh.splits << 8;
             continue;
         }
@@ -2410,10 +2486,7 @@ void launch_prefill_layers(const Model &m, int32_t pos0, int32_t n) {
                            m.norm_mlp[l], w.xn, t.f16_xg ? nullptr : xn_lo, h, c.rms_eps, to, (int)t.f16_xg);
         if (n < (h % kRingBK == 0 ? ring_min_rows(t.gu_two) : kSmallRows + 1)) {  // small chunk: gate/up as a plain split-K
                                                                            // GEMM over all 2I rows, SwiGLU in the consumer
-            int sg = gemm<false>(m, w.xn, t.f16_xg ? nullptr : xn_lo, h, t.f16_xg ? m.wgu16[l] : m.wgu[l], n, 2 * I, h,
-                                 nullptr, nullptr, 0, nullptr, t.f16_xg);
-            hipLaunchKernelGGL(k_swiglu_rows, dim3((I / 4 + 255) / 256, n), dim3(256), 0, m.stream, w.qkv, sg,
-                               (size_t)n * 2 * I, I, w.act, w.act_lo, (int)t.f16_act);
+            gate_up_short(m, w.xn, t.f16_xg ? nullptr : xn_lo, t.f16_xg ? m.wgu16[l] : m.wgu[l], n, t.f16_xg, t.f16_act);
         } else {
             gemm<true>(m, w.xn, t.gu_two ? xn_lo : nullptr, h, t.f16_xg ? m.wgu16[l] : m.wgu[l], n, I, h, w.act, act_lo, I,
                        nullptr, t.f16_xg, t.f16_act);
@@ -2571,9 +2644,7 @@ void launch_batch_step(const Model &m, const BatchRows &b, int n, int attn_block
         const int so = gemm<false>(m, w.attn, w.attn_lo, qd, m.wo[l], n, h, qd, nullptr, nullptr, 0);
         hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n), dim3(norm_threads(n)), 0, m.stream, w.x, w.qkv, so, (size_t)n * h,
                            m.norm_mlp[l], w.xn, w.xn_lo, h, c.rms_eps, PartTail{}, 0);
-        const int sg = gemm<false>(m, w.xn, w.xn_lo, h, m.wgu[l], n, 2 * I, h, nullptr, nullptr, 0);
-        hipLaunchKernelGGL(k_swiglu_rows, dim3((I / 4 + 255) / 256, n), dim3(256), 0, m.stream, w.qkv, sg,
-                           (size_t)n * 2 * I, I, w.act, w.act_lo, 0);
+        gate_up_short(m, w.xn, w.xn_lo, m.wgu[l], n, false, false);
         pending = gemm<false>(m, w.act, w.act_lo, I, m.wdown[l], n, h, I, nullptr, nullptr, 0);
     }
     hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n), dim3(norm_threads(n)), 0, m.stream, w.x, w.qkv, pending, (size_t)n * h,
@@ -2638,10 +2709,7 @@ void launch_prefill_varlen(const Model &m, const BatchRows &b, const FlashSeg *s
         hipLaunchKernelGGL(k_rmsnorm_rows, dim3(R), dim3(norm_threads(R)), 0, m.stream, w.x, w.qkv, so, (size_t)R * h,
                            m.norm_mlp[l], w.xn, t.f16_xg ? nullptr : xn_lo, h, c.rms_eps, PartTail{}, (int)t.f16_xg);
         if (R < (h % kRingBK == 0 ? ring_min_rows(t.gu_two) : kSmallRows + 1)) {
-            const int sg = gemm<false>(m, w.xn, t.f16_xg ? nullptr : xn_lo, h, t.f16_xg ? m.wgu16[l] : m.wgu[l], R, 2 * I, h,
-                                       nullptr, nullptr, 0, nullptr, t.f16_xg);
-            hipLaunchKernelGGL(k_swiglu_rows, dim3((I / 4 + 255) / 256, R), dim3(256), 0, m.stream, w.qkv, sg,
-                               (size_t)R * 2 * I, I, w.act, w.act_lo, (int)t.f16_act);
+            gate_up_short(m, w.xn, t.f16_xg ? nullptr : xn_lo, t.f16_xg ? m.wgu16[l] : m.wgu[l], R, t.f16_xg, t.f16_act);
         } else {
             gemm<true>(m, w.xn, t.gu_two ? xn_lo : nullptr, h, t.f16_xg ? m.wgu16[l] : m.wgu[l], R, I, h, w.act, act_lo, I,
                        nullptr, t.f16_xg, t.f16_act);

@@ -134,3 +134,26 @@ def test_streaming_blocks_of_two_and_three_weight_tiles(h, I, nq, nkv, m):
     print_case("worst row", worst)
     assert worst <= ROW_TOL["default"]
     g.close()
+
+
+@pytest.mark.parametrize("I", [8, 456, 1016])
+@pytest.mark.parametrize("m", [1, 33, 96])
+def test_fused_gate_up_with_a_ragged_last_tile(I, m):
+    """The streaming gate/up with its SwiGLU in the epilogue (one K slice), the last tile with eight of its sixteen columns: the
+    second layer's K/V rows of a pass against decode steps."""
+    print_case(f"2 layers, hidden 320, intermediate {I}: pass of {m} rows against decode steps")
+    cfg = synth.model_config("tiny_small", max_seq=96, max_chunk=96, n_layers=2)
+    cfg.update(hidden=320, intermediate=I, n_q_heads=3, n_kv_heads=1, head_dim=128, vocab=512)
+    assert B.st_prefill_plan_forms(cfg, m, 0)[0][2][2] == 1
+    g = B.Model(cfg, synth.make_weights(cfg, 29, device="cuda"))
+    toks = synth.make_prompt(m, cfg["vocab"], 30)
+    kv = g.kv.view(torch.bfloat16).view(2, 2, 1, 96, 128)[:, 1, :, :m]
+    g.prefill(toks, want_logits=False)
+    one = kv.float().clone()
+    g.truncate(0)
+    for t in toks:
+        g.decode_step(int(t), want_logits=False)
+    worst = float(((one - kv.float()).norm(dim=-1) / kv.float().norm(dim=-1)).max())
+    print_case("worst row", worst)
+    assert worst <= ROW_TOL["default"]
+    g.close()
