@@ -111,8 +111,8 @@ int st_prefill_plan_check(const st_config *cfg, int32_t rows, int32_t *launches,
 /* Host-only: which kernel forms a pass of `rows` rows at position `pos0` takes, so that a test can name the form it runs.
  * two_term: inputs in two bf16 terms (the default pass) or in one (ST_PREFILL_FAST).  forms[0..3], the QKV, O, gate/up and
  * down projection: 0 for the general kernel, K slices << 8 | weight tiles per block << 16 for the streaming kernel, K slices << 8 |
- * 1 (full-width tiles) | 2 (half-width tiles) | 4 (left-over columns in K slices of their own) for the ring kernel.  forms[4], the attention at head_dim 128: 1 = four waves,
- * 2 = eight waves in two halves.  forms[5]: its key ranges. */
+ * 1 (full-width tiles) | 8 (three-quarter-width tiles) | 2 (half-width tiles) | 4 (left-over columns in K slices of their own) for
+ * the ring kernel.  forms[4], the attention at head_dim 128: 1 = four waves, 2 = eight waves in two halves.  forms[5]: its key ranges. */
 int st_prefill_plan_forms(const st_config *cfg, int32_t rows, int32_t pos0, int32_t two_term, int32_t *forms);
 
 /* Creates a model over caller-owned device buffers (both 256-byte aligned).  Initialises the

@@ -147,12 +147,12 @@ def st_prefill_plan_check(cfg, rows):
 
 def st_prefill_plan_forms(cfg, rows, pos0, two_term=True):
     """Kernel forms of a pass of `rows` rows at position `pos0`: for QKV, O, gate/up and down ("stream", weight tiles per block,
-    K slices), ("ring", tile widths F / H / FH, sliced tail, K slices) or None (general kernel); then the attention's waves
+    K slices), ("ring", tile widths F (256 weight rows), Q (192), H (128) or two of them, sliced tail, K slices) or None (general kernel); then the attention's waves
     per block (None at head_dim 64) and key ranges."""
     f = (C.c_int32 * 6)()
     _check(lib().st_prefill_plan_forms(C.byref(make_config(cfg)), int(rows), int(pos0), int(two_term), f))
     gemms = [None if not v else ("stream", v >> 16, v >> 8 & 255) if v >> 16 else
-             ("ring", "F" * (v & 1) + "H" * (v >> 1 & 1), bool(v & 4), v >> 8) for v in f[:4]]
+             ("ring", "F" * (v & 1) + "Q" * (v >> 3 & 1) + "H" * (v >> 1 & 1), bool(v & 4), v >> 8) for v in f[:4]]
     return gemms, {0: None, 1: 4, 2: 8}[f[4]], f[5]
 
 

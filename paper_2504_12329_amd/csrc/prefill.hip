@@ -425,12 +425,12 @@ __device__ __forceinline__ void static_for(F &&f) {  // f(ic<0>{}), ..., f(ic<N-
 // Tail (block ids from `blocks` on): the column tiles from tail_x0 on, their K range cut into tail_s slices of
 // tail_kps columns; a unit is one slice of 32 tiles (column-major) and unit u runs on XCD u % 8.
 struct RingGrid {
-    int My, Nx, x0, TY, TX, S, kps, per, blocks;  // x0: column tile of the launch's first column (in its own tiles)
+    int My, Nx, col0, TY, TX, S, kps, per, blocks;  // col0: output column the launch's tiles start from
     int h_base, h_extra;                          // heights of the row tiles (see ring_units)
     int once;                                     // every weight is read by one block, from HBM (see ring_rot)
     int tail_x0, tail_tiles, tail_s, tail_kps;
 };
-// What block `bid` of a launch works on: tile (x, y) in the launch's own tiles (x before adding x0), K range
+// What block `bid` of a launch works on: tile (x, y) in the launch's own tiles, K range
 // [kbeg, kend), and for the plain form where its fp32 tile goes: part + part_off, row stride ldp (the offset
 // already discounts the tail's first column).  False: the id has no work.  Shared by the kernel and the host-side
 // check of the numbering.
@@ -491,23 +491,28 @@ __host__ __device__ inline int ring_row0(const RingGrid &gg, int y, int unit) {
 __host__ __device__ inline int ring_rot(int x, int nk) { return (x & 7) * nk >> 3; }
 
 // The block's tile: NF activation fragments of 32 LDS rows (one term: NF * 32 rows; two terms: NF * 16 rows, the high
-// terms in the first NF / 2 fragments, the low terms in the rest) against 256 weight rows (HALF: 128).  Full height:
+// terms in the first NF / 2 fragments, the low terms in the rest) against W = 256, 192 or 128 weight rows.  Full height:
 // four multiplying waves as 2 x 2; lower tiles: as 1 x 4, every wave all activation rows against a quarter of the weight
 // rows, so that all of them get shorter with the tile (at full height 2 x 2 reads fewer fragments per MFMA: 3-4 % faster).
-// HALF: half the columns and half the MFMAs per fragment of activations, for launches that full tiles would leave
+// W = 128: half the columns and half the MFMAs per fragment of activations, for launches that full tiles would leave
 // short of blocks, and for the tiles left over after whole rounds of full tiles.
-template <int NF, bool DUAL, bool HALF, int TERMS, bool F16, bool ONCE>
+// W = 192 (fused form at full height only): where full tiles leave CUs idle and half-width ones need another round.  Gate/up of
+// the 7B shape at 97 to 128 rows is 148 full tiles or 198 of these on 256 CUs.  Four layers, without / with them: 7B 126 rows
+// 1005 / 972 us, 256 fp16 rows 1091 / 1056; 1.5B 250 and 1000 rows 580 / 561 and 1132 / 1100, 500 fp16 rows 714 / 689; behind full
+// rounds 32B 250 rows 2267 / 2180, 500 fp16 rows 2565 / 2498, 7B 1000 rows 3579 / 3557 us.
+template <int NF, bool DUAL, int W, int TERMS, bool F16, bool ONCE>
 __device__ __forceinline__ void ring_tile(unsigned char *ring, const bf16_t *__restrict__ A, const bf16_t *__restrict__ Alo,
                                           int lda, const bf16_t *__restrict__ B, int M, int N, int K, float *__restrict__ pz,
                                           int ldp, bf16_t *__restrict__ outb, bf16_t *__restrict__ outlo, int ldo, int m0,
                                           int n0, int kbeg, int nk, int rot, int out_f16) {
     static_assert(TERMS == 1 || !F16, "two terms are bf16");
     constexpr bool SPEC = TERMS == 2;  // waves 4-7 load, waves 0-3 multiply
-    constexpr int WM = NF == 8 ? 2 : 1, WN = 4 / WM, TB = HALF ? 128 : 256;
+    static_assert(W == 256 || W == 128 || (W == 192 && DUAL && NF == 8), "tile widths");
+    constexpr int WM = NF == 8 ? 2 : 1, WN = 4 / WM, TB = W;
     constexpr int NB = TB / WN / 32;   // 32-row weight fragments per wave
-    constexpr int NLA = NF, NLB = HALF ? 4 : 8;  // direct loads per loading wave for one activation / weight slot
+    constexpr int NLA = NF, NLB = W / 32;  // direct loads per loading wave for one activation / weight slot
     constexpr int NI = NF / TERMS, NIW = NI / WM;  // 32-row tiles of the block; of a wave
-    constexpr bool GU16 = HALF && DUAL && WM == 1;  // a wave's one weight fragment holds 16 gate and 16 up rows
+    constexpr bool GU16 = DUAL && NB % 2 != 0;  // every weight fragment holds 16 gate rows and the matching 16 up rows
     const int tid = threadIdx.x, lane = tid & 63, wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool loader = SPEC && wave8 >= 4;
     const int wave = wave8 & 3, wm = wave / WN, wn = wave % WN, l32 = lane & 31, kg = lane >> 5;
@@ -727,17 +732,18 @@ __device__ __forceinline__ void ring_tile(unsigned char *ring, const bf16_t *__r
         // each stores two columns of one row
         const bool up_half = l32 & 16;
 #pragma unroll
-        for (int i = 0; i < NIW; ++i)
+        for (int ij = 0; ij < NIW * NB; ++ij)
 #pragma unroll
             for (int r = 0; r < 16; r += 4) {
+                const int i = ij / NB, j = ij % NB;
                 float g[4], u[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) with_xor16(acc[i][0][r + e], g[e], u[e]);
+                for (int e = 0; e < 4; ++e) with_xor16(acc[i][j][r + e], g[e], u[e]);
                 const float v0 = silu_mul(up_half ? g[1] : g[0], up_half ? u[1] : u[0]);
                 const float v1 = silu_mul(up_half ? g[3] : g[2], up_half ? u[3] : u[2]);
                 const float other = dpp_move<0xB1, 0xf>(0.f, odd ? v0 : v1);  // quad_perm [1,0,3,2]
                 const int row = mw + i * 32 + 8 * (r >> 2) + 4 * kg + (up_half ? 1 : 0) + (odd ? 2 : 0);
-                put2(row, n0 + wn * 16 + (l32 & 14), odd ? other : v0, odd ? v1 : other);
+                put2(row, n0 + (wn * NB + j) * 16 + (l32 & 14), odd ? other : v0, odd ? v1 : other);
             }
     } else if constexpr (DUAL) {
         // Two rows at a time: neighbouring lanes (columns c, c + 1) swap one value each, so that the even lane holds
@@ -773,7 +779,7 @@ __device__ __forceinline__ void ring_tile(unsigned char *ring, const bf16_t *__r
 
 // F16: A and B hold fp16 numbers (single-term activations, the model's fp16 copy of the weights).  out_f16: the
 // fused epilogue writes fp16 (one term) instead of bf16 (+ its low term).
-template <bool DUAL, bool HALF, int TERMS, bool F16, bool ONCE>
+template <bool DUAL, int W, int TERMS, bool F16, bool ONCE>
 __global__ __launch_bounds__(TERMS == 2 ? 512 : 256) void k_gemm_ring(const bf16_t *__restrict__ A,
                                                                       const bf16_t *__restrict__ Alo, int lda,
                                                                       const bf16_t *__restrict__ B, int M, int N, int K,
@@ -784,17 +790,21 @@ __global__ __launch_bounds__(TERMS == 2 ? 512 : 256) void k_gemm_ring(const bf16
     RingBlock rb;
     if (!ring_block(gg, blockIdx.x, M, N, K, &rb)) return;
     float *pz = DUAL ? nullptr : part + rb.part_off;  // where this block's fp32 tile goes (plain form)
-    const int m0 = ring_row0(gg, rb.y, 64 / TERMS), n0 = (rb.x + gg.x0) * ((HALF ? 128 : 256) / (DUAL ? 2 : 1));
+    const int m0 = ring_row0(gg, rb.y, 64 / TERMS), n0 = gg.col0 + rb.x * (W / (DUAL ? 2 : 1));
     const int kbeg = __builtin_amdgcn_readfirstlane(rb.kbeg);  // wave-uniform: the load bases live in scalar registers
     const int nk = __builtin_amdgcn_readfirstlane((rb.kend - rb.kbeg) / kRingBK);
     const int rot = ONCE ? __builtin_amdgcn_readfirstlane(ring_rot(rb.x, nk)) : 0;
 #define ST_RING_TILE(NFV)                                                                                                  \
-    ring_tile<NFV, DUAL, HALF, TERMS, F16, ONCE>(ring, A, Alo, lda, B, M, N, K, pz, rb.ldp, outb, outlo, ldo, m0, n0, kbeg, \
+    ring_tile<NFV, DUAL, W, TERMS, F16, ONCE>(ring, A, Alo, lda, B, M, N, K, pz, rb.ldp, outb, outlo, ldo, m0, n0, kbeg, \
                                                  nk, rot, out_f16)
-    switch (__builtin_amdgcn_readfirstlane(ring_units(gg, rb.y))) {
-        case 2: ST_RING_TILE(4); break;
-        case 3: ST_RING_TILE(6); break;
-        default: ST_RING_TILE(8); break;
+    if constexpr (W == 192) {  // (only launches whose row tiles are all of full height)
+        ST_RING_TILE(8);
+    } else {
+        switch (__builtin_amdgcn_readfirstlane(ring_units(gg, rb.y))) {
+            case 2: ST_RING_TILE(4); break;
+            case 3: ST_RING_TILE(6); break;
+            default: ST_RING_TILE(8); break;
+        }
     }
 #undef ST_RING_TILE
 }
@@ -1840,11 +1850,11 @@ static void gemm_launch(const Model &m, dim3 grid, const bf16_t *A, const bf16_t
                        outlo, ldo, gg);
 }
 
-template <bool DUAL, bool HALF>
+template <bool DUAL, int W>
 static void ring_launch(const Model &m, bool f16, bool out_f16, dim3 grid, const bf16_t *A, const bf16_t *Alo, int lda,
                         const bf16_t *B, int M, int N, int K, bf16_t *outb, bf16_t *outlo, int ldo, const RingGrid &gg) {
 #define ST_RING_GO(TERMSV, F16V, ONCEV)                                                                                         \
-    hipLaunchKernelGGL((k_gemm_ring<DUAL, HALF, TERMSV, F16V, ONCEV>), grid, dim3(TERMSV == 2 ? 512 : 256), kRingLds,        \
+    hipLaunchKernelGGL((k_gemm_ring<DUAL, W, TERMSV, F16V, ONCEV>), grid, dim3(TERMSV == 2 ? 512 : 256), kRingLds,        \
                        m.stream, A, Alo, lda, B, M, N, K, m.ws.qkv, outb, outlo, ldo, gg, (int)out_f16)
 #define ST_RING_GO2(TERMSV, F16V)                       \
     if (gg.once) ST_RING_GO(TERMSV, F16V, true);        \
@@ -1874,8 +1884,9 @@ hipError_t raise_lds_limits() {
         take(raise_one(k_gemm_ring<D, H, 2, false, O>));
     take(raise_one(k_flash_long<false, false>)), take(raise_one(k_flash_long<true, false>));
     take(raise_one(k_flash_long<false, true>)), take(raise_one(k_flash_long<true, true>));
-    ST_RING_LIMIT(false, false, false) ST_RING_LIMIT(false, true, false) ST_RING_LIMIT(true, false, false) ST_RING_LIMIT(true, true, false)
-    ST_RING_LIMIT(false, false, true) ST_RING_LIMIT(false, true, true) ST_RING_LIMIT(true, false, true) ST_RING_LIMIT(true, true, true)
+    ST_RING_LIMIT(false, 256, false) ST_RING_LIMIT(false, 128, false) ST_RING_LIMIT(false, 256, true) ST_RING_LIMIT(false, 128, true)
+    ST_RING_LIMIT(true, 256, false) ST_RING_LIMIT(true, 192, false) ST_RING_LIMIT(true, 128, false)
+    ST_RING_LIMIT(true, 256, true) ST_RING_LIMIT(true, 192, true) ST_RING_LIMIT(true, 128, true)
 #undef ST_RING_LIMIT
 #define ST_STREAM_LIMIT(MT)                                                                                  \
     take(raise_one(k_gemm_stream<MT, 1, false, false>)), take(raise_one(k_gemm_stream<MT, 1, true, false>)), \
@@ -2018,9 +2029,9 @@ static bool stream_fuses(const st_config &c, int M, int I, int K, int terms) {
 // Launches of the ring kernel for one GEMM of a long chunk: tile width, K slices, leftover tiles and block numbering.
 // Pure host arithmetic (ring_plan_check walks it without a GPU).
 struct RingPlan {
-    int n;             // launches: 1, or 2 for the fused form with half-width leftover tiles
+    int n;             // launches: 1, or 2 for the fused form with narrower leftover tiles
     RingGrid g[2];
-    bool half[2];
+    int width[2];      // weight rows of its tiles: 256, 192 or 128
     int grid_x[2];
     int slices;        // full-width K slices written to the partial buffer (0 for the fused form)
     PartTail tail;     // extra slices of the tail columns
@@ -2032,9 +2043,9 @@ struct RingPlan {
 struct RingCost {
     static constexpr double kFill = 2.5, kLaunch = 2.5;
     // rows: mean height of the row tiles, out of the bm of a full one
-    static double block(bool half, bool dual, int bm, double rows, int steps) {
-        const double tile_bytes = rows * (half ? 128 : 256) * (dual ? 1 : 4);
-        return steps * (half ? 0.35 + 0.70 * rows / bm : 0.50 + 1.20 * rows / bm) + kFill + tile_bytes / 58e3;
+    static double block(int width, bool dual, int bm, double rows, int steps) {
+        const double tile_bytes = rows * width * (dual ? 1 : 4), h = rows / bm;
+        return steps * (width == 128 ? 0.35 + 0.70 * h : width == 192 ? 0.43 + 0.95 * h : 0.50 + 1.20 * h) + kFill + tile_bytes / 58e3;
     }
     static double rounds(long blocks) { return (double)((blocks + 255) / 256); }
     static double slices(int s, int M, int N) { return (double)s * M * N * 8 / 4e6; }
@@ -2052,49 +2063,56 @@ static RingPlan ring_plan(bool dual, bool two_term, int M, int N, int K, size_t 
     gg.TY = 1;
     while (gg.TY * 2 <= gg.My && gg.TY < 8) gg.TY *= 2;
     gg.TX = 32 / gg.TY;
-    gg.S = 1, gg.kps = K, gg.x0 = 0;
+    gg.S = 1, gg.kps = K, gg.col0 = 0;
     gg.once = gg.My == 1 && (size_t)N * K * (dual ? 4 : 2) >= kStreamOnceBytes;
     gg.tail_x0 = gg.tail_tiles = 0, gg.tail_s = 1, gg.tail_kps = K;
-    const int width = dual ? 128 : 256;                          // output columns of a full tile
-    const int nx = (N + width - 1) / width, nxh = (N + width / 2 - 1) / (width / 2);
-    const long tiles = (long)gg.My * nx, tiles_h = (long)gg.My * nxh;
-    bool half = false;
+    const int nx = (N + (dual ? 127 : 255)) / (dual ? 128 : 256);  // column tiles of full width
+    const long tiles = (long)gg.My * nx;
+    int width = 256;
     p.n = 1;
     if (dual) {
-        // Full tiles only, half-width tiles only, or whole rounds of 256 full tiles and the column tiles left over as
-        // half-width tiles in a launch of their own: twice the blocks at half the length each, so the last round
-        // keeps every CU busy for half a round instead of half the CUs for a whole one.
-        double best = RingCost::rounds(tiles) * RingCost::block(false, true, bm, rows, nk);
-        const double all_half = RingCost::rounds(tiles_h) * RingCost::block(true, true, bm, rows, nk);
-        gg.Nx = nx;
-        if (all_half < best) best = all_half, half = true, gg.Nx = nxh;
-        const int nx_main = (int)(tiles / 256 * 256 / gg.My);
-        if (tiles > 256 && nx_main < nx) {
-            const int left_h = nxh - 2 * nx_main;  // half-width columns (a ragged last one included)
-            const double split = RingCost::rounds((long)nx_main * gg.My) * RingCost::block(false, true, bm, rows, nk) +
-                                 RingCost::rounds((long)left_h * gg.My) * RingCost::block(true, true, bm, rows, nk) + RingCost::kLaunch;
-            if (split < best) {
-                RingGrid th = gg;
-                th.Nx = left_h, th.x0 = 2 * nx_main;
-                th.per = (th.My * th.Nx + 7) / 8, th.blocks = 8 * th.per;
-                gg.Nx = nx_main, half = false;
-                p.n = 2, p.g[1] = th, p.half[1] = true, p.grid_x[1] = th.blocks;
-            }
+        // Tiles of one width, or whole rounds of 256 full tiles and the columns left over as narrower tiles in a launch of their
+        // own: more blocks of less length each, so that the last round keeps every CU busy for part of a round instead of part
+        // of the CUs for a whole one.  192 rows need row tiles of full
+        // height, and are taken alone up to eight of them (1024 rows of two terms, 2048 of one: the longest passes timed so).
+        auto cols = [&](int w, int left) { return (left + w / 2 - 1) / (w / 2); };
+        auto cost = [&](int w, long blocks) { return RingCost::rounds(blocks) * RingCost::block(w, true, bm, rows, nk); };
+        const bool full_height = units == 4 * gg.My;
+        double best = -1;
+        for (int w = 256; w >= 128; w -= 64) {
+            if (w == 192 && (!full_height || gg.My > 8)) continue;
+            const double c = cost(w, (long)gg.My * cols(w, N));
+            if (best < 0 || c < best) best = c, width = w, gg.Nx = cols(w, N);
         }
+        const int nx_main = (int)(tiles / 256 * 256 / gg.My);
+        if (tiles > 256 && nx_main < nx)
+            for (int w = 192; w >= 128; w -= 64) {
+                if (w == 192 && !full_height) continue;
+                const int left = cols(w, N - nx_main * 128);
+                const double c = cost(256, (long)nx_main * gg.My) + cost(w, (long)left * gg.My) + RingCost::kLaunch;
+                if (c >= best) continue;
+                best = c;
+                RingGrid th = gg;
+                th.Nx = left, th.col0 = nx_main * 128;
+                th.per = (th.My * th.Nx + 7) / 8, th.blocks = 8 * th.per;
+                gg.Nx = nx_main, width = 256;
+                p.n = 2, p.g[1] = th, p.width[1] = w, p.grid_x[1] = th.blocks;
+            }
     } else {
         double best = -1;
         const int max_s = M <= 512 ? 16 : 8;
+        const int nxh = (N + 127) / 128;
         for (int h = 0; h < 2; ++h)
             for (int s = 1; s <= max_s; ++s) {
                 const int steps = (nk + s - 1) / s;
                 if (s > 1 && (steps < 3 || (size_t)s * M * N > cap)) break;
                 const int used = (nk + steps - 1) / steps;
                 if (used != s || nk - (s - 1) * steps < 2) continue;  // the last slice needs two steps
-                const double cost = RingCost::rounds((h ? tiles_h : tiles) * s) * RingCost::block(h, false, bm, rows, steps) +
+                const double cost = RingCost::rounds((h ? (long)gg.My * nxh : tiles) * s) * RingCost::block(h ? 128 : 256, false, bm, rows, steps) +
                                     RingCost::slices(s, M, N);
-                if (best < 0 || cost < best) best = cost, gg.S = s, half = h;
+                if (best < 0 || cost < best) best = cost, gg.S = s, width = h ? 128 : 256;
             }
-        gg.Nx = half ? nxh : nx;
+        gg.Nx = width == 128 ? nxh : nx;
         gg.kps = (nk + gg.S - 1) / gg.S * kRingBK;
         // Or: whole rounds of 256 full tiles at full K, and only the column tiles left over cut into K slices (a
         // consumer that takes a PartTail adds their extra slices).  320 tiles with K = 432 steps: three rounds of
@@ -2108,14 +2126,14 @@ static RingPlan ring_plan(bool dual, bool two_term, int M, int N, int K, size_t 
                 const int steps = (nk + s - 1) / s;
                 if (s > 1 && (steps < 4 || nk - (s - 1) * steps < 2)) break;
                 if ((size_t)M * N + (size_t)(s - 1) * M * ld > cap) break;
-                const double cost = RingCost::rounds((long)tail_tiles * s) * RingCost::block(false, false, bm, rows, steps) +
+                const double cost = RingCost::rounds((long)tail_tiles * s) * RingCost::block(256, false, bm, rows, steps) +
                                     RingCost::slices(s - 1, M, ld);
                 if (tbest < 0 || cost < tbest) tbest = cost, ts = s;
             }
-            const double cost = RingCost::rounds((long)nx_main * gg.My) * RingCost::block(false, false, bm, rows, nk) + tbest +
+            const double cost = RingCost::rounds((long)nx_main * gg.My) * RingCost::block(256, false, bm, rows, nk) + tbest +
                                 RingCost::slices(1, M, N);
             if (cost < best) {
-                half = false;
+                width = 256;
                 gg.tail_x0 = nx_main, gg.tail_tiles = tail_tiles, gg.tail_s = ts;
                 gg.tail_kps = (nk + ts - 1) / ts * kRingBK;
                 gg.Nx = nx_main, gg.S = 1, gg.kps = K;  // the main part: the first nx_main column tiles at full K
@@ -2127,7 +2145,7 @@ static RingPlan ring_plan(bool dual, bool two_term, int M, int N, int K, size_t 
     gg.per = (gg.S * gg.My * gg.Nx + 7) / 8;
     gg.blocks = 8 * gg.per;
     const int tail_units = (gg.tail_tiles + 31) / 32 * gg.tail_s;
-    p.g[0] = gg, p.half[0] = half, p.grid_x[0] = gg.blocks + (tail_units + 7) / 8 * 256;
+    p.g[0] = gg, p.width[0] = width, p.grid_x[0] = gg.blocks + (tail_units + 7) / 8 * 256;
     return p;
 }
 
@@ -2138,10 +2156,12 @@ static int ring_gemm(const Model &m, bool f16, bool out_f16, const bf16_t *A, co
     const RingPlan p = ring_plan(DUAL, Alo != nullptr, M, N, K, partial_floats(m.c), tail != nullptr);
     for (int l = 0; l < p.n; ++l) {
         const dim3 grid(p.grid_x[l]);
-        if (p.half[l])
-            ring_launch<DUAL, true>(m, f16, out_f16, grid, A, Alo, lda, B, M, N, K, outb, outlo, ldo, p.g[l]);
+        if (p.width[l] == 128)
+            ring_launch<DUAL, 128>(m, f16, out_f16, grid, A, Alo, lda, B, M, N, K, outb, outlo, ldo, p.g[l]);
+        else if (DUAL && p.width[l] == 192)
+            ring_launch<DUAL, DUAL ? 192 : 256>(m, f16, out_f16, grid, A, Alo, lda, B, M, N, K, outb, outlo, ldo, p.g[l]);
         else
-            ring_launch<DUAL, false>(m, f16, out_f16, grid, A, Alo, lda, B, M, N, K, outb, outlo, ldo, p.g[l]);
+            ring_launch<DUAL, 256>(m, f16, out_f16, grid, A, Alo, lda, B, M, N, K, outb, outlo, ldo, p.g[l]);
     }
     if (tail) *tail = p.tail;
     return p.slices;
@@ -2155,20 +2175,21 @@ int ring_plan_check(int dual, int two_term, int M, int N, int K, long long cap_f
     if (M <= 0 || N <= 0 || K < 2 * kRingBK || K % kRingBK) return -1;
     const RingPlan p = ring_plan(dual != 0, two_term != 0, M, N, K, (size_t)cap_floats, allow_tail != 0);
     const int unit = ring_unit(two_term != 0), nk = K / kRingBK, my = p.g[0].My;
-    const int out_cols = dual ? 64 : 128;  // count output columns in units every tile width is a multiple of
+    const int out_cols = dual ? 32 : 128;  // count output columns in units every tile width is a multiple of
     const int ncu = (N + out_cols - 1) / out_cols;
     std::vector<unsigned char> seen((size_t)my * ncu * nk, 0);
     int working = 0, ids = 0;
     for (int l = 0; l < p.n; ++l) {
-        const int width = (p.half[l] ? 128 : 256) / (dual ? 2 : 1), per_tile = width / out_cols;
+        const int width = p.width[l] / (dual ? 2 : 1), per_tile = width / out_cols;
         ids += p.grid_x[l];
         for (int bid = 0; bid < p.grid_x[l]; ++bid) {
             RingBlock rb;
             if (!ring_block(p.g[l], bid, M, N, K, &rb)) continue;
             ++working;
-            const int n0 = (rb.x + p.g[l].x0) * width;
+            const int n0 = p.g[l].col0 + rb.x * width;
             const int units = ring_units(p.g[l], rb.y), r0 = ring_row0(p.g[l], rb.y, unit);
             if (rb.y < 0 || rb.y >= my || n0 < 0 || n0 >= N || units < 2 || units > 4 || r0 >= M) return -2;
+            if (n0 % out_cols || (p.width[l] == 192 && units != 4)) return -2;
             if (rb.y == my - 1 && r0 + units * unit < M) return -2;  // the last row tile ends at or past the last row
             if (rb.kbeg < 0 || rb.kend > K || (rb.kend - rb.kbeg) % kRingBK || rb.kend - rb.kbeg < 2 * kRingBK) return -3;
             for (int c = 0; c < per_tile; ++c) {
@@ -2451,7 +2472,7 @@ void prefill_plan_forms(const st_config &c, int rows, int pos0, bool two_term, i
         }
         if (g[i].K < 2 * kRingBK) continue;
         const RingPlan p = ring_plan(g[i].dual, two_term, rows, g[i].N, g[i].K, partial_floats(c), !g[i].dual);
-        for (int l = 0; l < p.n; ++l) forms[i] |= p.half[l] ? 2 : 1;
+        for (int l = 0; l < p.n; ++l) forms[i] |= p.width[l] == 128 ? 2 : p.width[l] == 192 ? 8 : 1;
         forms[i] |= (p.tail.n > 0 ? 4 : 0) | p.slices << 8;
     }
     const FlashPlan f = flash_plan(c, two_term && c.head_dim == 128, rows, (rows * G + 127) / 128,

@@ -103,11 +103,25 @@ def test_full_width_tiles_below_full_height(name, m, mode, widths):
 
 
 @pytest.mark.parametrize("name,m,mode,widths", [
-    ("qwen7b", 97, "default", "H H F H"), ("qwen32b", 128, "default", "H H F F"), ("qwen1p5b", 110, "default", "H H H H"),
-    ("qwen32b", 161, "f16", "F H F F"), ("qwen7b", 250, "f16", "H H F H"), ("qwen32b", 193, "fast", "H H F F")])
+    ("qwen7b", 97, "default", "H H Q H"), ("qwen32b", 128, "default", "H H F F"), ("qwen1p5b", 110, "default", "H H H H"),
+    ("qwen32b", 161, "f16", "F H F F"), ("qwen7b", 250, "f16", "H H Q H"), ("qwen32b", 193, "fast", "H H F F")])
 def test_one_row_tile_with_weights_larger_than_the_l2(name, m, mode, widths):
     """Passes of one row tile: matrices above 40 MB (gate/up of every shape, down of the 7B and all of the 32B shape) are read
     round the end of their K range from eight starting steps; K slices of unequal lengths among them."""
+    test_full_width_tiles_below_full_height(name, m, mode, widths)
+
+
+@pytest.mark.parametrize("name,m,mode,widths", [
+    ("qwen1p5b", 250, "default", "H H Q H"),
+    ("qwen1p5b", 500, "f16", "H H Q H"),
+    ("qwen1p5b", 512, "default", "H H Q H"),
+    ("qwen7b", 380, "default", "H H FQ F"),
+    ("qwen32b", 250, "default", "H H FQ F"),
+    ("qwen32b", 460, "fast", "H H FQ F"),
+    ("qwen7b", 193, "f16", "H H Q H")])
+def test_gate_up_tiles_of_192_weight_rows(name, m, mode, widths):
+    """Gate/up in tiles of 96 output columns, alone and behind whole rounds of full tiles, one to four row tiles, each operand form
+    (8960 columns: the last tile has 32)."""
     test_full_width_tiles_below_full_height(name, m, mode, widths)
 
 
