@@ -2039,7 +2039,8 @@ struct RingPlan {
 
 // One block per CU at a time, so a launch takes (rounds of 256 blocks) x (K steps per block x the time of a step + what
 // a block spends filling its ring and storing its tile); the fp32 slices of the plain form are written once and read
-// again by the consumer.  Microseconds; a step of a full tile measured 1.7, of a half-width one 0.97-1.1.
+// again by the consumer.  Microseconds; a step of a full tile measured 1.7, of one of 192 weight
+// rows 1.25-1.4, of a half-width one 0.97-1.1.
 struct RingCost {
     static constexpr double kFill = 2.5, kLaunch = 2.5;
     // rows: mean height of the row tiles, out of the bm of a full one
