@@ -36,39 +36,40 @@ __device__ __forceinline__ int wave_running_max(int v) {
     return dpp_max<0x143, 0xc>(v);  // row_bcast31 into rows 2 and 3
 }
 
-// A thread owns eight consecutive positions of an 8192-token tile: one block's chain of tiles is bound by the latency of a
+// A thread owns PER consecutive positions of a tile of 1024 * PER: one block's chain of tiles is bound by the latency of a
 // tile (token load, bitmap look-ups, two barriers) and by the look-ups, random 4-byte reads that a CU serves one lane a clock.
 // STAGED: both bitmaps are copied to LDS first, beside the token load (a vocabulary of 152 k ids takes 19 KB each), and looked
-// up there.  4608 / 18000 tokens, kernel alone: one position per thread 14.4 / 47.2 us, four 9.3 / 24.7, eight with the bitmaps in LDS
-// 7.7 / 18.4 (300 tokens: 4.1 with four, 5.4 now, which the call does not show: its 22 us are launch and wait).
-constexpr int kScanPer = 8, kScanTile = 1024 * kScanPer;
+// up there.  scan_form says which scan takes which form, and why.
 constexpr size_t kScanLds = 60 << 10;  // with the kernel's own arrays below the 64 KB every kernel may use
 
-template <bool STAGED>
+template <int PER, bool STAGED>
 __global__ __launch_bounds__(1024) void k_trigger_scan(const int32_t *__restrict__ tokens, int lo, int hi,
                                                        const uint32_t *kw, const uint32_t *delim, int window, int vocab,
                                                        int32_t *__restrict__ positions, int cap,
                                                        int32_t *__restrict__ n_found) {
+    constexpr int kTile = 1024 * PER, kBits = PER == 8 ? 4 : 3;  // bits of a count of 0 .. PER
+    static_assert(PER == 4 || PER == 8, "bits of a thread's count");
     __shared__ int wave_d[16], wave_k[16], wave_n[16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int w = window - 1;
     const int scan_from = w == 0 ? lo : max(0, lo - w);
     int carry_d = -1, carry_k = -1, base = 0;  // the same in every thread
-    auto fetch = [&](int start, int (&id)[kScanPer]) {
+    auto fetch = [&](int start, int (&id)[PER]) {
 #pragma unroll
-        for (int e = 0; e < kScanPer; ++e) {
-            const uint32_t p = (uint32_t)start + threadIdx.x * kScanPer + e;  // (a tile may end past 2^31)
+        for (int e = 0; e < PER; ++e) {
+            const uint32_t p = (uint32_t)start + threadIdx.x * PER + e;  // (a tile may end past 2^31)
             id[e] = p < (uint32_t)hi ? tokens[p] : -1;  // -1 belongs to no set
         }
     };
-    int id[kScanPer];
+    int id[PER];
     if (scan_from < hi) fetch(scan_from, id);
     extern __shared__ __align__(16) uint32_t bitmaps[];
     if constexpr (STAGED) {
         const int words = (vocab + 31) >> 5, pad = (words + 3) & ~3;
         auto stage = [&](const uint32_t *src, uint32_t *dst) {
             const int n4 = ((uintptr_t)src & 15) == 0 ? words >> 2 : 0;
-            for (int i = threadIdx.x; i < n4; i += 1024) reinterpret_cast<u32x4 *>(dst)[i] = reinterpret_cast<const u32x4 *>(src)[i];
+            for (int i = threadIdx.x; i < n4; i += 1024)
+                reinterpret_cast<u32x4 *>(dst)[i] = reinterpret_cast<const u32x4 *>(src)[i];
             for (int i = 4 * n4 + threadIdx.x; i < words; i += 1024) dst[i] = src[i];
         };
         stage(kw, bitmaps);
@@ -79,17 +80,17 @@ __global__ __launch_bounds__(1024) void k_trigger_scan(const int32_t *__restrict
         }
         __syncthreads();
     }
-    for (long start = scan_from; start < hi; start += kScanTile) {
-        const uint32_t p0 = (uint32_t)start + threadIdx.x * kScanPer;  // positions past `hi` hold no token and never fire
-        bool is_k[kScanPer], is_d[kScanPer];
+    for (long start = scan_from; start < hi; start += kTile) {
+        const uint32_t p0 = (uint32_t)start + threadIdx.x * PER;  // positions past `hi` hold no token and never fire
+        bool is_k[PER], is_d[PER];
         int own_d = -1, own_k = -1;
 #pragma unroll
-        for (int e = 0; e < kScanPer; ++e) {
+        for (int e = 0; e < PER; ++e) {
             is_k[e] = in_set(kw, id[e], vocab), is_d[e] = w > 0 && in_set(delim, id[e], vocab);
             if (is_d[e]) own_d = (int)(p0 + e);
             if (is_k[e]) own_k = (int)(p0 + e);
         }
-        if (start + kScanTile < hi) fetch((int)start + kScanTile, id);  // under this tile's reductions
+        if (start + kTile < hi) fetch((int)start + kTile, id);  // under this tile's reductions
         const int run_d = wave_running_max(own_d), run_k = wave_running_max(own_k);
         int last_d = __shfl_up(run_d, 1, kWave), last_k = __shfl_up(run_k, 1, kWave);  // of the lanes before this one
         if (lane == 0) last_d = last_k = -1;
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(1024) void k_trigger_scan(const int32_t *__restrict
         carry_d = all_d, carry_k = all_k;
         unsigned fire = 0;
 #pragma unroll
-        for (int e = 0; e < kScanPer; ++e) {
+        for (int e = 0; e < PER; ++e) {
             const int p = (int)(p0 + e);  // below `lo` if it has wrapped
             if (is_k[e]) last_k = p;
             // here last_d is the last delimiter before p, last_k the last keyword up to p
@@ -112,11 +113,11 @@ __global__ __launch_bounds__(1024) void k_trigger_scan(const int32_t *__restrict
             fire |= (unsigned)f << e;
             if (is_d[e]) last_d = p;
         }
-        const int cnt = __popc(fire);  // 0 .. 8: its four bits are summed over the lower lanes by ballots
+        const int cnt = __popc(fire);  // its bits are summed over the lower lanes by ballots
         const unsigned long long below = (1ull << lane) - 1ull;
         int off = 0, wave_total = 0;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
+        for (int b = 0; b < kBits; ++b) {
             const unsigned long long m = __ballot(cnt >> b & 1);
             off += __popcll(m & below) << b, wave_total += __popcll(m) << b;
         }
@@ -130,7 +131,7 @@ __global__ __launch_bounds__(1024) void k_trigger_scan(const int32_t *__restrict
         }
         base = all_n;
 #pragma unroll
-        for (int e = 0; e < kScanPer; ++e)
+        for (int e = 0; e < PER; ++e)
             if (fire >> e & 1u) {
                 if (off < cap) positions[off] = (int)(p0 + e);
                 ++off;
@@ -162,15 +163,40 @@ int deliver_scan(const int32_t *dev, int32_t range, int32_t *positions, int32_t 
     return ST_OK;
 }
 
+// The form of a scan that walks n positions with bitmaps of `lds` bytes.  Kernel alone, us, delimiter rule at 152 k ids (38 KB):
+//   positions           1000   4000   4097   5000   6000   8000   9000  12289  14000  18000  24000  30000
+//   4, not staged        4.5    6.0    8.1    8.7    8.9   10.1   13.0   16.9   17.8   22.2   27.8   35.5
+//   8, not staged        6.0    7.4    7.4    8.2    9.1   11.1   15.9   17.6   19.2   25.6   29.3   36.7
+//   4, staged            4.5    5.5    7.7    7.7    7.8    8.2   10.5   13.2   13.3   16.2   19.4   24.6
+//   8, staged            5.5    6.9    7.0    7.5    8.0    9.0   12.3   12.9   13.2   17.7   19.6   23.8
+// (4.2 is the rate of launches.)  So: one tile of four positions a thread unstaged, as short a kernel as there is; longer scans
+// four and staged; eight where they save the last tile of four and that one is short (unstaged only the second tile is worth
+// their slower look-ups), and in chains so long that whole tiles count.
+struct ScanForm {
+    int per;
+    bool staged;
+};
+static ScanForm scan_form(long n, size_t lds) {
+    const bool staged = n > 4096 && lds <= kScanLds;
+    const long last = (n - 1) % 8192 + 1;  // positions of the last tile at eight a thread
+    const bool saves = last > 4096 && last <= (n > 8192 ? 6144 : 5632);
+    const bool wide = staged ? saves || n > 24576 : saves && n <= 8192;
+    return {wide ? 8 : 4, staged};
+}
+
 void launch_trigger_scan(const st_trigger_rule &rule, const int32_t *tokens, int32_t lo, int32_t hi,
                          int32_t *positions, int32_t cap, int32_t *n_found, hipStream_t stream) {
-    const size_t lds = (size_t)(((rule.vocab + 31ll) / 32 + 3) & ~3ll) * sizeof(uint32_t) * (rule.window > 1 ? 2 : 1);
-    if (lds <= kScanLds)
-        hipLaunchKernelGGL(k_trigger_scan<true>, dim3(1), dim3(1024), lds, stream, tokens, lo, hi, rule.kw_bitmap,
-                           rule.delim_bitmap, rule.window, rule.vocab, positions, cap, n_found);
-    else
-        hipLaunchKernelGGL(k_trigger_scan<false>, dim3(1), dim3(1024), 0, stream, tokens, lo, hi, rule.kw_bitmap,
-                           rule.delim_bitmap, rule.window, rule.vocab, positions, cap, n_found);
+    const int w = rule.window - 1;
+    const size_t lds = (size_t)(((rule.vocab + 31ll) / 32 + 3) & ~3ll) * sizeof(uint32_t) * (w > 0 ? 2 : 1);
+    const ScanForm f = scan_form((long)hi - (lo > w ? lo - w : 0), lds);
+#define ST_SCAN(PERV, STAGEDV)                                                                                             \
+    hipLaunchKernelGGL((k_trigger_scan<PERV, STAGEDV>), dim3(1), dim3(1024), STAGEDV ? lds : 0, stream, tokens, lo, hi,    \
+                       rule.kw_bitmap, rule.delim_bitmap, rule.window, rule.vocab, positions, cap, n_found)
+    if (f.per == 8 && f.staged) ST_SCAN(8, true);
+    else if (f.per == 8) ST_SCAN(8, false);
+    else if (f.staged) ST_SCAN(4, true);
+    else ST_SCAN(4, false);
+#undef ST_SCAN
 }
 
 // ---------------------------------------------------------------------------------------

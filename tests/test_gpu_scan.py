@@ -65,7 +65,7 @@ def test_scan_ends_at_the_last_position(window):
 
 @pytest.mark.parametrize("vocab,window", [(33, 1), (151936, 2), (245760, 21), (245792, 2), (491520, 1), (600001, 1), (600001, 3)])
 def test_scan_tiles_of_8192_with_bitmaps_staged_or_not(vocab, window):
-    """Eight positions per thread, 8192 to a tile; bitmaps of up to 60 KB together are looked up in LDS, larger ones in global
+    """Ranges around 8192 and 16384 positions; bitmaps of up to 60 KB together are looked up in LDS, larger ones in global
     memory, also from addresses that are not 16-byte aligned."""
     rng = np.random.Generator(np.random.PCG64(vocab + window))
     toks = rng.integers(-2, vocab + 2, size=16500, dtype=np.int32)
@@ -84,5 +84,26 @@ def test_scan_tiles_of_8192_with_bitmaps_staged_or_not(vocab, window):
             want = _rule_written_out(toks.tolist(), kw, dl, lo, hi, window)
             n, pos = B.st_trigger_scan(rule, dev, lo, hi, 16500)
             assert n == len(want) and pos.tolist() == want
+            n, pos = B.st_trigger_scan_static(rule, dev, lo, hi, 4096)
+            assert n == len(want) and pos.tolist() == want[:4096]
+
+
+@pytest.mark.parametrize("vocab", [64, 151936, 600001])
+@pytest.mark.parametrize("window", [1, 3])
+def test_scan_lengths_at_which_the_form_changes(vocab, window):
+    """Four and eight positions a thread, bitmaps in LDS (not up to 4096 positions, nor for 600 001 ids) or not: the lengths on both
+    sides of each change, from the first position and from a later one."""
+    rng = np.random.Generator(np.random.PCG64(vocab + window))
+    toks = rng.integers(-2, vocab + 2, size=29000, dtype=np.int32)
+    kw, dl = set(range(0, vocab, 2)), set(range(3, vocab, 7))
+    rule = B.TriggerRule(vocab, B.host_bitmap(vocab, kw), B.host_bitmap(vocab, dl) if window > 1 else None, window)
+    dev = torch.from_numpy(toks).cuda()
+    for lo in (0, 3001):
+        for walked in (4096, 4097, 5632, 5633, 8193, 12288, 12289, 14336, 14337, 24576, 24577):
+            hi = lo + walked - (window - 1 if lo else 0)
+            print(f"scan [{lo}, {hi}) vocab {vocab} window {window}", flush=True)
+            want = _rule_written_out(toks.tolist(), kw, dl, lo, hi, window)
+            n, pos = B.st_trigger_scan(rule, dev, lo, hi, 29000)
+            assert want and n == len(want) and pos.tolist() == want
             n, pos = B.st_trigger_scan_static(rule, dev, lo, hi, 4096)
             assert n == len(want) and pos.tolist() == want[:4096]
