@@ -227,7 +227,10 @@ static int scan_stage(ScanStage *out) {
         const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
         void *host = nullptr, *p = nullptr;
         e = hipHostMalloc(&host, sizeof(scratch), hipHostMallocDefault);
-        if (e == hipSuccess) e = hipHostGetDevicePointer(&p, host, 0);
+        if (e == hipSuccess) {
+            e = hipHostGetDevicePointer(&p, host, 0);
+            if (e != hipSuccess || !p) (void)hipHostFree(host), p = nullptr;
+        }
         if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
         if (e == hipSuccess && p) {
             st.dev = static_cast<int32_t *>(p), st.host = static_cast<int32_t *>(host);

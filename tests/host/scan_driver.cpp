@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "../../include/st.h"
@@ -14,6 +15,13 @@
 static int g_device = 0;
 static size_t g_lds = 0;  // dynamic LDS of the last launch
 static int g_launches = 0, g_copies = 0;
+// pinned memory: what the next allocation does, and the blocks held
+enum Pinned { kWorks, kNoMemory, kNoAddress, kNullAddress };
+static Pinned g_pinned = kWorks;
+static int g_allocated = 0, g_held = 0;
+static hipStreamCaptureMode g_mode = hipStreamCaptureModeGlobal;
+static bool g_strict = false;  // an allocation or a release came under another capture mode than the relaxed one
+alignas(256) static int32_t g_symbol[1 + ST_SCAN_STATIC_MAX_CAP];  // the library's static device array
 
 extern "C" {
 hipError_t hipGetDevice(int *d) { return *d = g_device, hipSuccess; }
@@ -22,6 +30,22 @@ hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t) {
     return ++g_copies, memcpy(dst, src, n), hipSuccess;
 }
+
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *m) { return std::swap(*m, g_mode), hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
+    g_strict |= g_mode != hipStreamCaptureModeRelaxed;
+    if (g_pinned == kNoMemory) return hipErrorOutOfMemory;
+    return ++g_allocated, ++g_held, *p = malloc(n), hipSuccess;
+}
+hipError_t hipHostFree(void *p) {
+    g_strict |= g_mode != hipStreamCaptureModeRelaxed;
+    return --g_held, free(p), hipSuccess;
+}
+hipError_t hipHostGetDevicePointer(void **dev, void *host, unsigned) {
+    if (g_pinned == kNoAddress) return hipErrorInvalidValue;
+    return *dev = g_pinned == kNullAddress ? nullptr : host, hipSuccess;
+}
+hipError_t hipGetSymbolAddress(void **p, const void *) { return *p = g_symbol, hipSuccess; }
 
 // What a launch would be: stored by the call that the compiler puts in front of a kernel's stub, read back by the stub.
 static dim3 g_grid, g_block;
@@ -92,8 +116,34 @@ static int short_scans_copy_no_bitmaps() {
     return 0;
 }
 
+// st_trigger_scan_static on four GPUs, on three of which its pinned staging cannot be had: one block at most is held for each,
+// later calls allocate nothing, and the device array in its place delivers the same, below and above what one copy brings back.
+static int staging_with_and_without_pinned_memory() {
+    const int n = 9000, vocab = 1000;
+    std::vector<int32_t> toks(n);
+    for (int i = 0; i < n; ++i) toks[i] = i * 7 % vocab;
+    const auto kw = every(2, vocab);
+    const st_trigger_rule rule = {kw.data(), nullptr, 1, vocab};
+    for (Pinned how : {kWorks, kNoMemory, kNoAddress, kNullAddress}) {
+        g_device = how, g_pinned = how, g_allocated = g_held = g_copies = 0;
+        for (int hi : {9000, 300, 3000, 0})
+            for (int cap : {4096, 1024, 5, 0}) {
+                std::vector<int32_t> pos(cap + 1, -7);
+                int32_t found = -1;
+                CHECK(st_trigger_scan_static(&rule, toks.data(), 0, hi, pos.data(), cap, &found, nullptr) == ST_OK);
+                int32_t k = 0;
+                for (int p = 0; p < hi; ++p)
+                    if (toks[p] % 2 == 0 && k++ < cap) CHECK(pos[k - 1] == p);
+                CHECK(found == k && pos[k < cap ? k : cap] == -7);
+                CHECK(g_allocated <= 1 && g_held == (how == kWorks) && (g_copies == 0) == (how == kWorks));
+            }
+        CHECK(!g_strict && g_mode == hipStreamCaptureModeGlobal);
+    }
+    return g_device = 0;
+}
+
 int main() {
-    if (short_scans_copy_no_bitmaps()) return 1;
+    if (short_scans_copy_no_bitmaps() || staging_with_and_without_pinned_memory()) return 1;
     std::printf("ok\n");
     return 0;
 }

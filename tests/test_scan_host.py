@@ -12,7 +12,8 @@ PKG = os.path.join(ROOT, "paper_2504_12329_amd")
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
 def test_scans_against_a_runtime_of_our_own(tmp_path):
-    """Scans of up to one tile of positions are launched without LDS for bitmaps."""
+    """Scans of up to one tile of positions are launched without LDS for bitmaps; the static variant where pinned memory cannot be
+    allocated, or has no address on the device."""
     if not os.path.exists(os.path.join(PKG, "libst.so")):
         from paper_2504_12329_amd import build
         build.build()
