@@ -171,3 +171,34 @@ def test_fused_gate_up_with_a_ragged_last_tile(I, m):
     print_case("worst row", worst)
     assert worst <= ROW_TOL["default"]
     g.close()
+
+
+@pytest.mark.parametrize("name,m,mode", [
+    ("qwen7b", 20, "f16"), ("qwen7b", 64, "f16"), ("qwen7b", 96, "f16"), ("qwen7b", 97, "f16"), ("qwen7b", 128, "f16"),
+    ("qwen7b", 129, "f16"), ("qwen7b", 160, "f16"), ("qwen32b", 150, "f16"), ("qwen7b", 129, "fast"), ("qwen7b", 160, "fast")])
+def test_fused_gate_up_with_one_activation_term(name, m, mode):
+    """The streaming gate/up with its SwiGLU in the epilogue at one to five activation tiles of one term, one K slice of 56 or 80
+    stages (its rings go round many times): two layers, the second layer's K/V rows of one pass against passes of 48 rows in two
+    terms."""
+    print_case(f"{name} shape, 2 layers: one pass of {m} rows ({mode}) against passes of 48")
+    cfg = synth.model_config(name, max_seq=256, max_chunk=256, n_layers=2)
+    cfg["vocab"] = 2048
+    form = B.st_prefill_plan_forms(cfg, m, 0, False)[0][2]
+    assert form[0] == "stream" and form[2] == 1
+    g = B.Model(cfg, synth.make_weights(cfg, 31, device="cuda"))
+    if mode == "f16":
+        g.attach_f16()
+    toks = synth.make_prompt(m, cfg["vocab"], 32)
+    g.prefill(toks, want_logits=False, fast=mode == "fast")
+    kv = g.kv.view(torch.bfloat16).view(2, 2, cfg["n_kv_heads"], 256, 128)[:, 1, :, :m]
+    one = kv.float().clone()
+    g.truncate(0)
+    if mode == "f16":
+        g.attach_f16(False)
+    for a in range(0, m, 48):
+        g.prefill(toks[a:a + 48], want_logits=False)
+    ref = kv.float()
+    worst = float(((one - ref).norm(dim=-1) / ref.norm(dim=-1)).max())
+    print_case("worst row", worst)
+    assert worst <= ROW_TOL[mode]
+    g.close()
