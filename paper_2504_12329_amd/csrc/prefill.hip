@@ -489,6 +489,11 @@ __host__ __device__ inline int ring_row0(const RingGrid &gg, int y, int unit) {
 // 1612), 128 rows at 1.5B 480 / 460 / 460.  Smaller matrices the same way: 100 to 256 rows at 1.5B 2-4 % slower than without.
 // Two row tiles and more share their weights in L2: 400 fp16 rows at 32B 2471 -> 2555 us with it.
 __host__ __device__ inline int ring_rot(int x, int nk) { return (x & 7) * nk >> 3; }
+// Height of a single row tile in the shortest pass of the ring kernel, in units: no launch with `once` has a lower one.
+constexpr int ring_unit(bool two_term) { return two_term ? 32 : 64; }
+constexpr int ring_once_units(bool two_term) {
+    return ((two_term ? kRingMinRows : kRingMinRowsFast) + ring_unit(two_term) - 1) / ring_unit(two_term);
+}
 
 // The block's tile: NF activation fragments of 32 LDS rows (one term: NF * 32 rows; two terms: NF * 16 rows, the high
 // terms in the first NF / 2 fragments, the low terms in the rest) against W = 256, 192 or 128 weight rows.  Full height:
@@ -797,14 +802,15 @@ __global__ __launch_bounds__(TERMS == 2 ? 512 : 256) void k_gemm_ring(const bf16
 #define ST_RING_TILE(NFV)                                                                                                  \
     ring_tile<NFV, DUAL, W, TERMS, F16, ONCE>(ring, A, Alo, lda, B, M, N, K, pz, rb.ldp, outb, outlo, ldo, m0, n0, kbeg, \
                                                  nk, rot, out_f16)
-    if constexpr (W == 192) {  // (only launches whose row tiles are all of full height)
-        ST_RING_TILE(8);
+    // the heights that occur: W = 192 only where all row tiles are of full height, ONCE only with a single row tile
+    constexpr int kLowest = W == 192 ? 4 : ONCE ? ring_once_units(TERMS == 2) : 2;
+    const int units = __builtin_amdgcn_readfirstlane(ring_units(gg, rb.y));
+    if (kLowest <= 2 && units == 2) {
+        if constexpr (kLowest <= 2) ST_RING_TILE(4);
+    } else if (kLowest <= 3 && units == 3) {
+        if constexpr (kLowest <= 3) ST_RING_TILE(6);
     } else {
-        switch (__builtin_amdgcn_readfirstlane(ring_units(gg, rb.y))) {
-            case 2: ST_RING_TILE(4); break;
-            case 3: ST_RING_TILE(6); break;
-            default: ST_RING_TILE(8); break;
-        }
+        ST_RING_TILE(8);
     }
 #undef ST_RING_TILE
 }
@@ -1888,13 +1894,11 @@ hipError_t raise_lds_limits() {
     ST_RING_LIMIT(true, 256, false) ST_RING_LIMIT(true, 192, false) ST_RING_LIMIT(true, 128, false)
     ST_RING_LIMIT(true, 256, true) ST_RING_LIMIT(true, 192, true) ST_RING_LIMIT(true, 128, true)
 #undef ST_RING_LIMIT
-#define ST_STREAM_LIMIT(MT)                                                                                  \
-    take(raise_one(k_gemm_stream<MT, 1, false, false>)), take(raise_one(k_gemm_stream<MT, 1, true, false>)), \
-        take(raise_one(k_gemm_stream<MT, 1, false, true>)), take(raise_one(k_gemm_stream<MT, 1, true, true>));
-    ST_STREAM_LIMIT(1) ST_STREAM_LIMIT(2) ST_STREAM_LIMIT(3) ST_STREAM_LIMIT(4) ST_STREAM_LIMIT(5)
-    take(raise_one(k_gemm_stream<1, 2, false, false>)), take(raise_one(k_gemm_stream<1, 2, false, true>));
-    take(raise_one(k_gemm_stream<2, 2, false, false>)), take(raise_one(k_gemm_stream<2, 2, false, true>));
-    take(raise_one(k_gemm_stream<3, 2, false, false>)), take(raise_one(k_gemm_stream<3, 2, false, true>));
+#define ST_STREAM_LIMIT(MT, T, F) \
+    take(raise_one(k_gemm_stream<MT, T, F, false>)), take(raise_one(k_gemm_stream<MT, T, F, true>));
+    ST_STREAM_LIMIT(1, 1, true) ST_STREAM_LIMIT(2, 1, true) ST_STREAM_LIMIT(3, 1, true) ST_STREAM_LIMIT(4, 1, true)
+    ST_STREAM_LIMIT(5, 1, true) ST_STREAM_LIMIT(5, 1, false)
+    ST_STREAM_LIMIT(1, 2, false) ST_STREAM_LIMIT(2, 2, false) ST_STREAM_LIMIT(3, 2, false)
 #undef ST_STREAM_LIMIT
     return e;
 }
@@ -1940,19 +1944,19 @@ static void stream_dispatch(const Model &m, const StreamShape &sh, const bf16_t 
         }
         return;
     }
-    // one activation term: fp16 operands, or single bf16 (ST_PREFILL_FAST)
-#define ST_STREAM1(MTV)                                                                \
-    case MTV:                                                                          \
-        if (f16)                                                                       \
-            stream_launch<MTV, 1, true>(m, sh, A, nullptr, lda, B, M, N, K, dual);     \
-        else                                                                           \
-            stream_launch<MTV, 1, false>(m, sh, A, nullptr, lda, B, M, N, K, dual);    \
-        break;
-    switch (tiles) {
-        ST_STREAM1(1) ST_STREAM1(2) ST_STREAM1(3) ST_STREAM1(4)
-        default: ST_STREAM1(5)
+    // one activation term: fp16 operands, or single bf16 (ST_PREFILL_FAST, whose shortest passes have five tiles)
+    static_assert((kFastMinRows + 31) / 32 == 5 && kRingMinRowsFast - 1 <= 5 * 32, "tiles of a single-bf16 pass");
+    if (!f16) {
+        stream_launch<5, 1, false>(m, sh, A, nullptr, lda, B, M, N, K, dual);
+        return;
     }
-#undef ST_STREAM1
+    switch (tiles) {
+        case 1: stream_launch<1, 1, true>(m, sh, A, nullptr, lda, B, M, N, K, dual); break;
+        case 2: stream_launch<2, 1, true>(m, sh, A, nullptr, lda, B, M, N, K, dual); break;
+        case 3: stream_launch<3, 1, true>(m, sh, A, nullptr, lda, B, M, N, K, dual); break;
+        case 4: stream_launch<4, 1, true>(m, sh, A, nullptr, lda, B, M, N, K, dual); break;
+        default: stream_launch<5, 1, true>(m, sh, A, nullptr, lda, B, M, N, K, dual); break;
+    }
 }
 
 // One block per CU at a time, so the time is (rounds of 256 blocks) x (bytes a block loads, weights and activations
@@ -2053,7 +2057,6 @@ struct RingCost {
 };
 
 // two_term: A arrives as two bf16 terms; a block then takes up to 128 rows instead of 256 (see k_gemm_ring).
-static int ring_unit(bool two_term) { return two_term ? 32 : 64; }
 static RingPlan ring_plan(bool dual, bool two_term, int M, int N, int K, size_t cap, bool allow_tail) {
     RingPlan p{};
     RingGrid gg;
@@ -2065,7 +2068,7 @@ static RingPlan ring_plan(bool dual, bool two_term, int M, int N, int K, size_t 
     while (gg.TY * 2 <= gg.My && gg.TY < 8) gg.TY *= 2;
     gg.TX = 32 / gg.TY;
     gg.S = 1, gg.kps = K, gg.col0 = 0;
-    gg.once = gg.My == 1 && (size_t)N * K * (dual ? 4 : 2) >= kStreamOnceBytes;
+    gg.once = gg.My == 1 && units >= ring_once_units(two_term) && (size_t)N * K * (dual ? 4 : 2) >= kStreamOnceBytes;
     gg.tail_x0 = gg.tail_tiles = 0, gg.tail_s = 1, gg.tail_kps = K;
     const int nx = (N + (dual ? 127 : 255)) / (dual ? 128 : 256);  // column tiles of full width
     const long tiles = (long)gg.My * nx;
@@ -2191,6 +2194,7 @@ int ring_plan_check(int dual, int two_term, int M, int N, int K, long long cap_f
             const int units = ring_units(p.g[l], rb.y), r0 = ring_row0(p.g[l], rb.y, unit);
             if (rb.y < 0 || rb.y >= my || n0 < 0 || n0 >= N || units < 2 || units > 4 || r0 >= M) return -2;
             if (n0 % out_cols || (p.width[l] == 192 && units != 4)) return -2;
+            if (p.g[l].once && units < ring_once_units(two_term != 0)) return -2;
             if (rb.y == my - 1 && r0 + units * unit < M) return -2;  // the last row tile ends at or past the last row
             if (rb.kbeg < 0 || rb.kend > K || (rb.kend - rb.kbeg) % kRingBK || rb.kend - rb.kbeg < 2 * kRingBK) return -3;
             for (int c = 0; c < per_tile; ++c) {
@@ -2311,7 +2315,7 @@ struct PassTerms {
 };
 static PassTerms pass_terms(const Model &m, int n) {
     const Workspace &w = m.ws;
-    int terms = n <= 128 ? kTermAll : m.long_terms;  // (ST_PREFILL_FAST starts at 129 rows)
+    int terms = n < kFastMinRows ? kTermAll : m.long_terms;
     PassTerms t;
     // Default-precision passes of a model that has its fp16 weight copy: at every pass length the inputs of the
     // gate/up, O and down projections are single fp16 numbers.  The input of the QKV projection and the queries keep

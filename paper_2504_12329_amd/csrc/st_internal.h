@@ -93,7 +93,8 @@ struct AttnRows {
     bf16_t *out_hi, *out_lo;
 };
 
-// Inputs that may carry a second bf16 term in a pass of more than 128 rows (Model::long_terms): the activations of
+constexpr int kFastMinRows = 129;  // the shortest pass in which ST_PREFILL_FAST drops second terms
+// Inputs that may carry a second bf16 term in a pass of kFastMinRows rows and more (Model::long_terms): the activations of
 // the four projections and the rotated queries of the attention
 enum LongTerms { kTermQKV = 1, kTermO = 2, kTermGateUp = 4, kTermDown = 8, kTermQuery = 16, kTermAll = 31 };
 constexpr int kDefaultLongTerms = kTermAll;

@@ -3,6 +3,8 @@ arguments before touching the GPU.  No compute calls."""
 import ctypes as C
 import os
 import re
+import shutil
+import subprocess
 
 import pytest
 
@@ -213,3 +215,13 @@ def test_single_kernel_decode_plan_on_the_host(L):
         B.st_decode_persist_plan(small, 4)                 # fewer than 8 compute units
     with pytest.raises(B.StError):
         B.st_decode_persist_plan(dict(small, n_q_heads=16, n_kv_heads=16, hidden=1024), 8)  # 16 kv heads on 8 units
+
+
+@pytest.mark.skipif(shutil.which("nm") is None, reason="nm not on PATH")
+def test_streaming_kernels_built_are_the_ones_passes_launch(L):
+    """Two terms up to 96 rows (three activation tiles of 32), fp16 up to 160 (five), a single bf16 term at 129 to 160 rows
+    only (ST_PREFILL_FAST keeps both terms below): each plain and with the SwiGLU in its epilogue, and no others."""
+    names = subprocess.run(["nm", "-C", B.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    built = set(re.findall(r"__device_stub__k_gemm_stream<(\d), (\d), (\w+), (\w+)>", names))
+    forms = [(t, "2", "false") for t in "123"] + [(t, "1", "true") for t in "12345"] + [("5", "1", "false")]
+    assert built == {f + (dual,) for f in forms for dual in ("false", "true")}
