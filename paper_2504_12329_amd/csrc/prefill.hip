@@ -407,12 +407,13 @@ __device__ __forceinline__ void wait_loads() {  // until at most N of this wave'
 }
 template <int V>
 using ic = std::integral_constant<int, V>;
-template <int N, int I = 0, class F>
+template <class F, int... I>
+__device__ __forceinline__ void static_for_each(F &f, std::integer_sequence<int, I...>) {
+    (f(ic<I>{}), ...);
+}
+template <int N, class F>
 __device__ __forceinline__ void static_for(F &&f) {  // f(ic<0>{}), ..., f(ic<N-1>{})
-    if constexpr (I < N) {
-        f(ic<I>{});
-        static_for<N, I + 1>(f);
-    }
+    static_for_each(f, std::make_integer_sequence<int, N>{});
 }
 
 // Block ids -> work of the ring kernel.  Main part: S K slices of kps columns over My x Nx tiles, numbered slice by
@@ -493,6 +494,18 @@ __host__ __device__ inline int ring_rot(int x, int nk) { return (x & 7) * nk >> 
 constexpr int ring_unit(bool two_term) { return two_term ? 32 : 64; }
 constexpr int ring_once_units(bool two_term) {
     return ((two_term ? kRingMinRows : kRingMinRowsFast) + ring_unit(two_term) - 1) / ring_unit(two_term);
+}
+
+// What follows MFMA m of a 16-wide step of NM: the first fragment read from q on (of NR: they go in pairs, spread over the
+// step), and the first direct load from g on (of nl: each behind the MFMA at 3/4 of its share of the step).  NR / nl: none.
+// (Asked for each m rather than of every read and load: a tenth of the lambdas to inline.)
+constexpr int ring_read_at(int m, int q, int NM, int NR) {
+    while (q < NR && m != (q >> 1) * (2 * NM / NR) + (q & 1)) ++q;
+    return q;
+}
+constexpr int ring_load_at(int m, int g, int NM, int nl) {
+    while (g < nl && m != (4 * g + 3) * NM / (4 * nl) - ((4 * g + 3) * NM / (4 * nl) > 0 ? 1 : 0)) ++g;
+    return g;
 }
 
 // The block's tile: NF activation fragments of 32 LDS rows (one term: NF * 32 rows; two terms: NF * 16 rows, the high
@@ -644,23 +657,26 @@ __device__ __forceinline__ void ring_tile(unsigned char *ring, const bf16_t *__r
             constexpr int m = decltype(m_c)::value;
             mma(ic<cur>{}, m_c);
             __builtin_amdgcn_sched_barrier(0);
-            // reads go in pairs, spread over the step
-            if constexpr (FETCH)
-                static_for<NR>([&](auto q_c) {
-                    constexpr int q = decltype(q_c)::value;
-                    if constexpr (m == (q >> 1) * (2 * NM / NR) + (q & 1)) {
-                        fetch(ic<cur ^ 1>{}, q_c, slotA, slotB, ks_next);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                });
-            // load g follows the MFMA at 3/4 of its share of the step
-            static_for<nl>([&](auto g_c) {
-                constexpr int g = decltype(g_c)::value;
-                if constexpr (m == (4 * g + 3) * NM / (4 * nl) - ((4 * g + 3) * NM / (4 * nl) > 0 ? 1 : 0)) {
-                    if constexpr (kind == 1) loadA(ic<d0 + g>{}, dslot, dbase);
-                    if constexpr (kind == 2) loadB(ic<d0 + g>{}, dslot, dbase);
+            if constexpr (FETCH) {
+                constexpr int q = ring_read_at(m, 0, NM, NR), q2 = ring_read_at(m, q + 1, NM, NR);
+                static_assert(ring_read_at(m, q2 + 1, NM, NR) >= NR, "at most two reads behind an MFMA");
+                if constexpr (q < NR) {
+                    fetch(ic<cur ^ 1>{}, ic<q>{}, slotA, slotB, ks_next);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-            });
+                if constexpr (q2 < NR) {
+                    fetch(ic<cur ^ 1>{}, ic<q2>{}, slotA, slotB, ks_next);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            if constexpr (nl > 0) {
+                constexpr int g = ring_load_at(m, 0, NM, nl), g2 = ring_load_at(m, g + 1, NM, nl);
+                static_assert(ring_load_at(m, g2 + 1, NM, nl) >= nl, "at most two loads behind an MFMA");
+                if constexpr (kind == 1 && g < nl) loadA(ic<d0 + g>{}, dslot, dbase);
+                if constexpr (kind == 1 && g2 < nl) loadA(ic<d0 + g2>{}, dslot, dbase);
+                if constexpr (kind == 2 && g < nl) loadB(ic<d0 + g>{}, dslot, dbase);
+                if constexpr (kind == 2 && g2 < nl) loadB(ic<d0 + g2>{}, dslot, dbase);
+            }
             __builtin_amdgcn_sched_barrier(0);
         });
     };
