@@ -58,11 +58,12 @@ enum {
                               close to an fp32 evaluation as the decode step's.  Up to about 100 rows the second
                               term costs no time (the weight stream sets it); longer passes are bound by the MFMA
                               rate and pay twice the MFMA work.  With this flag passes of 129 rows and more take
-                              single bf16 inputs: at 1.5B / 7B / 32B (four layers on 512 keys) 0.96x / 1.17x / 1.36x
-                              as fast as the default at 129 to 160 rows, 1.05x / 1.29x / 1.41x at 256 and 1.22x /
-                              1.55x / 1.69x at 1024, at about twice the logit error at the depths the CPU oracle reaches (1.7e-2 against 0.8e-2
-                              through 28 layers of the 1.5B shape) and more beyond (6.8e-2 from the decode step
-                              through 64 layers of the 32B shape, where the default pass is at 1.3e-2).  Excludes
+                              single bf16 inputs: at 1.5B / 7B / 32B (four layers on 512 keys) 1.07x / 1.35x / 1.5x
+                              as fast as the default at 129 to 160 rows, 1.07x / 1.43x / 1.52x at 256 and 1.25x /
+                              1.60x / 1.71x at 1024, at about twice the logit error at the depths the CPU oracle
+                              reaches (1.7e-2 against 0.8e-2 through 28 layers of the 1.5B shape) and more beyond
+                              (6.8e-2 from the decode step through 64 layers of the 32B shape, where the default
+                              pass is at 1.3e-2).  Excludes
                               ST_PREFILL_TWO_TERM. */
 };
 
@@ -112,7 +113,8 @@ int st_prefill_plan_check(const st_config *cfg, int32_t rows, int32_t *launches,
  * two_term: inputs in two bf16 terms (the default pass) or in one (ST_PREFILL_FAST).  forms[0..3], the QKV, O, gate/up and
  * down projection: 0 for the general kernel, K slices << 8 | weight tiles per block << 16 for the streaming kernel, K slices << 8 |
  * 1 (full-width tiles) | 8 (three-quarter-width tiles) | 2 (half-width tiles) | 4 (left-over columns in K slices of their own) for
- * the ring kernel.  forms[4], the attention at head_dim 128: 1 = four waves, 2 = eight waves in two halves.  forms[5]: its key ranges. */
+ * the ring kernel.  A streaming gate/up of one K slice has its SwiGLU in the epilogue.  forms[4], the attention at head_dim 128:
+ * 1 = four waves, 2 = eight waves in two halves.  forms[5]: its key ranges. */
 int st_prefill_plan_forms(const st_config *cfg, int32_t rows, int32_t pos0, int32_t two_term, int32_t *forms);
 
 /* Creates a model over caller-owned device buffers (both 256-byte aligned).  Initialises the
@@ -374,8 +376,9 @@ typedef struct {
  * seqs[i] (host, capacity prompt_lens[i] + n_out) receives prompt + outputs, srcs[i] (host, n_out bytes; srcs or any
  * entry may be NULL) 0 / 1 per output token.  stats sums over the sequences. */
 int st_generate_batch(st_batch *small, st_batch *large, const st_host_rule *rule, int32_t forced_period,
-                      const int32_t *forced_phase, int32_t gather, int32_t n_seq, const int32_t *const *prompts, const int32_t *prompt_lens, int32_t n_out,
-                      int32_t n_seg, int32_t *const *seqs, uint8_t *const *srcs, st_gen_stats *stats);
+                      const int32_t *forced_phase, int32_t gather, int32_t n_seq, const int32_t *const *prompts,
+                      const int32_t *prompt_lens, int32_t n_out, int32_t n_seg, int32_t *const *seqs,
+                      uint8_t *const *srcs, st_gen_stats *stats);
 
 /* Measurement support: one chained greedy decode step (feeds the model's own last token) in which
  * every launch of the gate/up projection kernel -- the kernel that moves the most bytes of a step

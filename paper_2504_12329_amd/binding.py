@@ -16,11 +16,13 @@ LIB_PATH = os.path.join(HERE, "libst.so")
 ST_OK, ST_EINVAL, ST_ENOMEM, ST_ERANGE, ST_EHIP = 0, -1, -2, -3, -4
 ST_TOKENS_DEVICE, ST_OUT_DEVICE, ST_TOKEN_CHAINED, ST_PREFILL_TWO_TERM, ST_PREFILL_FAST = 1, 2, 4, 8, 16
 
-EXPORTS = ("st_query_sizes", "st_prefill_plan_check", "st_prefill_plan_forms", "st_model_create", "st_model_destroy", "st_kv_len", "st_kv_truncate", "st_prefill",
-           "st_query_f16_bytes", "st_model_attach_f16", "st_batch_attach_f16", "st_decode_step", "st_decode_graph_state", "st_decode_step_kind", "st_decode_persist_plan", "st_decode_step_timed", "st_decode_greedy", "st_trigger_scan", "st_trigger_scan_static", "st_handoff", "st_generate",
-           "st_generate_policy", "st_batch_query_sizes", "st_batch_create", "st_batch_destroy", "st_batch_kv_len",
-           "st_batch_truncate", "st_batch_prefill", "st_batch_prefill_many", "st_batch_decode_step", "st_generate_batch",
-           "st_last_error")
+EXPORTS = ("st_query_sizes", "st_prefill_plan_check", "st_prefill_plan_forms", "st_model_create", "st_model_destroy", "st_kv_len",
+           "st_kv_truncate", "st_prefill", "st_query_f16_bytes", "st_model_attach_f16", "st_batch_attach_f16",
+           "st_decode_step", "st_decode_graph_state", "st_decode_step_kind", "st_decode_persist_plan",
+           "st_decode_step_timed", "st_decode_greedy", "st_trigger_scan", "st_trigger_scan_static", "st_handoff",
+           "st_generate", "st_generate_policy", "st_batch_query_sizes", "st_batch_create", "st_batch_destroy",
+           "st_batch_kv_len", "st_batch_truncate", "st_batch_prefill", "st_batch_prefill_many", "st_batch_decode_step",
+           "st_generate_batch", "st_last_error")
 
 
 class StError(RuntimeError):
@@ -147,8 +149,8 @@ def st_prefill_plan_check(cfg, rows):
 
 def st_prefill_plan_forms(cfg, rows, pos0, two_term=True):
     """Kernel forms of a pass of `rows` rows at position `pos0`: for QKV, O, gate/up and down ("stream", weight tiles per block,
-    K slices), ("ring", tile widths F (256 weight rows), Q (192), H (128) or two of them, sliced tail, K slices) or None (general kernel); then the attention's waves
-    per block (None at head_dim 64) and key ranges."""
+    K slices), ("ring", tile widths F (256 weight rows), Q (192), H (128) or two of them, sliced tail, K slices) or None
+    (general kernel); then the attention's waves per block (None at head_dim 64) and key ranges."""
     f = (C.c_int32 * 6)()
     _check(lib().st_prefill_plan_forms(C.byref(make_config(cfg)), int(rows), int(pos0), int(two_term), f))
     gemms = [None if not v else ("stream", v >> 16, v >> 8 & 255) if v >> 16 else
@@ -193,8 +195,8 @@ ST_SCAN_STATIC_MAX_CAP = 4096
 
 
 def st_trigger_scan_static(rule, tokens_dev, lo, hi, cap, stream=None):
-    """st_trigger_scan without a caller-provided device scratch (the library's static staging array; allocates
-    nothing on the device).  Returns (total_count, positions ndarray)."""
+    """st_trigger_scan without a caller-provided device scratch (the library's own staging: pinned host memory the first
+    call on a GPU allocates, nothing on the device).  Returns (total_count, positions ndarray)."""
     pos = np.empty(max(cap, 1), dtype=np.int32)
     n = C.c_int32()
     s = torch.cuda.current_stream().cuda_stream if stream is None else stream

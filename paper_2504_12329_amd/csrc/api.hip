@@ -666,7 +666,8 @@ int st_decode_step_timed(st_model *h, double *gateup_mean_us, double *step_us) {
 int st_trigger_scan(const st_trigger_rule *rule, const int32_t *tokens, int32_t lo, int32_t hi, int32_t *positions,
                     int32_t cap, int32_t *n_found, int32_t *scratch, void *stream, uint32_t flags) {
     if (!rule || !rule->kw_bitmap || !tokens || !n_found) return fail(ST_EINVAL, "rule, bitmap, tokens or n_found is NULL");
-    if (rule->window < 1 || rule->window > ST_MAX_SCAN_WINDOW) return fail(ST_EINVAL, "window must be in [1, %d]", ST_MAX_SCAN_WINDOW);
+    if (rule->window < 1 || rule->window > ST_MAX_SCAN_WINDOW)
+        return fail(ST_EINVAL, "window must be in [1, %d]", ST_MAX_SCAN_WINDOW);
     if (rule->window >= 2 && !rule->delim_bitmap) return fail(ST_EINVAL, "a window above 1 needs a delimiter bitmap");
     if (rule->vocab <= 0) return fail(ST_EINVAL, "rule vocab must be positive");
     if (int rc = check_flags(flags, ST_OUT_DEVICE)) return rc;
@@ -775,7 +776,8 @@ int st_generate_policy(st_model *hs, st_model *hl, const st_policy *pol, const i
     if ((int64_t)P + n_out > M[0]->c.max_seq || (int64_t)P + n_out > M[1]->c.max_seq)
         return fail(ST_ERANGE, "P + n_out = %d exceeds a model's max_seq", P + n_out);
     for (int32_t i = 0; i < pol->n_aux; ++i)
-        if (pol->aux_tokens[i] < 0 || pol->aux_tokens[i] >= pol->vocab) return fail(ST_ERANGE, "auxiliary token outside the vocabulary");
+        if (pol->aux_tokens[i] < 0 || pol->aux_tokens[i] >= pol->vocab)
+            return fail(ST_ERANGE, "auxiliary token outside the vocabulary");
 
     auto in_class = [&](const uint32_t *bm, int32_t t) {
         return bm && t >= 0 && t < pol->vocab && ((bm[t >> 5] >> (t & 31)) & 1u);
@@ -1168,7 +1170,8 @@ int st_generate_batch(st_batch *hs, st_batch *hl, const st_host_rule *rule, int3
     if (S == L) return fail(ST_EINVAL, "small and large must be different batches");
     if (forced_period < 0) return fail(ST_EINVAL, "forced_period must be >= 0");
     if (forced_period == 0) {
-        if (!rule || !rule->kw_bitmap || rule->vocab <= 0) return fail(ST_EINVAL, "a trigger rule (or forced_period > 0) is required");
+        if (!rule || !rule->kw_bitmap || rule->vocab <= 0)
+            return fail(ST_EINVAL, "a trigger rule (or forced_period > 0) is required");
         if (rule->window != 1 && rule->window != 2) return fail(ST_EINVAL, "window must be 1 or 2");
         if (rule->window == 2 && !rule->delim_bitmap) return fail(ST_EINVAL, "window 2 needs a delimiter bitmap");
     }

@@ -658,7 +658,8 @@ __global__ __launch_bounds__(kPT) void k_decode_persist(const PersistArgs *ap, c
     int tok = __hip_atomic_load(as_global(a->state + kTok), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     tok = tok < 0 ? 0 : (tok >= a->V ? a->V - 1 : tok);
     const unsigned ep0 =
-        (unsigned)__hip_atomic_load(as_global(a->state + kEpoch), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) * (unsigned)(8 * (a->L + 1)) + 64u;
+        (unsigned)__hip_atomic_load(as_global(a->state + kEpoch), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) *
+            (unsigned)(8 * (a->L + 1)) + 64u;
 
     const int t = pos + 1;
     int chunk = (t + a->s_cap - 1) / a->s_cap;
@@ -740,7 +741,8 @@ __global__ __launch_bounds__(kPT) void k_decode_persist(const PersistArgs *ap, c
         ST_STAMP();
         if (s_act > 1) {
             const int per_head = D / a->dsl, items = a->nq * per_head;
-            for (int it = b; it < items; it += nb) merge_stage<D>(c, a, it / per_head, (it % per_head) * a->dsl, s_act, ep, area, red);
+            for (int it = b; it < items; it += nb)
+                merge_stage<D>(c, a, it / per_head, (it % per_head) * a->dsl, s_act, ep, area, red);
         }
         ST_STAMP();
         ST_ARGS_FRESH();
@@ -908,7 +910,8 @@ hipError_t launch_t(const PersistArgs *a, const PersistRule &r, int nb, size_t l
 }
 
 template <int D>
-hipError_t launch_d(int G, const PersistArgs *a, const PersistRule &r, int nb, size_t lds_bytes, hipStream_t stream, bool set_attr) {
+hipError_t launch_d(int G, const PersistArgs *a, const PersistRule &r, int nb, size_t lds_bytes, hipStream_t stream,
+                    bool set_attr) {
     switch (G) {
         case 1: return launch_t<D, 1>(a, r, nb, lds_bytes, stream, set_attr);
         case 2: return launch_t<D, 2>(a, r, nb, lds_bytes, stream, set_attr);

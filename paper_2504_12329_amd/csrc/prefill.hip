@@ -3,9 +3,9 @@
 // residual / SwiGLU epilogues, RoPE + KV append, and causal flash attention with a key offset.
 #include "st_device.h"
 #include "st_internal.h"
-#include <vector>
-
 #include <type_traits>
+#include <utility>
+#include <vector>
 
 namespace st {
 
@@ -80,8 +80,8 @@ static inline PartTail tail_at_row(PartTail t, int row, int h) {
 static inline int norm_threads(int rows) { return rows <= 512 ? 1024 : 256; }
 
 // x[row] += sum of the pending split-K partial results (fixed order), then y[row] = bf16(rmsnorm(x) * g).
-// part is [n_part][rows][h] (plus the extra slices `tail` describes); with g == nullptr only the residual update is done.  With Ylo the
-// normalised row is written as a sum of two bf16 numbers (Y + Ylo), which keeps 16 mantissa bits; with f16 (and no
+// part is [n_part][rows][h] (plus the extra slices `tail` describes); with g == nullptr only the residual update is done.  With
+// Ylo the normalised row is written as a sum of two bf16 numbers (Y + Ylo), which keeps 16 mantissa bits; with f16 (and no
 // Ylo) as one fp16 number.
 __global__ __launch_bounds__(1024) void k_rmsnorm_rows(float *__restrict__ X, const float *__restrict__ part,
                                                        int n_part, size_t part_stride, const bf16_t *__restrict__ g,
@@ -517,7 +517,9 @@ constexpr int ring_load_at(int m, int g, int NM, int nl) {
 // W = 192 (fused form at full height only): where full tiles leave CUs idle and half-width ones need another round.  Gate/up of
 // the 7B shape at 97 to 128 rows is 148 full tiles or 198 of these on 256 CUs.  Four layers, without / with them: 7B 126 rows
 // 1005 / 972 us, 256 fp16 rows 1091 / 1056; 1.5B 250 and 1000 rows 580 / 561 and 1132 / 1100, 500 fp16 rows 714 / 689; behind full
-// rounds 32B 250 rows 2267 / 2180, 500 fp16 rows 2565 / 2498, 7B 1000 rows 3579 / 3557 us.
+// rounds 32B 250 and 377 rows 2000 / 1897 and 2837 / 2737, 500 fp16 rows 2565 / 2498; at 7B nothing, where the plan expects 15 us
+// a layer: 353 to 384 rows 1445 / 1446, 993 to 1024 rows 3247 / 3252 us (the last, partly filled round of full tiles is shorter
+// than a whole one there).
 template <int NF, bool DUAL, int W, int TERMS, bool F16, bool ONCE>
 __device__ __forceinline__ void ring_tile(unsigned char *ring, const bf16_t *__restrict__ A, const bf16_t *__restrict__ Alo,
                                           int lda, const bf16_t *__restrict__ B, int M, int N, int K, float *__restrict__ pz,
@@ -700,9 +702,10 @@ __device__ __forceinline__ void ring_tile(unsigned char *ring, const bf16_t *__r
     auto kstep = [&](auto ahead_c) {
         constexpr int AHEAD = decltype(ahead_c)::value;
         const int sA = next_slot(sB, 1), sB1 = next_slot(sB, 2), sA1 = next_slot(sB, 3), sB2 = next_slot(sB, 4);
-        step(ic<0>{}, ic<1>{}, sA, sB, 1, ic<(!SPEC && AHEAD >= 1 ? 1 : 0)>{}, ic<HA>{}, ic<NLA - HA>{}, sA1, an1);  // rest of A(kt+1)
-        step(ic<1>{}, ic<1>{}, sA, sB, 2, ic<(!SPEC && AHEAD >= 2 ? 2 : 0)>{}, ic<0>{}, ic<HB>{}, sB2, bn2);   // B(kt+2)
-        step(ic<0>{}, ic<1>{}, sA, sB, 3, ic<(!SPEC && AHEAD >= 2 ? 2 : 0)>{}, ic<HB>{}, ic<HB>{}, sB2, bn2);  // B(kt+2)
+        // the rest of A(kt+1), then B(kt+2) in two steps
+        step(ic<0>{}, ic<1>{}, sA, sB, 1, ic<(!SPEC && AHEAD >= 1 ? 1 : 0)>{}, ic<HA>{}, ic<NLA - HA>{}, sA1, an1);
+        step(ic<1>{}, ic<1>{}, sA, sB, 2, ic<(!SPEC && AHEAD >= 2 ? 2 : 0)>{}, ic<0>{}, ic<HB>{}, sB2, bn2);
+        step(ic<0>{}, ic<1>{}, sA, sB, 3, ic<(!SPEC && AHEAD >= 2 ? 2 : 0)>{}, ic<HB>{}, ic<HB>{}, sB2, bn2);
         if constexpr (AHEAD >= 1) {
             // all fragments of this K step are in registers and K step kt+1 has landed (only B(kt+2) may
             // still be in flight); after the barrier that holds for every wave, so both slots are free
@@ -837,12 +840,14 @@ __global__ __launch_bounds__(TERMS == 2 ? 512 : 256) void k_gemm_ring(const bf16
 // ones).  Every block re-reads the activation rows from L2, so it is made tall -- up to 256 weight rows per activation fetch.
 // Eight waves: 0-3 multiply, 4 and 5 load weights, 6 and 7 activations, into two LDS rings of nw and na stages (a wave's
 // load counter retires in order: one wave could not wait for a recent activation load without also waiting for every older
-// weight load).  The loading waves' loop is unrolled for their load count, with wave-uniform bases and 32-bit lane offsets:
-// with 64-bit pointers, a branch per pair of loads and waves that did both above three activation tiles, a pass of 21 rows at
-// 1.5B took 1974 us (now 1843), one of 86 rows at 32B 1.50 ms (now 1.43), a step of 16 sequences at 32B 1.03 ms (now 0.95).
-// stream_once: see kStreamOnceBytes.  Wave w multiplies weight tiles w and w + 4 against every 32-row activation tile (C^T = W A^T, a lane owns
-// an activation row); raw fp32 partial sums of the K slice go to part[z][M][N].  Needs K % 64 == 0 and
-// (nw - 2) * (loads per weight wave per stage) <= 63.
+// weight load).  The loading waves' loop is unrolled for their load count, with wave-uniform bases and 32-bit lane offsets.
+// stream_once: see kStreamOnceBytes.  Before both -- 64-bit pointers, a branch per pair of loads, waves that did everything above
+// three activation tiles, all weights through the caches -- a pass of 21 rows at 1.5B took 1974 us (then 1847), one of 86 rows
+// at 32B 1492 us (1452), a step of 16 sequences at 32B 1001 us (914).  Wave w multiplies weight tiles w and w + 4 against every
+// 32-row activation tile (C^T = W A^T, a lane owns an activation row).  Raw fp32 partial sums of the K slice go to
+// part[z][M][N], or (DUAL, one slice) the SwiGLU of gate and up columns to outb / outlo: no sums written and read again, 1847 ->
+// 1811 us of that pass of 21 rows, 1452 -> 1402 us of the one of 86.  Needs K % 64 == 0 and (nw - 2) * (loads per weight wave
+// per stage) <= 63.
 // ---------------------------------------------------------------------------------------
 struct StreamGeom {
     static constexpr int BK = 64;
@@ -876,15 +881,16 @@ __device__ __forceinline__ void put_act4(bf16_t *hi, bf16_t *lo, int f16, float 
     }
     const u32x2 h = {pack_bf16x2(v0, v1), pack_bf16x2(v2, v3)};
     *reinterpret_cast<u32x2 *>(hi) = h;
-    *reinterpret_cast<u32x2 *>(lo) = u32x2{pack_bf16x2(v0 - bf16_lo(h.x), v1 - bf16_hi(h.x)), pack_bf16x2(v2 - bf16_lo(h.y), v3 - bf16_hi(h.y))};
+    *reinterpret_cast<u32x2 *>(lo) = u32x2{pack_bf16x2(v0 - bf16_lo(h.x), v1 - bf16_hi(h.x)),
+                                           pack_bf16x2(v2 - bf16_lo(h.y), v3 - bf16_hi(h.y))};
 }
 
 // A loading wave of k_gemm_stream: N direct loads a stage at wave-uniform base + off[i], into a ring of `depth` stages of
 // `stage` bytes from LDS offset lds on (the wave's share of a stage is N KB).  TWO: every other group of four loads reads
 // base1, the first one if `odd`.  One barrier per stage: stage st is whole, and stage st - 1 has been read.
 template <int N, bool NT, bool TWO = false>
-__device__ __forceinline__ void stream_load(const bf16_t *base, const bf16_t *base1, int odd, const uint32_t (&off)[N], uint32_t lds,
-                                            uint32_t stage, int depth, int nk) {
+__device__ __forceinline__ void stream_load(const bf16_t *base, const bf16_t *base1, int odd, const uint32_t (&off)[N],
+                                            uint32_t lds, uint32_t stage, int depth, int nk) {
     const uint32_t ring_bytes = stage * depth;
     const bf16_t *even_p = TWO && odd ? base1 : base, *odd_p = TWO && !odd ? base1 : base;
     uint32_t slot = 0;
@@ -958,7 +964,8 @@ __global__ __launch_bounds__(512) void k_gemm_stream(const bf16_t *__restrict__ 
 #pragma unroll
         for (int i = 0; i < kALoads; ++i) {
             const int row = (q * kALoads + i) * G::kRpi + lane / G::kLpr;
-            off[i] = (uint32_t)min(row / RT * 32 + (row & 31), M - 1) * (uint32_t)lda * 2u + (((lane % G::kLpr) ^ ring_swz(row)) << 4);
+            off[i] = (uint32_t)min(row / RT * 32 + (row & 31), M - 1) * (uint32_t)lda * 2u +
+                     (((lane % G::kLpr) ^ ring_swz(row)) << 4);
         }
         // 32-row block b of a stage is of term b % TERMS; wave q starts at block q * kALoads / 4
         stream_load<kALoads, false, TERMS == 2>(A + kbeg, (TERMS == 2 ? Alo : A) + kbeg, kALoads / 4 % 2 ? q : 0, off,
@@ -966,7 +973,10 @@ __global__ __launch_bounds__(512) void k_gemm_stream(const bf16_t *__restrict__ 
         return;
     }
     if (wave >= 4) {
-#define ST_SW(NTV) case NTV: stream_load_w<2 * NTV, DUAL>(B, wave - 4, lane, n0, N, K, kbeg, ring0 + a_ring, wstage, nw, nk, stream_once); break;
+#define ST_SW(NTV)                                                                                                      \
+    case NTV:                                                                                                           \
+        stream_load_w<2 * NTV, DUAL>(B, wave - 4, lane, n0, N, K, kbeg, ring0 + a_ring, wstage, nw, nk, stream_once); \
+        break;
         switch (nt) {
             ST_SW(2) ST_SW(3) ST_SW(4) ST_SW(5) ST_SW(6) ST_SW(7) ST_SW(8)
         }
@@ -1906,7 +1916,8 @@ hipError_t raise_lds_limits() {
         take(raise_one(k_gemm_ring<D, H, 2, false, O>));
     take(raise_one(k_flash_long<false, false>)), take(raise_one(k_flash_long<true, false>));
     take(raise_one(k_flash_long<false, true>)), take(raise_one(k_flash_long<true, true>));
-    ST_RING_LIMIT(false, 256, false) ST_RING_LIMIT(false, 128, false) ST_RING_LIMIT(false, 256, true) ST_RING_LIMIT(false, 128, true)
+    ST_RING_LIMIT(false, 256, false) ST_RING_LIMIT(false, 128, false)
+    ST_RING_LIMIT(false, 256, true) ST_RING_LIMIT(false, 128, true)
     ST_RING_LIMIT(true, 256, false) ST_RING_LIMIT(true, 192, false) ST_RING_LIMIT(true, 128, false)
     ST_RING_LIMIT(true, 256, true) ST_RING_LIMIT(true, 192, true) ST_RING_LIMIT(true, 128, true)
 #undef ST_RING_LIMIT
@@ -2059,14 +2070,15 @@ struct RingPlan {
 
 // One block per CU at a time, so a launch takes (rounds of 256 blocks) x (K steps per block x the time of a step + what
 // a block spends filling its ring and storing its tile); the fp32 slices of the plain form are written once and read
-// again by the consumer.  Microseconds; a step of a full tile measured 1.7, of one of 192 weight
-// rows 1.25-1.4, of a half-width one 0.97-1.1.
+// again by the consumer.  Microseconds; a step of a full tile measured 1.7, of one of 192 weight rows 1.25-1.4, of a
+// half-width one 0.97-1.1.
 struct RingCost {
     static constexpr double kFill = 2.5, kLaunch = 2.5;
     // rows: mean height of the row tiles, out of the bm of a full one
     static double block(int width, bool dual, int bm, double rows, int steps) {
         const double tile_bytes = rows * width * (dual ? 1 : 4), h = rows / bm;
-        return steps * (width == 128 ? 0.35 + 0.70 * h : width == 192 ? 0.43 + 0.95 * h : 0.50 + 1.20 * h) + kFill + tile_bytes / 58e3;
+        const double step = width == 128 ? 0.35 + 0.70 * h : width == 192 ? 0.43 + 0.95 * h : 0.50 + 1.20 * h;
+        return steps * step + kFill + tile_bytes / 58e3;
     }
     static double rounds(long blocks) { return (double)((blocks + 255) / 256); }
     static double slices(int s, int M, int N) { return (double)s * M * N * 8 / 4e6; }
@@ -2093,8 +2105,9 @@ static RingPlan ring_plan(bool dual, bool two_term, int M, int N, int K, size_t 
     if (dual) {
         // Tiles of one width, or whole rounds of 256 full tiles and the columns left over as narrower tiles in a launch of their
         // own: more blocks of less length each, so that the last round keeps every CU busy for part of a round instead of part
-        // of the CUs for a whole one.  192 rows need row tiles of full
-        // height, and are taken alone up to eight of them (1024 rows of two terms, 2048 of one: the longest passes timed so).
+        // of the CUs for a whole one.  192 rows need row tiles of full height, and are taken alone up to eight of those: the model
+        // shapes would not take them alone beyond at any pass length, other widths (2240 columns at 4096 rows) might and have not
+        // been timed there.
         auto cols = [&](int w, int left) { return (left + w / 2 - 1) / (w / 2); };
         auto cost = [&](int w, long blocks) { return RingCost::rounds(blocks) * RingCost::block(w, true, bm, rows, nk); };
         const bool full_height = units == 4 * gg.My;
@@ -2128,7 +2141,8 @@ static RingPlan ring_plan(bool dual, bool two_term, int M, int N, int K, size_t 
                 if (s > 1 && (steps < 3 || (size_t)s * M * N > cap)) break;
                 const int used = (nk + steps - 1) / steps;
                 if (used != s || nk - (s - 1) * steps < 2) continue;  // the last slice needs two steps
-                const double cost = RingCost::rounds((h ? (long)gg.My * nxh : tiles) * s) * RingCost::block(h ? 128 : 256, false, bm, rows, steps) +
+                const double cost = RingCost::rounds((h ? (long)gg.My * nxh : tiles) * s) *
+                                        RingCost::block(h ? 128 : 256, false, bm, rows, steps) +
                                     RingCost::slices(s, M, N);
                 if (best < 0 || cost < best) best = cost, gg.S = s, width = h ? 128 : 256;
             }
@@ -2241,7 +2255,7 @@ int ring_plan_check(int dual, int two_term, int M, int N, int K, long long cap_f
     return 0;
 }
 
-// Chunks below the ring threshold use the streaming kernel and an unfused SwiGLU wherever K is a multiple of 64; otherwise
+// Chunks below the ring threshold use the streaming kernel wherever K is a multiple of 64 (gate/up: gate_up_short); otherwise
 // (also longer chunks with K = 64 or an operand of 4 GB) the register-staged kernel, with many K slices and an unfused
 // SwiGLU up to kSmallRows rows.
 constexpr int kSmallRows = 64;
@@ -2484,7 +2498,7 @@ void prefill_plan_forms(const st_config &c, int rows, int pos0, bool two_term, i
     for (int i = 0; i < 4; ++i) {
         forms[i] = 0;
         if (g[i].K % kRingBK) continue;
-        if (rows < ring_min_rows(two_term)) {  // gate/up unfused, over all 2I rows
+        if (rows < ring_min_rows(two_term)) {  // (gate/up over all 2I rows: one slice where gate_up_short fuses it)
             const int terms = two_term ? 2 : 1;
             const StreamShape sh = stream_shape(c, rows, g[i].dual ? 2 * I : g[i].N, g[i].K, terms,
                                                 g[i].dual && stream_fuses(c, rows, I, g[i].K, terms));
@@ -2526,8 +2540,7 @@ void launch_prefill_layers(const Model &m, int32_t pos0, int32_t n) {
                              t.f16_attn);
         hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n), dim3(norm_threads(n)), 0, m.stream, w.x, w.qkv, so, (size_t)n * h,
                            m.norm_mlp[l], w.xn, t.f16_xg ? nullptr : xn_lo, h, c.rms_eps, to, (int)t.f16_xg);
-        if (n < (h % kRingBK == 0 ? ring_min_rows(t.gu_two) : kSmallRows + 1)) {  // small chunk: gate/up as a plain split-K
-                                                                           // GEMM over all 2I rows, SwiGLU in the consumer
+        if (n < (h % kRingBK == 0 ? ring_min_rows(t.gu_two) : kSmallRows + 1)) {
             gate_up_short(m, w.xn, t.f16_xg ? nullptr : xn_lo, t.f16_xg ? m.wgu16[l] : m.wgu[l], n, t.f16_xg, t.f16_act);
         } else {
             gemm<true>(m, w.xn, t.gu_two ? xn_lo : nullptr, h, t.f16_xg ? m.wgu16[l] : m.wgu[l], n, I, h, w.act, act_lo, I,

@@ -101,7 +101,8 @@ constexpr int kDefaultLongTerms = kTermAll;
 // Passes of at least this many rows take the ring GEMMs, shorter ones the weight-streaming kernel.  Time of a pass of
 // four layers on 512 cached keys, streaming against ring kernel, at the 1.5B / 7B / 32B shapes -- two bf16 terms: 84 rows
 // 452 : 432, 884 : 912, 1354 : 1358 us; 96 rows 460 : 443, 908 : 925, 1390 : 1381 us; above, a fourth activation tile of two
-// terms made the streaming kernel 12-14 % the slower one (144 rows 612 : 478, 1265 : 1087 us at 1.5B and 7B).
+// terms, last timed in a form without loading waves of its own, was 16-28 % slower (144 rows 612 : 478, 1265 : 1087 us at
+// 1.5B and 7B).
 // One term (fp16 operands): 132 rows 468 : 473, 905 : 949, 1404 : 1426 us; 160 rows 492 : 480, 946 : 931, 1458 : 1461 us.
 constexpr int kRingMinRows = 97;       // two bf16 terms
 constexpr int kRingMinRowsFast = 161;  // one term: ST_PREFILL_FAST, or the fp16 operand mode

@@ -202,8 +202,8 @@ void launch_trigger_scan(const st_trigger_rule &rule, const int32_t *tokens, int
 // ---------------------------------------------------------------------------------------
 // The scan for callers that cannot allocate device memory: the result staging (count + positions) belongs to the library --
 // pinned host memory the kernel writes straight into, so that no copy follows it (4608 tokens with their call: 33.5 us with a
-// device array and a copy, 22.8 us this way; 18000 tokens 49 and 35 us).  One per GPU the library has been called on, allocated by the first call, held
-// until the process ends.  Where it cannot be had, a file-scope device array and a copy take its place.
+// device array and a copy, 22.8 us this way; 18000 tokens 49 and 35 us).  One per GPU the library has been called on, allocated
+// by the first call, held until the process ends.  Where it cannot be had, a file-scope device array and a copy take its place.
 // ---------------------------------------------------------------------------------------
 static __device__ __align__(256) int32_t scratch[1 + ST_SCAN_STATIC_MAX_CAP];
 
@@ -253,12 +253,13 @@ using namespace st;
 extern "C" int st_trigger_scan_static(const st_trigger_rule *rule, const int32_t *tokens, int32_t lo, int32_t hi,
                                       int32_t *positions, int32_t cap, int32_t *n_found, void *stream) {
     if (!rule || !rule->kw_bitmap || !tokens || !n_found) return fail(ST_EINVAL, "rule, bitmap, tokens or n_found is NULL");
-    if (rule->window < 1 || rule->window > ST_MAX_SCAN_WINDOW) return fail(ST_EINVAL, "window must be in [1, %d]", ST_MAX_SCAN_WINDOW);
+    if (rule->window < 1 || rule->window > ST_MAX_SCAN_WINDOW)
+        return fail(ST_EINVAL, "window must be in [1, %d]", ST_MAX_SCAN_WINDOW);
     if (rule->window >= 2 && !rule->delim_bitmap) return fail(ST_EINVAL, "a window above 1 needs a delimiter bitmap");
     if (rule->vocab <= 0) return fail(ST_EINVAL, "rule vocab must be positive");
     if (cap < 0 || (cap > 0 && !positions)) return fail(ST_EINVAL, "cap < 0, or positions is NULL with cap > 0");
     if (cap > ST_SCAN_STATIC_MAX_CAP)
-        return fail(ST_ERANGE, "cap %d exceeds the static staging array (%d positions)", cap, ST_SCAN_STATIC_MAX_CAP);
+        return fail(ST_ERANGE, "cap %d exceeds the staging (%d positions)", cap, ST_SCAN_STATIC_MAX_CAP);
     if (lo < 0 || hi < lo) return fail(ST_ERANGE, "bad range [%d,%d)", lo, hi);
     ScanStage stage;
     if (int rc = scan_stage(&stage)) return rc;

@@ -18,8 +18,8 @@ def test_scans_against_a_runtime_of_our_own(tmp_path):
         from paper_2504_12329_amd import build
         build.build()
     exe = str(tmp_path / "scan_driver")
-    subprocess.run(["hipcc", "--offload-arch=gfx950", "-O1", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-                    os.path.join(ROOT, "tests", "host", "scan_driver.cpp"), "-o", exe, "-L" + PKG, "-lst", "-Wl,-rpath," + PKG,
-                    "-rdynamic"], check=True, capture_output=True)
+    subprocess.run(["hipcc", "--offload-arch=gfx950", "-O1", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+                    "-packed-fp32-ops", os.path.join(ROOT, "tests", "host", "scan_driver.cpp"), "-o", exe, "-L" + PKG, "-lst",
+                    "-Wl,-rpath," + PKG, "-rdynamic"], check=True, capture_output=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "ok" in r.stdout, r.stdout + r.stderr

@@ -1,5 +1,5 @@
-"""The trigger scan for callers that cannot allocate device memory (st_trigger_scan_static: staging in a static
-device array inside the library) against st_trigger_scan on the same inputs, through the C ABI: two calls in a row,
+"""The trigger scan for callers that cannot allocate device memory (st_trigger_scan_static: staging that
+belongs to the library) against st_trigger_scan on the same inputs, through the C ABI: two calls in a row,
 the second on a smaller input, so that nothing of the first call's staging contents may leak into the second."""
 import numpy as np
 import pytest
